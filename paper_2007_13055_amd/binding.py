@@ -1,4 +1,7 @@
-"""ctypes binding for libbsr_spmm.so: same names as the C entry points, marshalling only."""
+"""Binding for libbsr_spmm.so: same names as the C entry points, marshalling only.
+
+The products (bsr_spmm, bsr_spmm_ex, bsr_spmm_static, bsr_sddmm) go through the native module _binding, whose calls cost
+about what the launch itself does; everything called once per matrix goes through ctypes."""
 from __future__ import annotations
 
 import ctypes
@@ -14,6 +17,7 @@ PATH_AUTO, PATH_WAVE, PATH_MFMA = 0, 1, 2
 _DTYPE_CODE = {"f32": BSR_F32, "f16": BSR_F16, "bf16": BSR_BF16}
 
 _lib = None
+_native = None                             # the module _binding, bound to _lib
 
 
 class BsrError(RuntimeError):
@@ -64,7 +68,16 @@ def load_library():
               "bsr_query_path", "bsr_scratch_size", "bsr_set_scratch", "bsr_tune", "bsr_tune_result",
               "bsr_transpose_pattern", "bsr_transpose_values", "bsr_sddmm"):
         getattr(lib, f).restype = ctypes.c_int
-    _lib = lib
+    global _native
+    import torch                           # noqa: F401  (_binding links to torch's libraries)
+    try:
+        from . import _binding
+    except ImportError as e:
+        raise RuntimeError(f"the native module _binding is missing or does not load ({e}): build it with "
+                           "`python -m paper_2007_13055_amd.build`") from e
+    _binding.bind(*(ctypes.cast(f, vp).value for f in (lib.bsr_spmm_ex, lib.bsr_spmm_static, lib.bsr_sddmm,
+                                                       lib.bsr_scratch_size)), BsrError)
+    _native, _lib = _binding, lib
     return lib
 
 
@@ -108,6 +121,8 @@ class BsrMatrix:
         self.handle, self.n, self.k, self.bs_r, self.bs_c, self.dtype = handle, n, k, bs_r, bs_c, dtype
         self._tensors = tensors            # block_data, block_indices, index_pointer, workspace (device)
         self._scratch = None               # device scratch lent to the handle (see ensure_scratch)
+        nnzb = int(tensors[0].shape[0]) if tensors[0].dim() == 3 else 0
+        self._core = _native.Core(handle.value, n, k, nnzb, bs_r, bs_c, _DTYPE_CODE[dtype])   # what the calls read
 
     @property
     def block_data(self):
@@ -123,9 +138,11 @@ class BsrMatrix:
             st = load_library().bsr_set_scratch(self.handle, self._scratch.data_ptr(), self._scratch.numel())
             if st != 0:
                 raise BsrError(st, "bsr_set_scratch")
+            self._core.lent(self._scratch.numel())
 
     def close(self):
         if self.handle:
+            self._core.closed()
             load_library().bsr_destroy(self.handle)
             self.handle = None
 
@@ -219,27 +236,11 @@ def bsr_create_transposed(n, k, block_data, block_indices, index_pointer, dtype=
 
 def bsr_spmm_ex(W: BsrMatrix, X, Y=None, y_dtype=None, path=PATH_AUTO):
     """Y = X * W^T on torch's current stream; X (m, k) device tensor of W's dtype.  Returns Y."""
-    import torch
-    if X.dim() != 2 or X.shape[1] != W.k:
-        raise ValueError("X must be (m, k)")
-    if _dtype_name(X) != W.dtype or not X.is_contiguous():
-        raise ValueError("X must be contiguous and of W's dtype")
-    y_dtype = y_dtype or W.dtype
-    m = int(X.shape[0])
-    W.ensure_scratch(m)
-    if Y is None:
-        Y = torch.empty((m, W.n), dtype=_torch_dtype(y_dtype), device=X.device)
-    elif tuple(Y.shape) != (m, W.n) or _dtype_name(Y) != y_dtype or not Y.is_contiguous():
-        raise ValueError("Y must be a contiguous (m, n) tensor of y_dtype")
-    st = load_library().bsr_spmm_ex(W.handle, m, X.data_ptr(), Y.data_ptr(), _DTYPE_CODE[y_dtype], int(path),
-                                    torch.cuda.current_stream().cuda_stream)
-    if st != 0:
-        raise BsrError(st, "bsr_spmm")
-    return Y
+    return _native.spmm(W, W._core, X, Y, y_dtype, path)
 
 
 def bsr_spmm(W: BsrMatrix, X, Y=None, y_dtype=None):
-    return bsr_spmm_ex(W, X, Y, y_dtype, PATH_AUTO)
+    return _native.spmm(W, W._core, X, Y, y_dtype, PATH_AUTO)
 
 
 STATIC_SCRATCH_BYTES = 8 << 20
@@ -248,17 +249,7 @@ STATIC_SCRATCH_BYTES = 8 << 20
 def bsr_spmm_static(W: BsrMatrix, X, Y):
     """bsr_spmm for thin-block W on the library's built-in scratch array: nothing is allocated or lent, so Y
     must be given.  X (m, k) fp32, Y (m, n) fp32, both contiguous device tensors.  Returns Y."""
-    import torch
-    if X.dim() != 2 or X.shape[1] != W.k or _dtype_name(X) != W.dtype or not X.is_contiguous():
-        raise ValueError("X must be a contiguous (m, k) tensor of W's dtype")
-    m = int(X.shape[0])
-    if tuple(Y.shape) != (m, W.n) or _dtype_name(Y) != "f32" or not Y.is_contiguous():
-        raise ValueError("Y must be a contiguous (m, n) fp32 tensor")
-    st = load_library().bsr_spmm_static(W.handle, m, X.data_ptr(), Y.data_ptr(), BSR_F32,
-                                        torch.cuda.current_stream().cuda_stream)
-    if st != 0:
-        raise BsrError(st, "bsr_spmm_static")
-    return Y
+    return _native.spmm_static(W._core, X, Y)
 
 
 def bsr_tune(W: BsrMatrix, X, Y=None, y_dtype=None, trials: int = 20):
@@ -299,24 +290,7 @@ def bsr_sddmm(W: BsrMatrix, G, X, D=None, d_dtype=None, lend_scratch=True):
     """D[p] = G[:, block-row of p]^T @ X[:, block-column of p] for every stored block of W (the gradient
     of the block values); G (m, n), X (m, k) device tensors of W's dtype.  Returns D (nnzb, bs_r, bs_c).
     lend_scratch: lend the handle the scratch its thin-block kernel wants (as bsr_spmm does)."""
-    import torch
-    if G.dim() != 2 or X.dim() != 2 or G.shape[0] != X.shape[0] or G.shape[1] != W.n or X.shape[1] != W.k:
-        raise ValueError("G must be (m, n) and X (m, k)")
-    if _dtype_name(G) != W.dtype or _dtype_name(X) != W.dtype or not G.is_contiguous() or not X.is_contiguous():
-        raise ValueError("G and X must be contiguous and of W's dtype")
-    d_dtype = d_dtype or W.dtype
-    if lend_scratch:
-        W.ensure_scratch(int(G.shape[0]))
-    nnzb = int(W.block_data.shape[0]) if W.block_data.dim() == 3 else 0
-    if D is None:
-        D = torch.empty((nnzb, W.bs_r, W.bs_c), dtype=_torch_dtype(d_dtype), device=G.device)
-    elif tuple(D.shape) != (nnzb, W.bs_r, W.bs_c) or _dtype_name(D) != d_dtype or not D.is_contiguous():
-        raise ValueError("D must be a contiguous (nnzb, bs_r, bs_c) tensor of d_dtype")
-    st = load_library().bsr_sddmm(W.handle, int(G.shape[0]), G.data_ptr(), X.data_ptr(), D.data_ptr(),
-                                  _DTYPE_CODE[d_dtype], torch.cuda.current_stream().cuda_stream)
-    if st != 0:
-        raise BsrError(st, "bsr_sddmm")
-    return D
+    return _native.sddmm(W, W._core, G, X, D, d_dtype, lend_scratch)
 
 
 def bsr_scratch_size(W: BsrMatrix, m: int) -> int:

@@ -1,10 +1,12 @@
-"""Compile the HIP sources under csrc/ into libbsr_spmm.so (in-tree, gfx950 only)."""
+"""Compile the HIP sources under csrc/ into libbsr_spmm.so and the native module of the Python binding
+(csrc/bsr_binding.cpp, host code) into _binding.so (in-tree, gfx950 only)."""
 from __future__ import annotations
 
 import glob
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -81,11 +83,35 @@ def _compile(src, force, plain=False):
     return obj
 
 
+BINDING_SRC = os.path.join(CSRC, "bsr_binding.cpp")
+BINDING = os.path.join(HERE, "_binding.so")
+
+
+def build_binding(force: bool = True) -> str:
+    """Compile the native module of the Python binding (host code, torch's headers and libraries)."""
+    import torch
+    if not force and os.path.exists(BINDING) and os.path.getmtime(BINDING) >= os.path.getmtime(BINDING_SRC):
+        return BINDING
+    t = os.path.dirname(os.path.abspath(torch.__file__))
+    includes = [os.path.join(t, "include"), os.path.join(t, "include", "torch", "csrc", "api", "include"),
+                os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"), sysconfig.get_paths()["include"]]
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-I", os.path.join(ROOT, "include"), *(x for i in includes for x in ("-isystem", i)), BINDING_SRC, "-o", BINDING,
+           "-L", os.path.join(t, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_hip", "-ltorch", "-ltorch_python"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed on bsr_binding.cpp:\n" + r.stderr)
+    return BINDING
+
+
 def build(force: bool = True, jobs: int = 4, plain: bool = False) -> str:
     """Compile every .hip file and link the shared library (plain: the checking build); returns its path."""
     os.makedirs(OBJDIR_PLAIN if plain else OBJDIR, exist_ok=True)
     with ThreadPoolExecutor(max_workers=jobs) as ex:
+        native = None if plain else ex.submit(build_binding, force)
         objs = list(ex.map(lambda s: _compile(s, force, plain), sources()))
+        if native:
+            native.result()
     lib = LIB_PLAIN if plain else LIB
     r = subprocess.run(["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-fno-gpu-rdc",
                         "-Wno-unused-command-line-argument", "-o", lib, *objs],
