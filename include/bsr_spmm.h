@@ -247,6 +247,18 @@ bsr_status bsr_sddmm(const bsr_matrix* W, int64_t m, const void* G_dev, const vo
                      bsr_dtype d_dtype, void* hip_stream);
 
 /*
+ * bsr_sddmm() with memory for this one call: a W of few blocks keeps all CUs busy only if the rows of G and X are
+ * split, and the partial results (fp32) of the splits need a place until they are added.
+ *   bsr_sddmm_workspace_size  bytes a product with m rows would use (0: none); multiple of 256
+ *   workspace_dev             DEVICE, 16-byte aligned, or NULL; overwritten.  With fewer bytes than that the rows are
+ *                             not split (the result is as good, the call slower).  Calls with memory of their own may
+ *                             run concurrently on one handle.
+ */
+bsr_status bsr_sddmm_workspace_size(const bsr_matrix* W, int64_t m, size_t* bytes);
+bsr_status bsr_sddmm_ws(const bsr_matrix* W, int64_t m, const void* G_dev, const void* X_dev, void* D_dev,
+                        bsr_dtype d_dtype, void* workspace_dev, size_t workspace_bytes, void* hip_stream);
+
+/*
  * bsr_spmm() for callers that can neither allocate nor lend device memory: code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc.  (No passage of the paper defines this call; it is
  * the product of bsr_spmm_ex(..., BSR_PATH_MFMA, ...) for the one kernel family that needs per-call scratch.)

@@ -75,8 +75,8 @@ def load_library():
     except ImportError as e:
         raise RuntimeError(f"the native module _binding is missing or does not load ({e}): build it with "
                            "`python -m paper_2007_13055_amd.build`") from e
-    _binding.bind(*(ctypes.cast(f, vp).value for f in (lib.bsr_spmm_ex, lib.bsr_spmm_static, lib.bsr_sddmm,
-                                                       lib.bsr_scratch_size)), BsrError)
+    _binding.bind(*(ctypes.cast(f, vp).value for f in (lib.bsr_spmm_ex, lib.bsr_spmm_static, lib.bsr_sddmm_ws,
+                                                       lib.bsr_scratch_size, lib.bsr_sddmm_workspace_size)), BsrError)
     _native, _lib = _binding, lib
     return lib
 

@@ -18,7 +18,8 @@ namespace {
 
 bsr_status (*g_spmm)(const bsr_matrix*, int64_t, const void*, void*, bsr_dtype, bsr_path, void*) = nullptr;
 bsr_status (*g_spmm_static)(const bsr_matrix*, int64_t, const void*, void*, bsr_dtype, void*) = nullptr;
-bsr_status (*g_sddmm)(const bsr_matrix*, int64_t, const void*, const void*, void*, bsr_dtype, void*) = nullptr;
+bsr_status (*g_sddmm)(const bsr_matrix*, int64_t, const void*, const void*, void*, bsr_dtype, void*, size_t, void*) = nullptr;
+bsr_status (*g_sddmm_workspace)(const bsr_matrix*, int64_t, size_t*) = nullptr;
 bsr_status (*g_scratch_size)(const bsr_matrix*, int64_t, size_t*) = nullptr;
 PyObject* g_error = nullptr;                          // BsrError(status, where)
 
@@ -247,10 +248,15 @@ PyObject* sddmm(PyObject*, PyObject* const* a, Py_ssize_t nargs)
     }
     const void *gp = G->data_ptr(), *xp = X->data_ptr();
     void* dp = D->data_ptr();
+    // this call's workspace: from torch's allocator, which hands it on in stream order once the call has returned
+    size_t ws_bytes = 0;
+    at::Tensor ws;
+    if (g_sddmm_workspace(c->handle, m, &ws_bytes) == BSR_OK && ws_bytes > 0)
+        ws = at::Tensor(at::detail::empty_cuda({(int64_t)ws_bytes}, at::kByte, G->device(), std::nullopt));
     bsr_status st;
     {
         pybind11::gil_scoped_release no_gil;
-        st = g_sddmm(c->handle, m, gp, xp, dp, (bsr_dtype)d_code, stream());
+        st = g_sddmm(c->handle, m, gp, xp, dp, (bsr_dtype)d_code, ws_bytes ? ws.data_ptr() : nullptr, ws_bytes, stream());
     }
     if (st != BSR_OK) return failed(st, "bsr_sddmm");
     if (out == Py_None) return THPVariable_Wrap(std::move(fresh));
@@ -259,16 +265,17 @@ PyObject* sddmm(PyObject*, PyObject* const* a, Py_ssize_t nargs)
     END_HANDLE_TH_ERRORS
 }
 
-// bind(address of bsr_spmm_ex, bsr_spmm_static, bsr_sddmm, bsr_scratch_size, BsrError)
+// bind(address of bsr_spmm_ex, bsr_spmm_static, bsr_sddmm_ws, bsr_scratch_size, bsr_sddmm_workspace_size, BsrError)
 PyObject* bind(PyObject*, PyObject* args)
 {
-    unsigned long long f[4];
+    unsigned long long f[5];
     PyObject* error = nullptr;
-    if (!PyArg_ParseTuple(args, "KKKKO", &f[0], &f[1], &f[2], &f[3], &error)) return nullptr;
+    if (!PyArg_ParseTuple(args, "KKKKKO", &f[0], &f[1], &f[2], &f[3], &f[4], &error)) return nullptr;
     g_spmm = reinterpret_cast<decltype(g_spmm)>(f[0]);
     g_spmm_static = reinterpret_cast<decltype(g_spmm_static)>(f[1]);
     g_sddmm = reinterpret_cast<decltype(g_sddmm)>(f[2]);
     g_scratch_size = reinterpret_cast<decltype(g_scratch_size)>(f[3]);
+    g_sddmm_workspace = reinterpret_cast<decltype(g_sddmm_workspace)>(f[4]);
     Py_INCREF(error);
     Py_XDECREF(g_error);
     g_error = error;

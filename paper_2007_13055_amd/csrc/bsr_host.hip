@@ -41,14 +41,15 @@ size_t plan_bytes(int64_t R, int64_t nnzb, int32_t bs_r, int32_t bs_c, int64_t k
     // small blocks instead: tile-row descriptors (at most one per block-row) and 20 bytes per tile entry
     // (at most one per stored block)
     const size_t per_row = 4 + 8 * (size_t)kRowDescWords + 4 + 16 * (size_t)kStripeChunkPairs + 16;
-    // + 32 bytes per stored block for the sampled product: its block-row (4), runs (8), tiles (16 + 4)
-    size_t b = per_row * (size_t)R + 52 * (size_t)nnzb + 4096 + kItemSlots * item_table_bytes(R);
+    // + 4 bytes per stored block for the sampled product: its block-row
+    size_t b = per_row * (size_t)R + 24 * (size_t)nnzb + 4096 + kItemSlots * item_table_bytes(R);
     // row-group kernel (64x64 blocks): its group descriptors and window records
     b += sizeof(int32_t) * group_plan_words(R, bs_r, bs_c, nnzb);
     // thin blocks: the phase positions of every block-row
     b += sizeof(int32_t) * thinrow_plan_words(R, k, bs_r, bs_c);
     // blocks of one row: the pairs by block-column and their range positions
     b += sizeof(int32_t) * wide_plan_words(R, k, nnzb, bs_r, bs_c);
+    b += sizeof(int32_t) * sddmm_slab_plan_words(k, bs_r, bs_c, nnzb);
     b += 256;                                         // debug mode's result words
     return (b + 255) & ~(size_t)255;
 }
@@ -78,6 +79,7 @@ tune_opts read_tune_env()
             else if (key == "mt") t.mt = val;
             else if (key == "a") t.a = val;
             else if (key == "b") t.b = val;
+            else if (key == "sd") t.sd = val;
         }
         pos = end + 1;
     }
@@ -401,74 +403,6 @@ bsr_status bsr_create(bsr_matrix** out, int64_t n, int64_t k, int32_t bs_r, int3
             for (int32_t p = index_pointer_host[r]; p < index_pointer_host[r + 1]; ++p) W->staging[at + (size_t)p] = (int32_t)r;
         W->block_row = W->row_order + at;
         words = (at + (size_t)nnzb + 63) & ~(size_t)63;
-        // runs of the sampled product: ceil(count / NB) runs per block-row, lengths differing by at most 1
-        const int NB = sddmm_run_blocks(bs_r, bs_c, dtype);
-        const size_t run_at = words;
-        W->staging.resize(run_at + 2 * (size_t)nnzb + 64, 0);
-        size_t q = 0;
-        for (int64_t r = 0; r < R; ++r) {
-            const int32_t first = index_pointer_host[r], cnt = index_pointer_host[r + 1] - first;
-            const int32_t parts = (cnt + NB - 1) / NB;
-            for (int32_t j = 0, p = first; j < parts; ++j, ++q) {
-                const int32_t len = cnt / parts + (j < cnt % parts ? 1 : 0);
-                W->staging[run_at + 2 * q] = p;
-                W->staging[run_at + 2 * q + 1] = len;
-                p += len;
-            }
-        }
-        W->sd_runs = W->row_order + run_at;
-        W->sd_n_runs = (int32_t)q;
-        words = (run_at + 2 * q + 63) & ~(size_t)63;
-        // tiles of the sampled product, for the shapes its matrix-core kernel takes: a stored block goes
-        // to the first tile of its (super-row, column group) whose position is free (a duplicate opens
-        // another tile); tiles of a super-row by column group, super-rows in order
-        int SR = 1, LC = 1;
-        sddmm_tile_dims(bs_r, bs_c, dtype, &SR, &LC);
-        const bool mfma_shape = (bs_r == 16 || bs_r == 32 || bs_r == 64) && (bs_c == 16 || bs_c == 32 || bs_c == 64);
-        if (mfma_shape && SR * LC > 1 && SR * LC <= 16) {
-            struct tile { int32_t cg; uint32_t mask; int32_t p[16]; };
-            const size_t tile_at = words;
-            W->staging.resize(tile_at + 5 * (size_t)nnzb + 128, 0);
-            std::vector<int32_t> plist;
-            plist.reserve((size_t)nnzb);
-            std::vector<tile> list;
-            size_t nt = 0;
-            for (int64_t sr = 0; sr * SR < R; ++sr) {
-                list.clear();
-                for (int a = 0; a < SR && sr * SR + a < R; ++a) {
-                    const int64_t r = sr * SR + a;
-                    for (int32_t p = index_pointer_host[r]; p < index_pointer_host[r + 1]; ++p) {
-                        const int32_t cg = block_indices_host[p] / LC, pos = a * LC + block_indices_host[p] % LC;
-                        tile* slot = nullptr;
-                        for (auto& t : list)
-                            if (t.cg == cg && !((t.mask >> pos) & 1u)) { slot = &t; break; }
-                        if (!slot) {
-                            list.push_back(tile{cg, 0u, {}});
-                            slot = &list.back();
-                        }
-                        slot->mask |= 1u << pos;
-                        slot->p[pos] = p;
-                    }
-                }
-                std::stable_sort(list.begin(), list.end(), [](const tile& x, const tile& y) { return x.cg < y.cg; });
-                for (const tile& t : list) {
-                    int32_t* d = W->staging.data() + tile_at + 4 * nt++;
-                    d[0] = (int32_t)sr;
-                    d[1] = t.cg;
-                    d[2] = (int32_t)plist.size();
-                    d[3] = (int32_t)t.mask;
-                    for (int pos = 0; pos < SR * LC; ++pos)
-                        if ((t.mask >> pos) & 1u) plist.push_back(t.p[pos]);
-                }
-            }
-            const size_t plist_at = (tile_at + 4 * nt + 63) & ~(size_t)63;
-            W->staging.resize(plist_at + plist.size() + 64, 0);
-            std::copy(plist.begin(), plist.end(), W->staging.begin() + (ptrdiff_t)plist_at);
-            W->sd_tiles = W->row_order + tile_at;
-            W->sd_plist = W->row_order + plist_at;
-            W->sd_n_tiles = (int32_t)nt;
-            words = (plist_at + plist.size() + 63) & ~(size_t)63;
-        }
     }
     build_group_plan(W, index_pointer_host, block_indices_host, &words);
     build_thinrow_plan(W, index_pointer_host, block_indices_host, &words);
@@ -480,6 +414,14 @@ bsr_status bsr_create(bsr_matrix** out, int64_t n, int64_t k, int32_t bs_r, int3
         words += kItemSlots * W->item_capacity * kRowDescWords;
         W->debug_out = const_cast<int32_t*>(W->row_order) + words;
         words += 64;
+        // the sampled product's groups: room for them, and the pattern they are built from when first wanted
+        W->sl_words = sddmm_slab_plan_words(k, bs_r, bs_c, nnzb);
+        if (W->sl_words) {
+            W->sl_base = const_cast<int32_t*>(W->row_order) + words;
+            words += W->sl_words;
+            W->sl_indptr.assign(index_pointer_host, index_pointer_host + R + 1);
+            W->sl_indices.assign(block_indices_host, block_indices_host + nnzb);
+        }
     }
     // the plan must fit what bsr_workspace_size promised (its bound is per block-row and per stored block)
     if (sizeof(int32_t) * words > workspace_bytes) { delete W; return BSR_ERR_WORKSPACE; }
@@ -510,7 +452,7 @@ bsr_status bsr_create(bsr_matrix** out, int64_t n, int64_t k, int32_t bs_r, int3
 void bsr_destroy(bsr_matrix* W)
 {
     if (!W) return;
-    std::vector<hipEvent_t> events{W->plan_uploaded};
+    std::vector<hipEvent_t> events{W->plan_uploaded, W->sl.uploaded};
     for (const auto& t : W->item_tables) events.push_back(t.uploaded);
     for (hipEvent_t e : events) {                     // uploads read the handle's host buffers
         if (!e) continue;

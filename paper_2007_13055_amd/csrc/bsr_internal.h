@@ -31,8 +31,9 @@ constexpr int kItemSlots = 4;                     // k-split work-item tables a 
 //            started first; stripe a = block-row groups; thin a = groups of 4 blocks in flight
 //            thin blocks: variant 1 = transposed copy in scratch + gather, 2 = rows of X staged in LDS
 //            (a = slots per wavefront)
+//   sd       sampled product: 1 a workgroup per block, 2 groups of blocks that share slabs
 struct tune_opts {
-    int variant = 0, nw = 0, mt = 0, a = 0, b = 0;
+    int variant = 0, nw = 0, mt = 0, a = 0, b = 0, sd = 0;
     bool from_env = false;                   // BSR_SPMM_TUNE is set: it overrides what bsr_tune() remembered
 };
 
@@ -120,16 +121,25 @@ struct bsr_matrix {
     // byte offsets of the tile's blocks in block_data, [entries][4] (2^31: no block there), and its
     // tile-column, [entries].
     const int32_t* block_row = nullptr;      // device, [nnzb]: block-row of every stored block (sampled product)
-    // Runs of the sampled product: every block-row cut into runs of at most sddmm_run_blocks() stored
-    // blocks of about equal length, in storage order; [sd_n_runs][2] = {first block, blocks}.
-    const int32_t* sd_runs = nullptr;
-    int32_t sd_n_runs = 0;
-    // Tiles of the sampled product (block shapes whose pieces of G or X are narrower than 128 bytes, see
-    // sddmm_tile_dims): [sd_n_tiles][4] = {super-row, column group, first entry in sd_plist, position mask};
-    // sd_plist holds the stored-block numbers of a tile's set positions in position order.
-    const int32_t* sd_tiles = nullptr;
-    const int32_t* sd_plist = nullptr;
-    int32_t sd_n_tiles = 0;
+    // Groups of the sampled product (bsr_sddmm_slab.hip; block sides 8, 16, 32 or 64): per group a header of 16
+    // words {slabs, of G, first chunk, chunks, the slabs' first columns[12]}; per chunk 4 words {byte offsets of its
+    // rows of tiles, of its columns of tiles (16 bits each), first tile | tiles << 28}; per tile the elements of D at
+    // which its four quadrants start (-1: not stored).
+    // Built by the first sampled product that wants it (a handle that only multiplies never pays for it), from host
+    // copies of the pattern, into sl_words words of the workspace that bsr_create set aside.
+    std::vector<int32_t> sl_indptr, sl_indices;
+    int32_t* sl_base = nullptr;              // device
+    size_t sl_words = 0;
+    struct slab_plan {
+        bool built = false, sent = false;
+        std::vector<int32_t> host;           // headers, chunks, tiles; kept for the asynchronous upload
+        size_t chunks_at = 0, tiles_at = 0;  // words
+        int32_t groups = 0, n_tiles = 0, lds = 0;
+        hipEvent_t uploaded = nullptr;
+        std::atomic<bool> landed{false};
+    };
+    mutable std::mutex sl_mu;
+    mutable slab_plan sl;
     const int32_t* sb_desc = nullptr;
     const int32_t* sb_entries = nullptr;
     const int32_t* sb_cols = nullptr;
@@ -166,18 +176,6 @@ tune_opts read_tune_env();
 // synchronisation); BSR_OK when the handle is not in debug mode or the stream is being captured.
 bsr_status debug_check_device_arrays(const bsr_matrix* W, hipStream_t stream);
 uint64_t debug_plan_sum(const int32_t* words, size_t n);
-
-// Stored blocks of one block-row that a workgroup of the sampled product takes together (they share
-// the piece of G): 4 while a block is at most 2 KiB, else 2.
-// Tile of the sampled product: sr adjacent block-rows x lc adjacent block-columns, as many as make a
-// 128-byte line of a row of G and of X (1 when a block's piece is a line or more).
-inline void sddmm_tile_dims(int bs_r, int bs_c, bsr_dtype t, int* sr, int* lc)
-{
-    const int s = t == BSR_F32 ? 4 : 2;
-    *sr = bs_r * s >= 128 ? 1 : 128 / (bs_r * s);
-    *lc = bs_c * s >= 128 ? 1 : 128 / (bs_c * s);
-}
-inline int sddmm_run_blocks(int bs_r, int bs_c, bsr_dtype t) { return bs_r * bs_c * (t == BSR_F32 ? 4 : 2) <= 2048 ? 4 : 2; }
 
 // Each returns BSR_OK, BSR_ERR_UNSUPPORTED (shape not covered by that family) or BSR_ERR_HIP.
 bsr_status launch_wave(const spmm_args& a, const tune_opts& t);
@@ -233,6 +231,13 @@ size_t wide_plan_words(int64_t R, int64_t k, int64_t nnzb, int32_t bs_r, int32_t
 bsr_status launch_mfma_small(const spmm_args& a, const tune_opts& t);   // bs_r, bs_c in {8,16}, not both 16
 bool mfma_small_supports(const bsr_matrix* W);
 size_t mfma_thin_scratch_bytes(const bsr_matrix* W, int64_t m);   // bytes of the transposed copy of X
+// Sampled product by groups of stored blocks that share 128-byte wide slabs of G and X.
+bool sddmm_slab_supports(const bsr_matrix* W, int64_t m);
+void build_sddmm_slab_plan(const bsr_matrix* W);                    // into W->sl (once; caller holds W->sl_mu)
+size_t sddmm_slab_plan_words(int64_t k, int32_t bs_r, int32_t bs_c, int64_t nnzb);
+size_t sddmm_slab_workspace(const bsr_matrix* W, int64_t m);        // bytes of partial results it would like
+bsr_status launch_sddmm_slab(const bsr_matrix* W, int m, const void* G, const void* X, void* D, bsr_dtype d_dtype, void* ws,
+                             size_t ws_bytes, hipStream_t stream);
 // XT[c][i] = X[i][c], rows of XT (m rounded up to 4) floats apart
 bsr_status launch_transpose_f32(const float* X, float* XT, int m, int k, hipStream_t stream);
 
