@@ -407,8 +407,9 @@ bsr_status launch_sddmm_shape(const bsr_matrix* W, int m, const void* G, const v
 // the reduction, at 15-18 TB/s over the whole chip and 3 us to begin with; the groups move each slab once for many
 // blocks, but their two launches cost 10 us.  Measured on bf16, m x (n, k): 16x16 4096 x (3072, 768) 1.9 GB of lines,
 // 21 us against 37; 32x32 2048 x (2048, 2048) 107 MB, 14.6 against 11.3; fp32 16x16 2000 x (1024, 1024) 314 MB,
-// 20.9 against 19.1.  Few blocks and many rows leave most CUs idle when a workgroup takes a block, while the groups
-// split the rows (29 64x64 blocks, 3903 rows: 17 us against 22).  8-wide blocks have no matrix-core kernel of their
+// 20.9 against 19.1.  Few blocks and many rows leave most CUs idle when a workgroup takes a block, 128 rows in 0.6 us
+// (fp32: 0.6, 0.9 and 2.8 us for blocks of 256, 1024 and 4096 elements, the matrix cores' time), while the groups
+// split the rows (29 fp16 64x64 blocks, 3903 rows: 14.8 us against 22).  8-wide blocks have no matrix-core kernel of their
 // own: 16-bit ones take the groups from 256 rows on (530 x (576, 384): 8.1 us against 11.0); fp32 ones, three
 // quarters of whose matrix-core tiles are padding, only when the lines are many.
 bool takes_slabs(const bsr_matrix* W, int64_t m)
@@ -418,7 +419,9 @@ bool takes_slabs(const bsr_matrix* W, int64_t m)
     const int s = W->dtype == BSR_F32 ? 4 : 2;
     const double lines = (double)W->nnzb * m * (std::max(128, W->bs_r * s) + std::max(128, W->bs_c * s));
     if (W->bs_r == 8 || W->bs_c == 8) return W->dtype == BSR_F32 ? m >= 512 && lines > 2e9 : m >= 256;
-    return lines > 350e6 || (W->nnzb <= 128 && m >= 3072);
+    const int elems = W->bs_r * W->bs_c;
+    const double alone = 3.0 + (double)m / 128 * (W->dtype != BSR_F32 || elems < 1024 ? 0.6 : elems < 4096 ? 0.9 : 2.8);
+    return lines > 350e6 || (W->nnzb <= 256 && alone > (W->nnzb <= 64 ? 13.0 : 17.0));
 }
 
 template <typename T, typename O>

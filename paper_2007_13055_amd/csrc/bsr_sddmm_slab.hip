@@ -351,11 +351,12 @@ __global__ __launch_bounds__(256) void bsr_sddmm_slab_sum(const float* __restric
 }
 
 // Splits of the rows for m rows: as many as give every CU one workgroup, each at least 4 steps (128 rows) long; at
-// most 16, beyond which adding up takes longer than is saved.
+// most 16, beyond which adding up takes longer than is saved (32 where all blocks together are 256 KiB or less).
 int sddmm_slab_splits(const bsr_matrix* W, int64_t m)
 {
     const int64_t steps = (m + kRows - 1) / kRows;
-    return (int)std::max<int64_t>(1, std::min<int64_t>({(int64_t)W->n_cu / std::max(W->sl.groups, 1), steps / 4, 16}));
+    const int most = W->nnzb * W->bs_r * W->bs_c <= 65536 ? 32 : 16;
+    return (int)std::max<int64_t>(1, std::min<int64_t>({(int64_t)W->n_cu / std::max(W->sl.groups, 1), steps / 4, (int64_t)most}));
 }
 
 template <typename T, typename O, int V, int CR, int CC, int NCH>
