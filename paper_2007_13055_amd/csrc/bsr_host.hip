@@ -466,12 +466,17 @@ void bsr_destroy(bsr_matrix* W)
 bsr_status bsr_query_path(const bsr_matrix* W, int64_t m, bsr_path* path_out)
 {
     if (!W || !path_out) return BSR_ERR_NULL;
-    // Matrix-core tiles are at least 16 rows of X tall: below that most of a tile is padding and
-    // the wavefront-reduction kernels (the paper's own regime, m <= 8) stream W once instead.
+    // Matrix-core tiles are 16 rows of X tall: below that most of a tile is padding, and the wavefront-reduction
+    // kernels (the paper's own regime, m <= 8) stream W once instead.  They start a wavefront per output column and
+    // group of rows, though, at about 11 cycles each per XCD, while the k-split kernel takes the same 3-5 us whatever m
+    // is: it wins from 9 rows on (8 x (1024, 1024): 3.2 against 3.4 us, 12 rows 3.8 against 3.4), and earlier once
+    // there are some 6000 wavefronts (8 x (5888, 2944): 7.8 against 5.4 us).
+    const bool square = mfma_supports(W);
+    const int64_t waves = W->n * (m > 8 ? (m + 7) / 8 : (m + 3) / 4);
+    if ((square && (m >= 9 || waves >= 6000)) || (mfma_small_supports(W) && m >= 16)) *path_out = BSR_PATH_MFMA;
     // Thin 16x1 fp32 blocks take the matrix-core path when the caller has lent enough scratch for
     // the transposed copy of X, or when their block-rows are stored in block-column order (one launch,
     // no scratch).
-    if ((mfma_supports(W) || mfma_small_supports(W)) && m >= 16) *path_out = BSR_PATH_MFMA;
     else if (mfma_thin_supports(W) && m >= 32 && W->scratch && W->scratch_bytes >= mfma_thin_scratch_bytes(W, m))
         *path_out = BSR_PATH_MFMA;
     else if (mfma_thinrow_supports(W) && m >= 16) *path_out = BSR_PATH_MFMA;   // no scratch: rows of X staged in LDS

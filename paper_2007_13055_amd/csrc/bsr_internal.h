@@ -26,7 +26,7 @@ constexpr int kItemSlots = 4;                     // k-split work-item tables a 
 // the settings bsr_tune() remembers per m.  Unset keys are 0 and mean "the library's own choice".
 //   variant  1 direct, 2 ksplit, 3 tile, 4 stripe, 5 row groups + tile  (matrix-core kernel variant)
 //   nw       wavefronts per workgroup      mt   MFMA tiles along m per wavefront (wave path: rows of X
-//            per wavefront; ksplit: 1 = 16-row, 2 = 32-row tiles)
+//            per wavefront; ksplit: 1 = 16-row, 2 = 32-row tiles, 3 = strips of 16 rows of the blocks)
 //   a, b     per-variant: ksplit a = blocks per wavefront; tile a = blocks in flight, b-1 = long rows
 //            started first; stripe a = block-row groups; thin a = groups of 4 blocks in flight
 //            thin blocks: variant 1 = transposed copy in scratch + gather, 2 = rows of X staged in LDS

@@ -88,8 +88,10 @@ struct ksplit_geom {
     static constexpr int REGION = ((STAGE > PART ? STAGE : PART) + 15) & ~15;   // LDS bytes per wavefront
 };
 
-template <typename T, typename O, int BS_R, int BS_C, int MM_>
-__global__ __launch_bounds__(512) void bsr_mfma_ksplit(const T* __restrict__ X, const T* __restrict__ data,
+// STR > 1: the stored blocks are STR * BS_R rows tall and the workgroup takes strip blockIdx.y of them -- few items
+// otherwise leave most CUs idle while a wavefront works through a whole block by itself.
+template <typename T, typename O, int BS_R, int BS_C, int MM_, int STR>
+__global__ __launch_bounds__(BS_R == 16 ? 1024 : 512) void bsr_mfma_ksplit(const T* __restrict__ X, const T* __restrict__ data,
                                                        const int32_t* __restrict__ indices,
                                                        const int32_t* __restrict__ row_desc, O* __restrict__ Y,
                                                        int m, int k, int n, int R, int per, int items)
@@ -140,7 +142,8 @@ __global__ __launch_bounds__(512) void bsr_mfma_ksplit(const T* __restrict__ X, 
 
     if (wave < nw && wave < cnt) {                     // this wavefront has at least one block
         // W of this block-row and the X rows of this m-tile as buffers: offsets past their ends read zero
-        const rsrc_t wrsrc = make_rsrc(data + (size_t)p0 * (BS_R * BS_C), cnt * BLK);
+        const int strip = STR > 1 ? (int)blockIdx.y * BLK : 0;
+        const rsrc_t wrsrc = make_rsrc(data + (size_t)p0 * (STR * BS_R * BS_C), cnt * (STR * BLK));
         const rsrc_t xrsrc = make_rsrc(X + (size_t)i_base * (size_t)k, min(MM, m - i_base) * k * S);
         // lane's pieces: W piece t is bytes t*1024 + lane*16 of the block; X piece t is 16 bytes of
         // row t*RPI + lane/LPR of the tile
@@ -148,7 +151,7 @@ __global__ __launch_bounds__(512) void bsr_mfma_ksplit(const T* __restrict__ X, 
 #pragma unroll
         for (int t = 0; t < NLW; ++t) {
             const unsigned b = (unsigned)(t * 1024 + lane * 16);
-            w_g[t] = b < (unsigned)BLK ? b : kDead;
+            w_g[t] = b < (unsigned)BLK ? b + (unsigned)strip : kDead;
             w_l[t] = (b / RBS) * P + (b % RBS);
         }
 #pragma unroll
@@ -166,7 +169,7 @@ __global__ __launch_bounds__(512) void bsr_mfma_ksplit(const T* __restrict__ X, 
         auto issue = [&](int s, int j) {
             const int c = j < kRowDescCols ? __builtin_amdgcn_readlane(dword, kRowDescColsAt + j) : indices[p0 + j];
 #pragma unroll
-            for (int t = 0; t < NLW; ++t) load_b128(gw[s][t], wrsrc, w_g[t] + (unsigned)j * BLK);
+            for (int t = 0; t < NLW; ++t) load_b128(gw[s][t], wrsrc, w_g[t] + (unsigned)j * (STR * BLK));
 #pragma unroll
             for (int t = 0; t < NLX; ++t) load_b128(gx[s][t], xrsrc, x_g[t] + (unsigned)c * RBS);
         };
@@ -248,32 +251,33 @@ __global__ __launch_bounds__(512) void bsr_mfma_ksplit(const T* __restrict__ X, 
         for (int w = 0; w < used; ++w)
             s += *reinterpret_cast<const f32x4*>(lds + (size_t)w * geo::REGION + ((size_t)i * LD + 4 * q) * 4);
         if (i_base + i < m)
-            store4<O>(Y + (size_t)(i_base + i) * (size_t)n + (size_t)r * BS_R + 4 * q, s.x, s.y, s.z, s.w);
+            store4<O>(Y + (size_t)(i_base + i) * (size_t)n + (size_t)(STR > 1 ? r * STR + (int)blockIdx.y : r) * BS_R + 4 * q, s.x, s.y, s.z, s.w);
     }
 }
 
-template <typename T, typename O, int BS_R, int BS_C, int MM>
+template <typename T, typename O, int BS_R, int BS_C, int MM, int STR = 1>
 bsr_status launch_ksplit_tile(const spmm_args& a, const tune_opts& tune)
 {
     typedef ksplit_geom<T, BS_R, BS_C, MM> geo;
     const bsr_matrix* W = a.W;
     const int m = (int)a.m, n = (int)W->n, k = (int)W->k, R = W->R;
     // 32-bit byte offsets inside a block-row's blocks and inside an m-tile's rows of X
-    if ((int64_t)W->max_row_blocks * geo::BLK >= ((int64_t)1 << 31) || (int64_t)MM * k * geo::S >= ((int64_t)1 << 31))
+    if ((int64_t)W->max_row_blocks * geo::BLK * STR >= ((int64_t)1 << 31) || (int64_t)MM * k * geo::S >= ((int64_t)1 << 31))
         return BSR_ERR_UNSUPPORTED;
     // wavefronts per workgroup: about `per` stored blocks each for the longest block-row; at most 8
-    // when every workgroup has a CU to itself, at most 4 up to four workgroups per CU and 2 beyond
-    // (starting wavefronts costs time too, about 11 cycles each per XCD, and with many workgroups the
-    // CUs are busy anyway), and no more than LDS has room for
+    // when every workgroup has a CU to itself (16 where the wavefront's tile is 16 rows of W), at most 4 up to four
+    // workgroups per CU and 2 beyond (starting wavefronts costs time too, about 11 cycles each per XCD, and with many
+    // workgroups the CUs are busy anyway), and no more than LDS has room for.  Strips carry less work each: twice that.
     const int64_t tiles = (m + MM - 1) / MM;
     int64_t blocks = tiles * R;
-    int per = tune.a > 0 ? tune.a : 2;
+    int per = tune.a > 0 ? tune.a : (STR == 4 && std::is_same<T, float>::value ? 1 : 2);
     int nw = (W->max_row_blocks + per - 1) / per;
-    const int nw_cap = blocks > 1024 ? 2 : (blocks > 256 ? 4 : 8);
+    int nw_cap = blocks > 1024 ? 2 : (blocks > 256 ? 4 : (blocks > 128 || BS_R > 16 ? 8 : 16));
+    if (STR > 1) nw_cap = blocks * STR <= 256 ? 16 : (blocks * STR <= (W->long_rows > 0 ? 4096 : 512) ? 8 : 4);
     nw = nw < 1 ? 1 : (nw > nw_cap ? nw_cap : nw);
-    if (tune.nw >= 1 && tune.nw <= 8) nw = tune.nw;
+    if (tune.nw >= 1 && tune.nw <= (BS_R == 16 ? 16 : 8)) nw = tune.nw;
     nw = std::min(nw, 160 * 1024 / geo::REGION);
-    if (blocks >= ((int64_t)1 << 31) || blocks * 64 * nw >= ((int64_t)1 << 32)) return BSR_ERR_SHAPE;
+    if (blocks >= ((int64_t)1 << 31) || blocks * STR * 64 * nw >= ((int64_t)1 << 32)) return BSR_ERR_SHAPE;
     // CU-balanced work-item table when there are more items than CUs (else every item has a CU to itself)
     const int32_t* table = W->row_desc;
     int items = 0;
@@ -284,12 +288,29 @@ bsr_status launch_ksplit_tile(const spmm_args& a, const tune_opts& tune)
     }
     const size_t lds = (size_t)nw * geo::REGION;
     static const hipError_t attr =
-        hipFuncSetAttribute(reinterpret_cast<const void*>(&bsr_mfma_ksplit<T, O, BS_R, BS_C, MM>),
+        hipFuncSetAttribute(reinterpret_cast<const void*>(&bsr_mfma_ksplit<T, O, BS_R, BS_C, MM, STR>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (attr != hipSuccess) return BSR_ERR_HIP;
-    hipLaunchKernelGGL((bsr_mfma_ksplit<T, O, BS_R, BS_C, MM>), dim3((unsigned)blocks), dim3(64 * nw), lds, a.stream,
+    hipLaunchKernelGGL((bsr_mfma_ksplit<T, O, BS_R, BS_C, MM, STR>), dim3((unsigned)blocks, STR), dim3(64 * nw), lds, a.stream,
                        (const T*)a.X, (const T*)W->data, W->indices, table, (O*)a.Y, m, k, n, R, per, items);
     return hipGetLastError() == hipSuccess ? BSR_OK : BSR_ERR_HIP;
+}
+
+// Blocks of 32 and 64 rows in strips of 16, a workgroup each, while there are few items: a block's whole height is
+// then up to four times the work for one wavefront while CUs idle.  Measured (16-row items; before -> after, us):
+// fp32 64x64, 40 x (832, 576) 5.4 -> 3.3, 256 x 4096^2 at 10 % 25.3 -> 18.6 (the matrix cores' time per block is what
+// a wavefront is bound by), 500 rows 32.7 -> 34.4; fp32 32x32 16 x 3072^2 4.5 -> 3.9, 128 rows even, 256 rows
+// 9.8 -> 11.0, but with a few long block-rows 256 x (6080, 3392) 39.9 -> 30.3; fp16 64x64 with long block-rows,
+// 16 x (1792, 6592) 13.1 -> 6.8, 125 rows 13.9 -> 10.7; bf16 64x64 4096^2 16 rows 4.6 -> 3.5, 40 rows 4.65 -> 4.4, 128
+// rows 5.1 -> 5.7.
+template <typename T>
+bool in_strips(const bsr_matrix* W, int64_t m)
+{
+    const int64_t wgs = (m + 15) / 16 * W->R * (W->bs_r / 16);
+    const bool uneven = W->long_rows > 0;
+    if (std::is_same<T, float>::value) return wgs <= (uneven || W->bs_r == 64 ? 6144 : 1024);
+    if (W->bs_r == 64) return wgs < 1024;
+    return wgs <= (uneven ? 1024 : 256);
 }
 
 // Rows of X per workgroup: 32 (the larger MFMA tile: every W block is fetched half as often) when
@@ -300,6 +321,7 @@ template <typename T, typename O, int BS_R, int BS_C>
 bsr_status launch_ksplit_shape(const spmm_args& a, const tune_opts& tune)
 {
     if constexpr (BS_R >= 32) {
+        if (tune.mt == 3 || (tune.mt == 0 && in_strips<T>(a.W, a.m))) return launch_ksplit_tile<T, O, 16, BS_C, 16, BS_R / 16>(a, tune);
         const int64_t items32 = (a.m + 31) / 32 * a.W->R;
         const bool slow16 = sizeof(T) == 2 && BS_C < 32;
         bool tall = items32 >= 768 || slow16;

@@ -125,7 +125,7 @@ bsr_status launch_generic(const spmm_args& a, const tune_opts& tune)
     constexpr int V16 = 16 / (int)sizeof(T);
     // rows of X per wavefront: 8 amortise the reads of W best when there are many rows; up to m = 8
     // the wavefronts are few and short, and 4 rows each (twice the wavefronts) finish sooner
-    const int rows = tune.mt > 0 ? tune.mt : (m > 8 ? 8 : (m >= 4 ? 4 : m));
+    const int rows = tune.mt > 0 ? tune.mt : (m > 8 ? 8 : (m >= 3 ? 4 : m));
     auto with_tm = [&](auto vec_tag) -> bsr_status {
         if (rows >= 8) return go(std::integral_constant<int, 8>{}, vec_tag);
         if (rows >= 4) return go(std::integral_constant<int, 4>{}, vec_tag);

@@ -1,0 +1,27 @@
+"""The k-split kernel on strips of 16 rows of a block, and small m on the matrix cores."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from gpu_util import check, gpu_product
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,out", [("f32", "f32"), ("f16", "f16"), ("bf16", "f32")])
+@pytest.mark.parametrize("bs", [(32, 32), (64, 64), (32, 64), (64, 16)])
+@pytest.mark.parametrize("tune", ["", "variant=2,mt=3", "variant=2,mt=3,nw=16,a=1"])
+def test_strips_of_blocks(oracle_mod, monkeypatch, dtype, out, bs, tune):
+    """Rows of X on both sides of one tile; block-rows empty, of one block, and longer than the descriptor's inline
+    list; forced strips with the default and with 16 wavefronts, and whatever the library takes by itself."""
+    import paper_2007_13055_amd as lib
+    if tune:
+        monkeypatch.setenv("BSR_SPMM_TUNE", tune)
+    counts = [3, 0, 40, 1, 17]
+    for m in (1, 9, 16, 17, 70):
+        p = wl.make_problem("strip", m, 40 * bs[1], len(counts) * bs[0], bs[0], bs[1], dtype, out, ("counts", counts),
+                            ("normal", 1.0), ("normal", 1.0), 900 + m)
+        Yo, So = oracle_mod.bsr_spmm(p.X, p.block_data, p.block_indices, p.index_pointer, p.n)
+        Y, W = gpu_product(p, path=lib.PATH_MFMA if tune else lib.PATH_AUTO)
+        check(Y, Yo, So, p.tau, f"strips {bs} {dtype}->{out} m={m} {tune}", out_dtype=out)
+        Y2, _ = gpu_product(p, path=lib.PATH_MFMA if tune else lib.PATH_AUTO, W=W)
+        assert np.array_equal(Y, Y2)
