@@ -20,6 +20,7 @@ constexpr int kRowDescColsAt = 4;                 // word index of the first inl
 constexpr int kRowDescCols = kRowDescWords - kRowDescColsAt;
 constexpr int kMaxKsplitItems = 4096;             // the k-split kernel is used below this many (block-row, m-tile) items
 constexpr int kStripeChunkPairs = 3;              // the stripe kernel's pair table lists block-rows in chunks of this many pairs
+constexpr int kThinRange = 256;                   // columns between the positions kept for thin blocks
 constexpr int kItemSlots = 4;                     // k-split work-item tables a handle keeps (one per recent m)
 
 // Development knobs, read from the environment variable BSR_SPMM_TUNE ("key=value,key=value"), and
@@ -31,7 +32,7 @@ constexpr int kItemSlots = 4;                     // k-split work-item tables a 
 //            started first; stripe a = block-row groups; thin a = groups of 4 blocks in flight
 //            thin blocks: variant 1 = transposed copy in scratch + gather, 2 = rows of X staged in LDS
 //            (a = slots per wavefront)
-//   sd       sampled product: 1 a workgroup per block, 2 groups of blocks that share slabs
+//   sd       sampled product: 1 a workgroup per block (thin: X transposed), 2 groups of blocks that share slabs (thin: turned over in LDS)
 struct tune_opts {
     int variant = 0, nw = 0, mt = 0, a = 0, b = 0, sd = 0;
     bool from_env = false;                   // BSR_SPMM_TUNE is set: it overrides what bsr_tune() remembered
@@ -93,11 +94,12 @@ struct bsr_matrix {
     std::vector<int32_t> grp_host;           // host copy of both (descriptors first), for the plan checker
     size_t grp_host_recs_at = 0;             // word offset of the records in grp_host
     // Thin blocks (16x1 fp32) whose block-rows store their blocks in non-decreasing block-column order
-    // (bsr_mfma_thinrow.hip): per slot the stored-block positions where the block-columns cross the multiples
-    // of 1024, [R][thin_nph + 1] (device); null when the kernel cannot take this W.
-    const int32_t* thin_ph = nullptr;
-    int32_t thin_nph = 0;
-    int32_t thin_max_run = 0;                // stored blocks of the longest (block-row, 1024 columns) run
+    // (bsr_mfma_thinrow.hip, bsr_sddmm_thin.hip): per slot the stored-block positions where the block-columns cross
+    // the multiples of kThinRange, [R][thin_pos_stride] (device); null when the kernels cannot take this W.
+    const int32_t* thin_pos = nullptr;
+    int32_t thin_pos_stride = 0;             // ceil(k / kThinRange) + 1
+    int32_t thin_nph = 0;                    // phases of 1024 columns
+    int32_t thin_max_range = 0;              // stored blocks of the longest (block-row, kThinRange columns) run
     // Blocks of one row (1x16 fp32: a thin W transposed) without duplicates (bsr_mfma_wide.hip): the stored blocks
     // by (block-column, block-row) as pairs {byte offset of the block, block-row}, [nnzb][2]; the chunks (at most
     // 16 pairs of one block-column inside one range of 256 block-rows) as {block-column, first pair, pairs, 0},
@@ -238,6 +240,10 @@ size_t sddmm_slab_plan_words(int64_t k, int32_t bs_r, int32_t bs_c, int64_t nnzb
 size_t sddmm_slab_workspace(const bsr_matrix* W, int64_t m);        // bytes of partial results it would like
 bsr_status launch_sddmm_slab(const bsr_matrix* W, int m, const void* G, const void* X, void* D, bsr_dtype d_dtype, void* ws,
                              size_t ws_bytes, hipStream_t stream);
+// Sampled product, 16x1 fp32 blocks in block-column order.
+bool sddmm_thin_supports(const bsr_matrix* W, int64_t m);
+size_t sddmm_thin_workspace(const bsr_matrix* W, int64_t m);
+bsr_status launch_sddmm_thin(const bsr_matrix* W, int m, const void* G, const void* X, void* D, void* ws, size_t ws_bytes, hipStream_t stream);
 // XT[c][i] = X[i][c], rows of XT (m rounded up to 4) floats apart
 bsr_status launch_transpose_f32(const float* X, float* XT, int m, int k, hipStream_t stream);
 

@@ -13,7 +13,7 @@
 //
 // Plan (bsr_create): the stored blocks of every block-row must come in non-decreasing block-column
 // order (else this kernel is not used); per slot the plan keeps the positions where the block-columns
-// cross the multiples of 1024, so the blocks of a (block-row, phase) are a contiguous run.
+// cross the multiples of 256, so the blocks of a (block-row, phase) are a contiguous run.
 //
 // Workgroup = 16 rows of X x 16 slots; 16 wavefronts.  Wavefront w moves row w of the row group (4 KiB per
 // phase through registers into one of two LDS buffers, one phase ahead of its use) and multiplies slot w:
@@ -58,7 +58,7 @@ __global__ __launch_bounds__(kThreads) void bsr_thin16_rows(const float* __restr
                                                            const int32_t* __restrict__ indices,
                                                            const int32_t* __restrict__ row_desc,
                                                            const int32_t* __restrict__ ph_ptr, float* __restrict__ Y,
-                                                           int m, int k, int n, int R, int nph, int n_rg, int n_set)
+                                                           int m, int k, int n, int R, int nph, int n_rg, int n_set, int pos_stride)
 {
     static_assert(CAP % 4 == 0 && CAP <= kMaxCap, "MFMAs are skipped four at a time");
     constexpr int NC = (4 * CAP + 63) / 64;           // loads of 64 block-columns per run
@@ -107,7 +107,7 @@ __global__ __launch_bounds__(kThreads) void bsr_thin16_rows(const float* __restr
     // ---- multiplying: slot set*16 + wave ----
     const int slot = set * kWaves + wave;
     // phase positions of the slot, one per lane: lane l holds position min(l, nph); a slot past R has empty runs
-    const int pp = slot < R ? ph_ptr[(size_t)slot * (size_t)(nph + 1) + min(lane, nph)] : 0;
+    const int pp = slot < R ? ph_ptr[(size_t)slot * (size_t)pos_stride + min(lane * (kPW / kThinRange), pos_stride - 1)] : 0;
     stage_load(st, nph > 1 ? 1 : 0);
     // the run of step s as a pair of buffer resources: its blocks (64 bytes each) and its block-columns
     struct run_t { __amdgpu_buffer_rsrc_t w, i; int cnt; };
@@ -206,16 +206,15 @@ __global__ __launch_bounds__(kThreads) void bsr_thin16_rows(const float* __restr
 size_t thinrow_plan_words(int64_t R, int64_t k, int32_t bs_r, int32_t bs_c)
 {
     if (bs_r != 16 || bs_c != 1) return 0;
-    return (size_t)R * (size_t)((k + kPW - 1) / kPW + 1) + 64;
+    return (size_t)R * (size_t)((k + kThinRange - 1) / kThinRange + 1) + 64;
 }
 
-bool mfma_thinrow_supports(const bsr_matrix* W) { return W->thin_ph != nullptr; }
+bool mfma_thinrow_supports(const bsr_matrix* W) { return W->thin_pos != nullptr; }
 
 void build_thinrow_plan(bsr_matrix* W, const int32_t* ptr, const int32_t* idx, size_t* words)
 {
-    W->thin_ph = nullptr;
-    W->thin_nph = 0;
-    W->thin_max_run = 0;
+    W->thin_pos = nullptr;
+    W->thin_nph = W->thin_pos_stride = W->thin_max_range = 0;
     if (W->bs_r != 16 || W->bs_c != 1 || W->dtype != BSR_F32 || W->R <= 0 || W->k < 4 || (W->k & 3) != 0) return;
     if (W->nnzb <= 0 || W->nnzb >= ((int64_t)1 << 25)) return;   // byte offsets into block_data are 32-bit
     if ((W->k + kPW - 1) / kPW > kMaxPhases) return;
@@ -223,23 +222,26 @@ void build_thinrow_plan(bsr_matrix* W, const int32_t* ptr, const int32_t* idx, s
     for (int r = 0; r < R; ++r)
         for (int32_t p = ptr[r] + 1; p < ptr[r + 1]; ++p)
             if (idx[p] < idx[p - 1]) return;          // a block-row out of order: the other kernels take this W
-    const int nph = (int)((W->k + kPW - 1) / kPW);
-    const int32_t* order = W->staging.data();         // slot -> block-row
-    const size_t at = *words, end = (at + (size_t)R * (size_t)(nph + 1) + 63) & ~(size_t)63;
+    const int stride = (int)((W->k + kThinRange - 1) / kThinRange) + 1;
+    const size_t at = *words, end = (at + (size_t)R * (size_t)stride + 63) & ~(size_t)63;
     W->staging.resize(end + 64, 0);
-    order = W->staging.data();
+    const int32_t* order = W->staging.data();         // slot -> block-row
     int32_t longest = 0;
     for (int s = 0; s < R; ++s) {
         const int r = order[s];
-        int32_t* out = W->staging.data() + at + (size_t)s * (size_t)(nph + 1);
-        for (int ph = 0; ph <= nph; ++ph)
-            out[ph] = (int32_t)(std::lower_bound(idx + ptr[r], idx + ptr[r + 1], ph * kPW) - idx);
-        out[nph] = ptr[r + 1];
-        for (int ph = 0; ph < nph; ++ph) longest = std::max(longest, out[ph + 1] - out[ph]);
+        int32_t* out = W->staging.data() + at + (size_t)s * (size_t)stride;
+        int32_t p = ptr[r];
+        for (int q = 0; q + 1 < stride; ++q) {
+            out[q] = p;
+            while (p < ptr[r + 1] && idx[p] < (q + 1) * kThinRange) ++p;
+            longest = std::max(longest, p - out[q]);
+        }
+        out[stride - 1] = ptr[r + 1];
     }
-    W->thin_ph = W->row_order + at;
-    W->thin_nph = nph;
-    W->thin_max_run = longest;
+    W->thin_pos = W->row_order + at;
+    W->thin_pos_stride = stride;
+    W->thin_nph = (int)((W->k + kPW - 1) / kPW);
+    W->thin_max_range = longest;
     *words = end;
 }
 
@@ -257,8 +259,8 @@ bsr_status launch_mfma_thinrow(const spmm_args& a, const tune_opts& tune)
                                                            hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
         if (attr != hipSuccess) return BSR_ERR_HIP;
         hipLaunchKernelGGL((bsr_thin16_rows<CAP>), dim3((unsigned)grid), dim3(kThreads), kLds, a.stream, (const float*)a.X,
-                           (const float*)W->data, W->indices, W->row_desc, W->thin_ph, (float*)a.Y, m, k, n, R,
-                           W->thin_nph, n_rg, n_set);
+                           (const float*)W->data, W->indices, W->row_desc, W->thin_pos, (float*)a.Y, m, k, n, R,
+                           W->thin_nph, n_rg, n_set, W->thin_pos_stride);
         return hipGetLastError() == hipSuccess ? BSR_OK : BSR_ERR_HIP;
     };
     // MFMAs of a phase whose operands are loaded ahead (4 blocks each): enough for the average run and a

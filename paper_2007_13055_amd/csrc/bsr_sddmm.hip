@@ -469,7 +469,8 @@ extern "C" bsr_status bsr_sddmm_workspace_size(const bsr_matrix* W, int64_t m, s
     if (!W || !bytes) return BSR_ERR_NULL;
     *bytes = 0;
     if (m < 0) return BSR_ERR_SHAPE;
-    if (takes_slabs(W, m)) *bytes = (sddmm_slab_workspace(W, m) + 255) & ~(size_t)255;
+    const size_t b = takes_slabs(W, m) ? sddmm_slab_workspace(W, m) : sddmm_thin_supports(W, m) ? sddmm_thin_workspace(W, m) : 0;
+    *bytes = (b + 255) & ~(size_t)255;
     return BSR_OK;
 }
 
@@ -499,6 +500,8 @@ extern "C" bsr_status bsr_sddmm_ws(const bsr_matrix* W, int64_t m, const void* G
     const int mi = (int)m;
     if (takes_slabs(W, m))
         return launch_sddmm_slab(W, mi, G_dev, X_dev, D_dev, d_dtype, workspace_dev, workspace_bytes, stream);
+    if (sddmm_thin_supports(W, m) && d_dtype == BSR_F32)
+        return launch_sddmm_thin(W, mi, G_dev, X_dev, D_dev, workspace_dev, workspace_bytes, stream);
     if (W->dtype == BSR_F32) return launch_sddmm_types<float, float>(W, mi, G_dev, X_dev, D_dev, stream);
     if (W->dtype == BSR_F16) return d_dtype == BSR_F32 ? launch_sddmm_types<_Float16, float>(W, mi, G_dev, X_dev, D_dev, stream)
                                                        : launch_sddmm_types<_Float16, _Float16>(W, mi, G_dev, X_dev, D_dev, stream);
