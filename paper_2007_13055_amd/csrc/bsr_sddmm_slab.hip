@@ -450,10 +450,15 @@ bsr_status launch_sddmm_slab(const bsr_matrix* W, int m, const void* G, const vo
             if (W->sl.host.size() > W->sl_words) return BSR_ERR_WORKSPACE;
             if (hipMemcpyAsync(W->sl_base, W->sl.host.data(), W->sl.host.size() * sizeof(int32_t), hipMemcpyHostToDevice, stream) != hipSuccess)
                 return BSR_ERR_HIP;
-            if (hipEventCreateWithFlags(&W->sl.uploaded, hipEventDisableTiming) != hipSuccess) W->sl.uploaded = nullptr;
-            if (W->sl.uploaded) (void)hipEventRecord(W->sl.uploaded, stream);
-            (void)hipGetLastError();                  // a refused record (stream capture) is not an error of the product
-            W->sl.sent = true;
+            // A copy recorded into a graph runs when the graph does, perhaps never: it serves that graph's products only,
+            // and the next product outside sends the plan itself.
+            hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+            if (hipStreamIsCapturing(stream, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone) {
+                if (hipEventCreateWithFlags(&W->sl.uploaded, hipEventDisableTiming) != hipSuccess) W->sl.uploaded = nullptr;
+                if (W->sl.uploaded) (void)hipEventRecord(W->sl.uploaded, stream);
+                W->sl.sent = true;
+            }
+            (void)hipGetLastError();
         } else {
             order_after_upload(stream, W->sl.uploaded, W->sl.landed);
         }

@@ -43,3 +43,38 @@ def test_sampled_product_slab_groups(oracle_mod, monkeypatch, dtype, out, bs):
             torch.cuda.synchronize()
             check(D.double().cpu().numpy().reshape(p.nnzb, -1), Do.reshape(p.nnzb, -1), So.reshape(p.nnzb, -1), p.tau,
                   f"slabs {bs} {dtype}->{out} m={m} workspace={lent}", out_dtype=out)
+
+
+@pytest.mark.gpu
+def test_sampled_product_captured_first(oracle_mod, monkeypatch):
+    """A handle whose first sampled product is recorded into a graph: the copy of its plan runs only with the graph, so an
+    eager product before the first replay sends the plan itself; then replays with eager work in between."""
+    import torch
+    import paper_2007_13055_amd as lib
+    monkeypatch.setenv("BSR_SPMM_TUNE", "sd=2")
+    m = 1100
+    p = wl.make_problem("slab", m, 19 * 16, 13 * 16, 16, 16, "f32", "f32", ("counts", np.full(13, 9)), ("normal", 1.0),
+                        ("normal", 1.0), 2190)
+    G = np.random.default_rng(5).normal(size=(m, p.n)).astype(np.float32)
+    Do, So = oracle_mod.bsr_sddmm(G, p.X, p.block_indices, p.index_pointer, 16, 16)
+    W, Gd, Xd = lib.bsr_create(p.n, p.k, p.block_data, p.block_indices, p.index_pointer), to_device(G, "f32"), to_device(p.X, "f32")
+    D, E = (torch.full((p.nnzb, 16, 16), float("nan"), device="cuda") for _ in range(2))
+
+    def right(t, what):
+        torch.cuda.synchronize()
+        check(t.double().cpu().numpy().reshape(p.nnzb, -1), Do.reshape(p.nnzb, -1), So.reshape(p.nnzb, -1), p.tau, what)
+        t.fill_(float("nan"))
+
+    W.ensure_scratch(m)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        for _ in range(2):
+            lib.bsr_sddmm(W, Gd, Xd, D)
+    lib.bsr_sddmm(W, Gd, Xd, E)
+    right(E, "eager product before the first replay")
+    for replay in range(4):
+        g.replay()
+        right(D, f"replay {replay}")
+        lib.bsr_sddmm(W, Gd, Xd, E)
+        right(E, f"eager product after replay {replay}")
