@@ -236,7 +236,7 @@ def bsr_create_transposed(n, k, block_data, block_indices, index_pointer, dtype=
 
 def bsr_spmm_ex(W: BsrMatrix, X, Y=None, y_dtype=None, path=PATH_AUTO):
     """Y = X * W^T on torch's current stream; X (m, k) device tensor of W's dtype.  Returns Y."""
-    return _native.spmm(W, W._core, X, Y, y_dtype, path)
+    return _native.spmm(W, W._core, X, Y, y_dtype, int(path))
 
 
 def bsr_spmm(W: BsrMatrix, X, Y=None, y_dtype=None):

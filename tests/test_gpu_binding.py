@@ -19,6 +19,7 @@ def test_entry_points_arguments_and_errors(dtype):
     assert lib.bsr_sddmm(W, G, X, D, d_dtype="f32", lend_scratch=False) is D and bool((D == 5).all())
     new = lib.bsr_spmm_ex(W, X, y_dtype="f32", path=lib.PATH_WAVE)
     assert new.dtype == torch.float32 and new.device == X.device and not new.requires_grad and torch.equal(new, want)
+    assert torch.equal(lib.bsr_spmm_ex(W, X, path=1.0).float(), want)                        # whatever int() takes
     new = lib.bsr_sddmm(W=W, G=G, X=X)
     assert new.shape == (3, 16, 16) and new.dtype == T and bool((new == 5).all())
     assert lib.bsr_spmm(W, X[:0]).shape == (0, 32)
