@@ -135,6 +135,9 @@ void bsr_destroy(bsr_matrix* W);
  * the 4 most recent values of m; other streams wait for that upload the same way).  With more than
  * 4 distinct m in flight at once on one handle a list may be replaced while an earlier product still
  * reads it: keep such products ordered on one stream.
+ * A product recorded into a graph uses such a list only if an eager product of that m has uploaded it before and the
+ * upload is over; the list is then kept for the graph's replays (up to 3 values of m per handle, as long as the handle
+ * or its workspace lives).  Otherwise it is recorded without one: the same result, less evenly spread over the CUs.
  * NaN or Inf in X: kernels that fill their last, partial group of blocks with zero-valued dummy
  * blocks multiply those zeros by real entries of X (the thin-block kernels: by column 0 of X), so a
  * non-finite entry there can reach outputs it does not belong to.  Finite inputs are unaffected.

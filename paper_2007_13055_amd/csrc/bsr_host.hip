@@ -86,6 +86,105 @@ tune_opts read_tune_env()
     return t;
 }
 
+bool is_capturing(hipStream_t stream)
+{
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    const bool ok = hipStreamIsCapturing(stream, &cs) == hipSuccess;
+    (void)hipGetLastError();
+    return !ok || cs != hipStreamCaptureStatusNone;   // the default stream beside a capture: refused, and treated as one
+}
+
+// hipEventQuery() in the relaxed mode: in the default mode a query ends a capture that is under way.
+static bool event_done(hipEvent_t ev)
+{
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool swapped = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    const bool done = hipEventQuery(ev) == hipSuccess;
+    if (swapped) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    (void)hipGetLastError();                          // hipErrorNotReady is not an error of the product
+    return done;
+}
+
+void order_after_upload(hipStream_t stream, hipEvent_t ev, std::atomic<bool>& landed)
+{
+    if (!ev || landed.load(std::memory_order_acquire) || is_capturing(stream)) return;
+    if (event_done(ev)) { landed.store(true, std::memory_order_release); return; }
+    (void)hipStreamWaitEvent(stream, ev, 0);
+    (void)hipGetLastError();
+}
+
+bool upload_landed(hipEvent_t ev, std::atomic<bool>& landed)
+{
+    if (landed.load(std::memory_order_acquire)) return true;
+    if (!ev || !event_done(ev)) return false;
+    landed.store(true, std::memory_order_release);
+    return true;
+}
+
+bool upload_words(int32_t* dev, const std::vector<int32_t>& host, hipStream_t stream, hipEvent_t& ev, std::atomic<bool>& landed)
+{
+    landed.store(false, std::memory_order_release);
+    if (hipMemcpyAsync(dev, host.data(), host.size() * sizeof(int32_t), hipMemcpyHostToDevice, stream) != hipSuccess) return false;
+    if (!ev && hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) ev = nullptr;
+    if (ev && hipEventRecord(ev, stream) == hipSuccess) return true;
+    (void)hipGetLastError();                          // nothing to wait for it by later: wait now
+    if (hipStreamSynchronize(stream) != hipSuccess) return false;
+    landed.store(true, std::memory_order_release);
+    return true;
+}
+
+int cached_table(const bsr_matrix* W, bsr_matrix::item_table* tables, int key, hipStream_t stream, int32_t* dev_base,
+                 size_t capacity_words, const std::function<int(std::vector<int32_t>&)>& build, const int32_t** table_out)
+{
+    const bool capturing = is_capturing(stream);
+    std::lock_guard<std::mutex> lock(W->item_mu);
+    bsr_matrix::item_table* slot = nullptr;
+    int pinned = 0;
+    for (int i = 0; i < kItemSlots; ++i) {
+        if (tables[i].tiles == key) slot = &tables[i];
+        pinned += tables[i].pinned;
+    }
+    if (capturing) {
+        // What is recorded reads the table at every replay, long after this call, and cannot be made to wait for an
+        // upload outside the graph.  So it takes a table only if the upload is over, and that table then stays for as
+        // long as the handle does; one table always stays free for eager products.  Else it runs without (the same
+        // result, less evenly spread over the CUs).
+        if (!slot || (!slot->pinned && pinned + 1 >= kItemSlots) || !upload_landed(slot->uploaded, slot->landed)) return 0;
+        slot->pinned = true;
+    }
+    if (slot) {
+        slot->last_use = ++W->item_clock;
+        *table_out = dev_base + (size_t)(slot - tables) * capacity_words;
+        if (!capturing) order_after_upload(stream, slot->uploaded, slot->landed);
+        return slot->grid;
+    }
+    for (int none : W->item_none)
+        if (none == key) return 0;
+    for (int i = 0; i < kItemSlots; ++i) {            // an unused table, else the least recently used one no graph reads
+        if (tables[i].pinned) continue;
+        if (!slot || (slot->tiles >= 0 && (tables[i].tiles < 0 || tables[i].last_use < slot->last_use))) slot = &tables[i];
+    }
+    // a replaced table's upload may still be reading its host copy: wait for it before rewriting the buffer
+    if (slot->uploaded && !slot->landed.load(std::memory_order_acquire)) (void)hipEventSynchronize(slot->uploaded);
+    (void)hipGetLastError();
+    slot->tiles = -1;
+    const int grid = build(slot->host);
+    if (grid <= 0 || slot->host.size() > capacity_words) {
+        // no table for this m: remembered, or every product would try again (3273 x (176, 1168) in 16x16 fp32
+        // blocks, 11 block-rows that do not spread over 8 XCDs: 55 us of host time a call, 7.4 of GPU time)
+        W->item_none[W->item_none_at] = key;
+        W->item_none_at = (W->item_none_at + 1) % kItemSlots;
+        return 0;
+    }
+    int32_t* dev = dev_base + (size_t)(slot - tables) * capacity_words;
+    if (!upload_words(dev, slot->host, stream, slot->uploaded, slot->landed)) return 0;
+    slot->tiles = key;
+    slot->grid = grid;
+    slot->last_use = ++W->item_clock;
+    *table_out = dev;
+    return grid;
+}
+
 // Work-item table of the k-split kernel.
 //
 // The hardware hands workgroup b to XCD b mod 8 and, inside an XCD, round-robin to its CUs, so with
@@ -94,69 +193,6 @@ tune_opts read_tune_env()
 // first on the least loaded CU -- all m-tiles of a block-row on one XCD, so the block-row's W
 // blocks are fetched into one L2 only -- and writes the table level by level: entry c + #CUs*level
 // is the level-th item of CU c, or an empty descriptor (block-row -1) that makes the workgroup exit.
-void order_after_upload(hipStream_t stream, hipEvent_t ev, std::atomic<bool>& landed)
-{
-    if (!ev || landed.load(std::memory_order_acquire)) return;
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &cs) != hipSuccess) { (void)hipGetLastError(); return; }
-    if (cs != hipStreamCaptureStatusNone) return;
-    if (hipEventQuery(ev) == hipSuccess) { landed.store(true, std::memory_order_release); return; }
-    (void)hipGetLastError();                          // hipErrorNotReady is not an error of the product
-    (void)hipStreamWaitEvent(stream, ev, 0);
-    (void)hipGetLastError();
-}
-
-int cached_table(const bsr_matrix* W, bsr_matrix::item_table* tables, int key, hipStream_t stream, int32_t* dev_base,
-                 size_t capacity_words, const std::function<int(std::vector<int32_t>&)>& build, const int32_t** table_out)
-{
-    std::lock_guard<std::mutex> lock(W->item_mu);
-    bsr_matrix::item_table* slot = nullptr;
-    for (int i = 0; i < kItemSlots; ++i)
-        if (tables[i].tiles == key) slot = &tables[i];
-    if (slot) {
-        slot->last_use = ++W->item_clock;
-        *table_out = dev_base + (size_t)(slot - tables) * capacity_words;
-        order_after_upload(stream, slot->uploaded, slot->landed);
-        return slot->grid;
-    }
-    for (int i = 0; i < kItemSlots && !slot; ++i)      // an unused table, else the least recently used one
-        if (tables[i].tiles < 0) slot = &tables[i];
-    if (!slot) {
-        slot = &tables[0];
-        for (int i = 1; i < kItemSlots; ++i)
-            if (tables[i].last_use < slot->last_use) slot = &tables[i];
-    }
-    // a replaced table's upload may still be reading its host copy: wait for it before rewriting the
-    // buffer (an event that was only captured into a graph cannot be waited for; its upload ran at
-    // capture's warm-up or will read the buffer at replay, which a caller changing m must order itself)
-    if (slot->uploaded && !slot->landed.load(std::memory_order_acquire)) (void)hipEventSynchronize(slot->uploaded);
-    (void)hipGetLastError();
-    slot->tiles = -1;
-    const int grid = build(slot->host);
-    if (grid <= 0 || slot->host.size() > capacity_words) {
-        // no table for this m: remembered like one, or every product would try again (3273 x (176, 1168) in 16x16 fp32
-        // blocks, 11 block-rows that do not spread over 8 XCDs: 55 us of host time a call, 7.4 of GPU time)
-        slot->tiles = key;
-        slot->grid = 0;
-        slot->landed.store(true, std::memory_order_release);
-        slot->last_use = ++W->item_clock;
-        return 0;
-    }
-    int32_t* dev = dev_base + (size_t)(slot - tables) * capacity_words;
-    if (hipMemcpyAsync(dev, slot->host.data(), slot->host.size() * sizeof(int32_t), hipMemcpyHostToDevice, stream) != hipSuccess)
-        return 0;
-    slot->landed.store(false, std::memory_order_release);
-    if (!slot->uploaded && hipEventCreateWithFlags(&slot->uploaded, hipEventDisableTiming) != hipSuccess)
-        slot->uploaded = nullptr;
-    if (slot->uploaded) (void)hipEventRecord(slot->uploaded, stream);
-    (void)hipGetLastError();                          // a refused record (stream capture) is not an error of the product
-    slot->tiles = key;
-    slot->grid = grid;
-    slot->last_use = ++W->item_clock;
-    *table_out = dev;
-    return grid;
-}
-
 int ksplit_items(const bsr_matrix* W, int tiles, hipStream_t stream, const int32_t** table_out)
 {
     const int n_cu = W->n_cu;

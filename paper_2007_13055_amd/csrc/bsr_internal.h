@@ -70,11 +70,12 @@ struct bsr_matrix {
     int32_t* item_desc = nullptr;            // kItemSlots tables of item_capacity descriptors each
     size_t item_capacity = 0;                // descriptors that fit one table
     std::vector<int32_t> slot_blocks;        // stored blocks per slot (host)
-    // One cached table per recent number of m-tiles; the least recently used one is replaced.
+    // One cached table per recent number of m-tiles; the least recently used one that no graph reads is replaced.
     struct item_table {
         int tiles = -1;                      // m-tiles the table was built for (-1: none)
         int grid = 0;                        // its workgroups
         uint64_t last_use = 0;
+        bool pinned = false;                 // a graph reads it: never replaced
         std::vector<int32_t> host;           // host copy (kept alive for the asynchronous upload)
         hipEvent_t uploaded = nullptr;       // recorded behind the upload
         std::atomic<bool> landed{false};     // the upload is known to have finished
@@ -82,6 +83,8 @@ struct bsr_matrix {
     mutable std::mutex item_mu;              // guards the tables below
     mutable item_table item_tables[kItemSlots];
     mutable uint64_t item_clock = 0;
+    mutable int item_none[kItemSlots] = {-1, -1, -1, -1};   // recent numbers of m-tiles that have no table
+    mutable int item_none_at = 0;
     // Row-group kernel (64x64 blocks of a 16-bit type, bsr_mfma_group.hip): the leading grp_slots slots (the
     // longest block-rows) are multiplied in groups of up to 8 that share their X tiles; the tile kernel takes
     // the slots behind them.  grp_desc = per group {8 block-rows (-1: none), first window record, windows, 0...}
@@ -189,7 +192,8 @@ bsr_status launch_mfma_direct(const spmm_args& a, const tune_opts& t);
 bsr_status launch_mfma_ksplit(const spmm_args& a, const tune_opts& t);
 // Builds (or reuses) the k-split work-item table for `tiles` m-tiles, queues its upload on `stream` (or
 // makes `stream` wait for an upload another stream still has in flight); returns the number of
-// workgroups and the table's device address, 0 if the table does not fit the workspace.
+// workgroups and the table's device address, 0 if there is none (it does not fit the workspace, or `stream` is being
+// captured and no table for it has landed before).
 int ksplit_items(const bsr_matrix* W, int tiles, hipStream_t stream, const int32_t** table_out);
 // One cached per-m table out of `tables` (kItemSlots of them, `capacity_words` int32 each, starting at
 // `dev_base`): the one built for `key`, else `build` fills a host vector (returning the number of
@@ -201,6 +205,12 @@ int cached_table(const bsr_matrix* W, bsr_matrix::item_table* tables, int key, h
 // finished.  Under stream capture nothing is recorded: an event from outside the capture cannot be
 // waited for there, and a caller that captures a handle's first product orders it itself.
 void order_after_upload(hipStream_t stream, hipEvent_t ev, std::atomic<bool>& landed);
+// Whether that upload has finished (asked of the event where it is not known; allowed during a capture).
+bool upload_landed(hipEvent_t ev, std::atomic<bool>& landed);
+// Queues the copy of `host` to `dev` and records `ev` (created if need be) behind it; false if that failed.  Not for a
+// stream that is being captured.
+bool upload_words(int32_t* dev, const std::vector<int32_t>& host, hipStream_t stream, hipEvent_t& ev, std::atomic<bool>& landed);
+bool is_capturing(hipStream_t stream);
 bsr_status launch_mfma_tile(const spmm_args& a, const tune_opts& t);
 // Row-group kernel: the grouped (longest) block-rows of a W with 64x64 blocks of a 16-bit type; the caller
 // launches the tile kernel with first_slot = W->grp_slots for the rest
