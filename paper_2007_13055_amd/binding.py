@@ -68,17 +68,28 @@ def load_library():
               "bsr_query_path", "bsr_scratch_size", "bsr_set_scratch", "bsr_tune", "bsr_tune_result",
               "bsr_transpose_pattern", "bsr_transpose_values", "bsr_sddmm"):
         getattr(lib, f).restype = ctypes.c_int
+    _lib = lib
+    return lib
+
+
+def _native_module():
+    """The module _binding, bound to the library's entry points.  Only matrices need it (it needs torch); the checks of
+    patterns and sizes do not."""
     global _native
+    if _native is not None:
+        return _native
+    lib = load_library()
     import torch                           # noqa: F401  (_binding links to torch's libraries)
     try:
         from . import _binding
     except ImportError as e:
         raise RuntimeError(f"the native module _binding is missing or does not load ({e}): build it with "
                            "`python -m paper_2007_13055_amd.build`") from e
-    _binding.bind(*(ctypes.cast(f, vp).value for f in (lib.bsr_spmm_ex, lib.bsr_spmm_static, lib.bsr_sddmm_ws,
-                                                       lib.bsr_scratch_size, lib.bsr_sddmm_workspace_size)), BsrError)
-    _native, _lib = _binding, lib
-    return lib
+    _binding.bind(*(ctypes.cast(f, ctypes.c_void_p).value
+                    for f in (lib.bsr_spmm_ex, lib.bsr_spmm_static, lib.bsr_sddmm_ws, lib.bsr_scratch_size,
+                              lib.bsr_sddmm_workspace_size)), BsrError)
+    _native = _binding
+    return _native
 
 
 def bsr_status_string(status: int) -> str:
@@ -122,7 +133,7 @@ class BsrMatrix:
         self._tensors = tensors            # block_data, block_indices, index_pointer, workspace (device)
         self._scratch = None               # device scratch lent to the handle (see ensure_scratch)
         nnzb = int(tensors[0].shape[0]) if tensors[0].dim() == 3 else 0
-        self._core = _native.Core(handle.value, n, k, nnzb, bs_r, bs_c, _DTYPE_CODE[dtype])   # what the calls read
+        self._core = _native_module().Core(handle.value, n, k, nnzb, bs_r, bs_c, _DTYPE_CODE[dtype])   # what the calls read
 
     @property
     def block_data(self):
@@ -161,6 +172,7 @@ def bsr_create(n, k, block_data, block_indices, index_pointer, dtype=None, devic
     """
     import torch
     lib = load_library()
+    _native_module()
     if isinstance(block_data, torch.Tensor):
         dtype = dtype or _dtype_name(block_data)
         data_dev = block_data.to(device=device, dtype=_torch_dtype(dtype)).contiguous()

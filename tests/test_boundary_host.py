@@ -3,6 +3,8 @@ symbol, and its structural validation returns the documented codes."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -134,3 +136,16 @@ def test_plan_fits_the_promised_workspace(lib, bs_r, bs_c, dtype, pattern):
     st = so.bsr_create(ctypes.byref(handle), n, k, bs_r, bs_c, nnzb, code, align(data), idx.ctypes.data, ptr.ctypes.data,
                        idx.ctypes.data, ptr.ctypes.data, align(ws), need - 256, None)
     assert st == 7
+
+
+def test_pattern_checks_need_no_torch(lib):
+    """bsr_validate, bsr_workspace_size and bsr_transpose_pattern work on host arrays: neither torch nor the native
+    module of the binding has to be there."""
+    code = ("import sys\n"
+            "sys.modules['torch'] = sys.modules['paper_2007_13055_amd._binding'] = None\n"
+            "import paper_2007_13055_amd as lib\n"
+            "assert lib.bsr_validate(64, 64, 16, 16, [0, 1, 1, 2, 2], [0, 3]) == 0\n"
+            "assert lib.bsr_workspace_size(64, 64, 16, 16, 2) > 0\n"
+            "assert lib.bsr_transpose_pattern(32, 32, 16, 16, [0, 1, 1], [1])[1].tolist() == [0]\n")
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr
