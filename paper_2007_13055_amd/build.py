@@ -90,7 +90,8 @@ BINDING = os.path.join(HERE, "_binding.so")
 def build_binding(force: bool = True) -> str:
     """Compile the native module of the Python binding (host code, torch's headers and libraries)."""
     import torch
-    if not force and os.path.exists(BINDING) and os.path.getmtime(BINDING) >= os.path.getmtime(BINDING_SRC):
+    deps = [BINDING_SRC, os.path.join(ROOT, "include", "bsr_spmm.h")]      # it calls the header's functions by address
+    if not force and os.path.exists(BINDING) and all(os.path.getmtime(BINDING) >= os.path.getmtime(d) for d in deps):
         return BINDING
     t = os.path.dirname(os.path.abspath(torch.__file__))
     includes = [os.path.join(t, "include"), os.path.join(t, "include", "torch", "csrc", "api", "include"),
