@@ -202,8 +202,9 @@ bsr_status bsr_tune(bsr_matrix* W, int64_t m, const void* X_dev, void* Y_dev, bs
  */
 bsr_status bsr_tune_result(const bsr_matrix* W, int64_t m, bsr_dtype y_dtype, int32_t settings_out[6], float* us_out);
 
-/* The path BSR_PATH_AUTO resolves to for this handle and m (never AUTO; what bsr_tune()
- * remembered is not consulted).  Errors: NULL. */
+/* The path BSR_PATH_AUTO resolves to for this handle, m and an output of W's type (never AUTO; what bsr_tune()
+ * remembered is not consulted).  Below 16 rows a 16-bit W may resolve to another one for a BSR_F32 output, whose sums
+ * are kept as exact as the wavefront-reduction kernels'.  Errors: NULL. */
 bsr_status bsr_query_path(const bsr_matrix* W, int64_t m, bsr_path* path_out);
 
 /*

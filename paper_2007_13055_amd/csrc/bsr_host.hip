@@ -507,25 +507,33 @@ void bsr_destroy(bsr_matrix* W)
     delete W;
 }
 
-bsr_status bsr_query_path(const bsr_matrix* W, int64_t m, bsr_path* path_out)
+// Matrix-core tiles are 16 rows of X tall: below that most of a tile is padding, and the wavefront-reduction
+// kernels (the paper's own regime, m <= 8) stream W once instead.  They start a wavefront per output column and
+// group of rows, though, at about 11 cycles each per XCD, while the k-split kernel takes the same 3-5 us whatever m
+// is: it is quicker from 9 rows on (8 x (1024, 1024): 3.2 against 3.4 us, 12 rows 3.8 against 3.4), and earlier once
+// there are some 6000 wavefronts (8 x (5888, 2944): 7.8 against 5.4 us).  But it sums a wavefront's blocks in one
+// chain where the wavefront-reduction kernels keep 64 partial sums, and an fp32 result shows that (root mean square
+// error of m = 12, uniform blocks: (1024, 1024) 25 % fp32 1.18e-7 against 0.80e-7, (8192, 8192) 25 % 4.1e-7
+// against 1.2e-7, bf16 with fp32 results 1.3e-7 against 0.75e-7): below 16 rows it takes only products whose result
+// is rounded to 16 bits, 1000 times coarser.
+static bsr_path auto_path(const bsr_matrix* W, int64_t m, bsr_dtype y_dtype)
 {
-    if (!W || !path_out) return BSR_ERR_NULL;
-    // Matrix-core tiles are 16 rows of X tall: below that most of a tile is padding, and the wavefront-reduction
-    // kernels (the paper's own regime, m <= 8) stream W once instead.  They start a wavefront per output column and
-    // group of rows, though, at about 11 cycles each per XCD, while the k-split kernel takes the same 3-5 us whatever m
-    // is: it wins from 9 rows on (8 x (1024, 1024): 3.2 against 3.4 us, 12 rows 3.8 against 3.4), and earlier once
-    // there are some 6000 wavefronts (8 x (5888, 2944): 7.8 against 5.4 us).
-    const bool square = mfma_supports(W);
     const int64_t waves = W->n * (m > 8 ? (m + 7) / 8 : (m + 3) / 4);
-    if ((square && (m >= 9 || waves >= 6000)) || (mfma_small_supports(W) && m >= 16)) *path_out = BSR_PATH_MFMA;
+    if (mfma_supports(W) && (m >= 16 || (y_dtype != BSR_F32 && (m >= 9 || waves >= 6000)))) return BSR_PATH_MFMA;
+    if (mfma_small_supports(W) && m >= 16) return BSR_PATH_MFMA;
     // Thin 16x1 fp32 blocks take the matrix-core path when the caller has lent enough scratch for
     // the transposed copy of X, or when their block-rows are stored in block-column order (one launch,
     // no scratch).
-    else if (mfma_thin_supports(W) && m >= 32 && W->scratch && W->scratch_bytes >= mfma_thin_scratch_bytes(W, m))
-        *path_out = BSR_PATH_MFMA;
-    else if (mfma_thinrow_supports(W) && m >= 16) *path_out = BSR_PATH_MFMA;   // no scratch: rows of X staged in LDS
-    else if (mfma_wide_supports(W) && m >= 16) *path_out = BSR_PATH_MFMA;      // 1x16 blocks, by block-column
-    else *path_out = BSR_PATH_WAVE;
+    if (mfma_thin_supports(W) && m >= 32 && W->scratch && W->scratch_bytes >= mfma_thin_scratch_bytes(W, m)) return BSR_PATH_MFMA;
+    if (mfma_thinrow_supports(W) && m >= 16) return BSR_PATH_MFMA;   // no scratch: rows of X staged in LDS
+    if (mfma_wide_supports(W) && m >= 16) return BSR_PATH_MFMA;      // 1x16 blocks, by block-column
+    return BSR_PATH_WAVE;
+}
+
+bsr_status bsr_query_path(const bsr_matrix* W, int64_t m, bsr_path* path_out)
+{
+    if (!W || !path_out) return BSR_ERR_NULL;
+    *path_out = auto_path(W, m, W->dtype);
     return BSR_OK;
 }
 
@@ -601,7 +609,7 @@ bsr_status bsr_spmm_ex(const bsr_matrix* W, int64_t m, const void* X_dev, void* 
         // a remembered thin-block choice needs its scratch still lent
         if (tuned && path == BSR_PATH_MFMA && mfma_thin_supports(W) && !(t.variant == 2 && mfma_thinrow_supports(W)) &&
             (!W->scratch || W->scratch_bytes < mfma_thin_scratch_bytes(W, m))) tuned = false;
-        if (!tuned) { bsr_query_path(W, m, &path); if (!t.from_env) t = tune_opts{}; }
+        if (!tuned) { path = auto_path(W, m, y_dtype); if (!t.from_env) t = tune_opts{}; }
     }
     return run_product(spmm_args{W, m, X_dev, Y_dev, y_dtype, (hipStream_t)hip_stream}, path, t);
 }
