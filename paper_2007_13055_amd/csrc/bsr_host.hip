@@ -515,11 +515,12 @@ void bsr_destroy(bsr_matrix* W)
 // chain where the wavefront-reduction kernels keep 64 partial sums, and an fp32 result shows that (root mean square
 // error of m = 12, uniform blocks: (1024, 1024) 25 % fp32 1.18e-7 against 0.80e-7, (8192, 8192) 25 % 4.1e-7
 // against 1.2e-7, bf16 with fp32 results 1.3e-7 against 0.75e-7): below 16 rows it takes only products whose result
-// is rounded to 16 bits, 1000 times coarser.
+// is rounded to 16 bits, 1000 times coarser, and whose operands its offsets reach.
 static bsr_path auto_path(const bsr_matrix* W, int64_t m, bsr_dtype y_dtype)
 {
     const int64_t waves = W->n * (m > 8 ? (m + 7) / 8 : (m + 3) / 4);
-    if (mfma_supports(W) && (m >= 16 || (y_dtype != BSR_F32 && (m >= 9 || waves >= 6000)))) return BSR_PATH_MFMA;
+    if (mfma_supports(W) && (m >= 16 || (y_dtype != BSR_F32 && (m >= 9 || waves >= 6000) && mfma_ksplit_reaches(W))))
+        return BSR_PATH_MFMA;
     if (mfma_small_supports(W) && m >= 16) return BSR_PATH_MFMA;
     // Thin 16x1 fp32 blocks take the matrix-core path when the caller has lent enough scratch for
     // the transposed copy of X, or when their block-rows are stored in block-column order (one launch,

@@ -190,6 +190,8 @@ bool mfma_supports(const bsr_matrix* W);
 // matrix-core kernel variants (bsr_mfma*.hip)
 bsr_status launch_mfma_direct(const spmm_args& a, const tune_opts& t);
 bsr_status launch_mfma_ksplit(const spmm_args& a, const tune_opts& t);
+// Whether its 32-bit byte offsets reach every block of the longest block-row and 32 rows of X.
+bool mfma_ksplit_reaches(const bsr_matrix* W);
 // Builds (or reuses) the k-split work-item table for `tiles` m-tiles, queues its upload on `stream` (or
 // makes `stream` wait for an upload another stream still has in flight); returns the number of
 // workgroups and the table's device address, 0 if there is none (it does not fit the workspace, or `stream` is being

@@ -173,7 +173,8 @@ bsr_status launch_mfma(const spmm_args& a, const tune_opts& tune)
         // thresholds from timed trials over many sizes (bsr_tune's candidates) on MI355X
         const int MM = a.W->bs_r >= 32 ? 32 : 16;
         const int64_t sub = (a.m + MM - 1) / MM;
-        if (sub * a.W->R < 6000 && (a.W->mean_row_blocks > 1.5 || sub * a.W->R < 768)) variant = 2;
+        if (sub * a.W->R < 6000 && (a.W->mean_row_blocks > 1.5 || (sub * a.W->R < 768 && mfma_ksplit_reaches(a.W))))
+            variant = 2;
         else if (a.W->bs_r >= 32 && a.m >= 512) variant = 3;
         else if (a.m >= 256 && mfma_stripe_supports(a.W, 16)) variant = 4;
         else if (a.W->mean_row_blocks > 4.0) variant = 2;     // 16-row blocks the tile kernel does not take

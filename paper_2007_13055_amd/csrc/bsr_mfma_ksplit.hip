@@ -334,6 +334,12 @@ bsr_status launch_ksplit_shape(const spmm_args& a, const tune_opts& tune)
 
 }  // namespace
 
+bool mfma_ksplit_reaches(const bsr_matrix* W)
+{
+    const int64_t S = W->dtype == BSR_F32 ? 4 : 2, limit = (int64_t)1 << 31;
+    return (int64_t)W->max_row_blocks * W->bs_r * W->bs_c * S < limit && 32 * W->k * S < limit;
+}
+
 bsr_status launch_mfma_ksplit(const spmm_args& a, const tune_opts& t)
 {
     BSR_MFMA_DISPATCH(launch_ksplit_shape, a.W, a.y_dtype, a, t);

@@ -26,3 +26,28 @@ def test_fp32_results_keep_their_sums_apart(oracle_mod, dtype, out, m, R):
     else:
         assert np.array_equal(Y, mfma)
     assert lib.bsr_query_path(W, m) == (lib.PATH_WAVE if m < 16 and dtype == "f32" else lib.PATH_MFMA)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,m,k", [("bf16", 9, 1 << 26), ("f16", 15, 1 << 26), ("f32", 16, 1 << 25)])
+def test_wide_rows_of_x_stay_accepted(oracle_mod, dtype, m, k):
+    """Rows of X beyond the k-split kernel's 32-bit offsets: the library's own choice is a kernel that takes them.  Two
+    block-rows of one and two blocks; the oracle sees the columns that they name."""
+    import torch
+    import paper_2007_13055_amd as lib
+    from gpu_util import torch_dtype
+    bs, C = 16, k // 16
+    cols = np.array([C - 1, 0, C // 3], dtype=np.int32)
+    ptr = np.array([0, 1, 3], dtype=np.int32)
+    rng = np.random.default_rng(m)
+    data = wl.round_to_storage(rng.normal(size=(3, bs, bs)).astype(np.float32), dtype)
+    Xs = wl.round_to_storage(rng.normal(size=(m, 3 * bs)).astype(np.float32), dtype)
+    X = torch.zeros((m, k), dtype=torch_dtype(dtype), device="cuda")
+    for j, c in enumerate(cols):
+        X[:, int(c) * bs:(int(c) + 1) * bs] = torch.from_numpy(Xs[:, j * bs:(j + 1) * bs]).to("cuda", torch_dtype(dtype))
+    Yo, So = oracle_mod.bsr_spmm(Xs, data, np.arange(3, dtype=np.int32), ptr, 2 * bs)
+    W = lib.bsr_create(2 * bs, k, data, cols, ptr, dtype=dtype)
+    Y = torch.full((m, 2 * bs), float("nan"), dtype=torch_dtype(dtype), device="cuda")
+    lib.bsr_spmm(W, X, Y)
+    torch.cuda.synchronize()
+    check(Y.double().cpu().numpy(), Yo, So, 1e-5, f"{dtype} m={m} k={k}", out_dtype=dtype)
