@@ -301,7 +301,8 @@ def bsr_tune_result(W: BsrMatrix, m: int, y_dtype=None):
 def bsr_sddmm(W: BsrMatrix, G, X, D=None, d_dtype=None, lend_scratch=True):
     """D[p] = G[:, block-row of p]^T @ X[:, block-column of p] for every stored block of W (the gradient
     of the block values); G (m, n), X (m, k) device tensors of W's dtype.  Returns D (nnzb, bs_r, bs_c).
-    lend_scratch: lend the handle the scratch its thin-block kernel wants (as bsr_spmm does)."""
+    lend_scratch: lend the handle the scratch its thin-block kernel wants (as bsr_spmm does) and the product the memory
+    its splits want; without, nothing is allocated but a D that is not given."""
     return _native.sddmm(W, W._core, G, X, D, d_dtype, lend_scratch)
 
 

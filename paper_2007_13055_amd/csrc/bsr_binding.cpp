@@ -248,11 +248,18 @@ PyObject* sddmm(PyObject*, PyObject* const* a, Py_ssize_t nargs)
     }
     const void *gp = G->data_ptr(), *xp = X->data_ptr();
     void* dp = D->data_ptr();
-    // this call's workspace: from torch's allocator, which hands it on in stream order once the call has returned
+    // This call's workspace: from torch's allocator, which hands it on in stream order once the call has returned.  The
+    // product runs without it too: a caller that lends nothing gets nothing allocated, and memory that is not there is
+    // no error.
     size_t ws_bytes = 0;
     at::Tensor ws;
-    if (g_sddmm_workspace(c->handle, m, &ws_bytes) == BSR_OK && ws_bytes > 0)
-        ws = at::Tensor(at::detail::empty_cuda({(int64_t)ws_bytes}, at::kByte, G->device(), std::nullopt));
+    if (lend && g_sddmm_workspace(c->handle, m, &ws_bytes) == BSR_OK && ws_bytes > 0) {
+        try {
+            ws = at::Tensor(at::detail::empty_cuda({(int64_t)ws_bytes}, at::kByte, G->device(), std::nullopt));
+        } catch (const c10::OutOfMemoryError&) {
+            ws_bytes = 0;
+        }
+    }
     bsr_status st;
     {
         pybind11::gil_scoped_release no_gil;

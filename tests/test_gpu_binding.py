@@ -42,3 +42,50 @@ def test_entry_points_arguments_and_errors(dtype):
     W.close()
     with pytest.raises(lib.BsrError):
         lib.bsr_spmm(W, X)
+
+
+def _splitting_product():
+    """G, X, W, D of a sampled product whose rows are split, with 6 MB or so of partial results, and the D it has."""
+    import torch
+    import paper_2007_13055_amd as lib
+    g = torch.Generator(device="cuda").manual_seed(3)
+    ptr = np.arange(0, 48 * 33, 48)
+    W = lib.bsr_create(512, 768, torch.zeros((48 * 32, 16, 16), dtype=torch.bfloat16, device="cuda"), np.tile(np.arange(48), 32), ptr)
+    G, X = (torch.randint(-2, 3, (4096, c), generator=g, device="cuda").bfloat16() for c in (512, 768))
+    want = (G.float().t() @ X.float()).reshape(32, 16, 48, 16).transpose(1, 2).reshape(-1, 16, 16)   # whole numbers: exact
+    return W, G, X, torch.empty((48 * 32, 16, 16), device="cuda"), want
+
+
+@pytest.mark.gpu
+def test_sampled_product_allocates_nothing_unless_lent():
+    import torch
+    import paper_2007_13055_amd as lib
+    W, G, X, D, want = _splitting_product()
+    for lend in (False, True):
+        torch.cuda.synchronize()
+        torch.cuda.reset_peak_memory_stats()
+        before = torch.cuda.memory_allocated()
+        lib.bsr_sddmm(W, G, X, D, d_dtype="f32", lend_scratch=lend)
+        assert (torch.cuda.max_memory_allocated() > before) == lend        # the case is one that wants memory
+        assert torch.equal(D, want)
+        D.fill_(float("nan"))
+
+
+@pytest.mark.gpu
+def test_sampled_product_without_memory_for_its_splits():
+    import torch
+    import paper_2007_13055_amd as lib
+    W, G, X, D, want = _splitting_product()
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    total = torch.cuda.get_device_properties(0).total_memory
+    torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + 4096) / total)
+    try:
+        rest = []
+        with pytest.raises(torch.cuda.OutOfMemoryError):                   # take what is left of the segments in use
+            while len(rest) < 1000:
+                rest.append(torch.empty(1 << 20, dtype=torch.uint8, device="cuda"))
+        lib.bsr_sddmm(W, G, X, D, d_dtype="f32")
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert torch.equal(D, want)
