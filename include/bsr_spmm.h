@@ -253,7 +253,9 @@ bsr_status bsr_sddmm(const bsr_matrix* W, int64_t m, const void* G_dev, const vo
 /*
  * bsr_sddmm() with memory for this one call: a W of few blocks keeps all CUs busy only if the rows of G and X are
  * split, and the partial results (fp32) of the splits need a place until they are added.
- *   bsr_sddmm_workspace_size  bytes a product with m rows would use (0: none); multiple of 256
+ *   bsr_sddmm_workspace_size  bytes a product with m rows would use (0: none); multiple of 256.  The first call of
+ *                             these on a handle builds the product's plan on the host (milliseconds for tens of
+ *                             thousands of stored blocks)
  *   workspace_dev             DEVICE, 16-byte aligned, or NULL; overwritten.  With fewer bytes than that the rows are
  *                             not split (the result is as good, the call slower).  Calls with memory of their own may
  *                             run concurrently on one handle.

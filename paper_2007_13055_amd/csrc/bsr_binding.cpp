@@ -253,7 +253,11 @@ PyObject* sddmm(PyObject*, PyObject* const* a, Py_ssize_t nargs)
     // no error.
     size_t ws_bytes = 0;
     at::Tensor ws;
-    if (lend && g_sddmm_workspace(c->handle, m, &ws_bytes) == BSR_OK && ws_bytes > 0) {
+    if (lend) {
+        pybind11::gil_scoped_release no_gil;          // the first one of a pattern builds the product's plan: milliseconds
+        if (g_sddmm_workspace(c->handle, m, &ws_bytes) != BSR_OK) ws_bytes = 0;
+    }
+    if (ws_bytes > 0) {
         try {
             ws = at::Tensor(at::detail::empty_cuda({(int64_t)ws_bytes}, at::kByte, G->device(), std::nullopt));
         } catch (const c10::OutOfMemoryError&) {

@@ -84,8 +84,47 @@ def test_sampled_product_without_memory_for_its_splits():
         rest = []
         with pytest.raises(torch.cuda.OutOfMemoryError):                   # take what is left of the segments in use
             while len(rest) < 1000:
-                rest.append(torch.empty(1 << 20, dtype=torch.uint8, device="cuda"))
+                rest.append(torch.empty(2 << 20, dtype=torch.uint8, device="cuda"))
         lib.bsr_sddmm(W, G, X, D, d_dtype="f32")
     finally:
         torch.cuda.set_per_process_memory_fraction(1.0)
     assert torch.equal(D, want)
+
+
+@pytest.mark.gpu
+def test_other_threads_run_while_a_plan_is_built():
+    """The first sampled product on a pattern builds its plan on the host, tens of ms here: another Python thread goes on
+    meanwhile."""
+    import threading
+    import time
+    import torch
+    import paper_2007_13055_amd as lib
+
+    def matrix(R, C):
+        return lib.bsr_create(8 * R, 8 * C, torch.zeros((R * C, 8, 8), dtype=torch.bfloat16, device="cuda"), np.tile(np.arange(C), R),
+                              np.arange(0, R * C + 1, C))
+
+    def inputs(R, C):
+        return (torch.ones((512, 8 * c), dtype=torch.bfloat16, device="cuda") for c in (R, C))
+
+    lib.bsr_sddmm(matrix(8, 8), *inputs(8, 8))                             # the kernels are loaded
+    W, (G, X) = matrix(1000, 2000), inputs(1000, 2000)
+    torch.cuda.synchronize()
+    ticks, stop = [], threading.Event()
+
+    def watch():
+        while not stop.is_set():
+            ticks.append(time.perf_counter())
+
+    t = threading.Thread(target=watch)
+    t.start()
+    while len(ticks) < 1000:
+        time.sleep(0.001)
+    start = time.perf_counter()
+    lib.bsr_sddmm(W, G, X)
+    end = time.perf_counter()
+    stop.set()
+    t.join()
+    inside = [start, *(x for x in ticks if start <= x <= end), end]
+    assert end - start > 0.01
+    assert max(np.diff(inside)) < 0.3 * (end - start)
