@@ -10,6 +10,7 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <ATen/hip/EmptyTensor.h>
+#include <ATen/ops/empty.h>
 #include <c10/hip/HIPStream.h>
 
 #include "bsr_spmm.h"
@@ -140,6 +141,12 @@ bool ensure_scratch(PyObject* W, const core_object* c, int64_t m)
 
 void* stream() { return c10::hip::getCurrentHIPStream().stream(); }
 
+// A result: through torch's dispatcher, so that its modes and its deterministic fill see it.
+at::Tensor result(at::IntArrayRef shape, int code, const at::Tensor& like)
+{
+    return at::empty(shape, at::TensorOptions().dtype(kTypes[code]).device(like.device()));
+}
+
 bool dims2(const at::Tensor& t, int64_t rows, int64_t cols)
 {
     return t.dim() == 2 && t.size(0) == rows && t.size(1) == cols;
@@ -165,7 +172,7 @@ PyObject* spmm(PyObject*, PyObject* const* a, Py_ssize_t nargs)
     at::Tensor fresh;
     PyObject* out = a[3];
     if (out == Py_None) {
-        fresh = at::Tensor(at::detail::empty_cuda({m, c->n}, kTypes[y_code], X->device(), std::nullopt));
+        fresh = result({m, c->n}, y_code, *X);
         Y = &fresh;
     } else {
         if (!tensor_of(out, "Y", &Y)) return nullptr;
@@ -238,7 +245,7 @@ PyObject* sddmm(PyObject*, PyObject* const* a, Py_ssize_t nargs)
     at::Tensor fresh;
     PyObject* out = a[4];
     if (out == Py_None) {
-        fresh = at::Tensor(at::detail::empty_cuda({c->nnzb, c->bs_r, c->bs_c}, kTypes[d_code], G->device(), std::nullopt));
+        fresh = result({c->nnzb, c->bs_r, c->bs_c}, d_code, *G);
         D = &fresh;
     } else {
         if (!tensor_of(out, "D", &D)) return nullptr;

@@ -128,3 +128,24 @@ def test_other_threads_run_while_a_plan_is_built():
     inside = [start, *(x for x in ticks if start <= x <= end), end]
     assert end - start > 0.01
     assert max(np.diff(inside)) < 0.3 * (end - start)
+
+
+@pytest.mark.gpu
+def test_results_come_through_the_dispatcher():
+    """A dispatch mode sees the results being made, as it saw torch.empty's."""
+    import torch
+    import paper_2007_13055_amd as lib
+    from torch.utils._python_dispatch import TorchDispatchMode
+
+    class Seen(TorchDispatchMode):
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            made.append((func.overloadpacket.__name__, tuple(args[0])))
+            return func(*args, **(kwargs or {}))
+
+    made = []
+    W = lib.bsr_create(32, 48, torch.ones((3, 16, 16), device="cuda"), np.array([0, 2, 1]), np.array([0, 2, 3]))
+    X, G = torch.ones((5, 48), device="cuda"), torch.ones((5, 32), device="cuda")
+    with Seen():
+        Y, D = lib.bsr_spmm(W, X), lib.bsr_sddmm(W, G, X)
+    assert made == [("empty", (5, 32)), ("empty", (3, 16, 16))]
+    assert bool((Y[:, :16] == 32).all()) and bool((D == 5).all())
