@@ -247,7 +247,8 @@ bool mfma_small_supports(const bsr_matrix* W);
 size_t mfma_thin_scratch_bytes(const bsr_matrix* W, int64_t m);   // bytes of the transposed copy of X
 // Sampled product by groups of stored blocks that share 128-byte wide slabs of G and X.
 bool sddmm_slab_supports(const bsr_matrix* W, int64_t m);
-void build_sddmm_slab_plan(const bsr_matrix* W);                    // into W->sl (once; caller holds W->sl_mu)
+void build_sddmm_slab_plan(const bsr_matrix* W);                    // into W->sl (once; caller holds W->sl_mu); may throw
+bool sddmm_slab_ready(const bsr_matrix* W);                         // builds the plan if need be; what follows needs it
 size_t sddmm_slab_plan_words(int64_t k, int32_t bs_r, int32_t bs_c, int64_t nnzb);
 size_t sddmm_slab_workspace(const bsr_matrix* W, int64_t m);        // bytes of partial results it would like
 bsr_status launch_sddmm_slab(const bsr_matrix* W, int m, const void* G, const void* X, void* D, bsr_dtype d_dtype, void* ws,

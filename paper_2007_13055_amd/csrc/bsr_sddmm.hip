@@ -469,7 +469,7 @@ extern "C" bsr_status bsr_sddmm_workspace_size(const bsr_matrix* W, int64_t m, s
     if (!W || !bytes) return BSR_ERR_NULL;
     *bytes = 0;
     if (m < 0) return BSR_ERR_SHAPE;
-    const size_t b = takes_slabs(W, m) ? sddmm_slab_workspace(W, m) : sddmm_thin_supports(W, m) ? sddmm_thin_workspace(W, m) : 0;
+    const size_t b = takes_slabs(W, m) && sddmm_slab_ready(W) ? sddmm_slab_workspace(W, m) : sddmm_thin_supports(W, m) ? sddmm_thin_workspace(W, m) : 0;
     *bytes = (b + 255) & ~(size_t)255;
     return BSR_OK;
 }
@@ -498,7 +498,7 @@ extern "C" bsr_status bsr_sddmm_ws(const bsr_matrix* W, int64_t m, const void* G
     }
     // m == 0 needs no special case: the kernels then read nothing and store zeros (an empty sum)
     const int mi = (int)m;
-    if (takes_slabs(W, m))
+    if (takes_slabs(W, m) && sddmm_slab_ready(W))
         return launch_sddmm_slab(W, mi, G_dev, X_dev, D_dev, d_dtype, workspace_dev, workspace_bytes, stream);
     if (sddmm_thin_supports(W, m) && d_dtype == BSR_F32)
         return launch_sddmm_thin(W, mi, G_dev, X_dev, D_dev, workspace_dev, workspace_bytes, stream);

@@ -430,11 +430,6 @@ bool sddmm_slab_supports(const bsr_matrix* W, int64_t m)
 
 size_t sddmm_slab_workspace(const bsr_matrix* W, int64_t m)
 {
-    if (!sddmm_slab_supports(W, m)) return 0;
-    {
-        std::lock_guard<std::mutex> lock(W->sl_mu);
-        build_sddmm_slab_plan(W);
-    }
     const int splits = sddmm_slab_splits(W, m);
     const int V = slab_shape_of(W->bs_r, W->bs_c).V;
     return splits > 1 ? (size_t)splits * W->sl.n_tiles * V * V * sizeof(float) : 0;
@@ -445,9 +440,7 @@ bsr_status launch_sddmm_slab(const bsr_matrix* W, int m, const void* G, const vo
 {
     {
         std::lock_guard<std::mutex> lock(W->sl_mu);
-        build_sddmm_slab_plan(W);
         if (!W->sl.sent) {
-            if (W->sl.host.size() > W->sl_words) return BSR_ERR_WORKSPACE;
             if (hipMemcpyAsync(W->sl_base, W->sl.host.data(), W->sl.host.size() * sizeof(int32_t), hipMemcpyHostToDevice, stream) != hipSuccess)
                 return BSR_ERR_HIP;
             // A copy recorded into a graph runs when the graph does, perhaps never: it serves that graph's products only,
@@ -474,7 +467,6 @@ bsr_status launch_sddmm_slab(const bsr_matrix* W, int m, const void* G, const vo
 void build_sddmm_slab_plan(const bsr_matrix* W)
 {
     if (W->sl.built) return;
-    W->sl.built = true;
     const int bs_r = W->bs_r, bs_c = W->bs_c;
     const int32_t *indptr = W->sl_indptr.data(), *indices = W->sl_indices.data();
     const slab_shape sh = slab_shape_of(bs_r, bs_c);
@@ -671,4 +663,16 @@ void build_sddmm_slab_plan(const bsr_matrix* W)
     plan.groups = group;
     plan.lds = lds;
     plan.n_tiles = (int32_t)(tiles.size() / 4);
+    plan.built = true;                                // not before: whatever throws leaves it to be built again
+}
+
+bool sddmm_slab_ready(const bsr_matrix* W)
+{
+    std::lock_guard<std::mutex> lock(W->sl_mu);
+    try {
+        build_sddmm_slab_plan(W);
+    } catch (const std::bad_alloc&) {                 // no memory for the plan: the caller takes a kernel that needs none
+        return false;
+    }
+    return W->sl.host.size() <= W->sl_words;
 }
