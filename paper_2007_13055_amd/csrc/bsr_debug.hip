@@ -3,7 +3,8 @@
 //   - index_pointer starts at 0, does not decrease, ends at the number of stored blocks;
 //   - every block_indices entry lies in [0, k/bs_c) (the paper's three BSR arrays, Background);
 //   - every row descriptor of the plan still names its block-row's range of index_pointer;
-//   - the plan in the caller's workspace still holds what bsr_create() wrote (a position-weighted sum).
+//   - the plan in the caller's workspace still holds what bsr_create() wrote (a position-weighted sum); before a sampled
+//     product by groups of blocks also that product's own plan, which its first call wrote.
 // Together with the host checks of m, k, n, alignment and types this bounds every address a kernel forms:
 // rows of X and Y come from m and the launch grid, columns from block_indices and the plan.  The check
 // costs one extra launch, a 16-byte copy and a stream synchronisation per product; it is skipped while the
@@ -38,6 +39,15 @@ __global__ __launch_bounds__(256) void bsr_debug_check(const int32_t* __restrict
     if (sum) atomicAdd(reinterpret_cast<unsigned long long*>(out + 2), sum);
 }
 
+__global__ __launch_bounds__(256) void bsr_debug_sum(const int32_t* __restrict__ words, size_t n, int32_t* __restrict__ out)
+{
+    const size_t stride = (size_t)gridDim.x * blockDim.x;
+    unsigned long long sum = 0;
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
+        sum += (unsigned long long)(uint32_t)words[i] * (unsigned long long)(i + 1);
+    if (sum) atomicAdd(reinterpret_cast<unsigned long long*>(out + 2), sum);
+}
+
 __global__ void bsr_debug_clear(int32_t* out)
 {
     if (threadIdx.x < 4) out[threadIdx.x] = 0;
@@ -52,17 +62,9 @@ uint64_t debug_plan_sum(const int32_t* words, size_t n)
     return sum;
 }
 
-bsr_status debug_check_device_arrays(const bsr_matrix* W, hipStream_t stream)
+// What a check left in debug_out: the code of a failure, else whether the sum is the one expected.
+static bsr_status debug_result(const bsr_matrix* W, hipStream_t stream, uint64_t expected)
 {
-    if (!W->debug || W->R <= 0 || !W->debug_out) return BSR_OK;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
-        (void)hipGetLastError();
-        return BSR_OK;                                // cannot synchronise inside a capture
-    }
-    hipLaunchKernelGGL(bsr_debug_clear, dim3(1), dim3(64), 0, stream, W->debug_out);
-    hipLaunchKernelGGL(bsr_debug_check, dim3(256), dim3(256), 0, stream, W->indptr, W->indices, W->row_order, W->row_desc,
-                       W->R, W->C, (int)W->nnzb, (int)W->debug_words, W->debug_out);
     int32_t host[4] = {0, 0, 0, 0};
     if (hipGetLastError() != hipSuccess) return BSR_ERR_HIP;
     if (hipMemcpyAsync(host, W->debug_out, sizeof(host), hipMemcpyDeviceToHost, stream) != hipSuccess) return BSR_ERR_HIP;
@@ -70,5 +72,22 @@ bsr_status debug_check_device_arrays(const bsr_matrix* W, hipStream_t stream)
     if (host[0] != 0) return (bsr_status)(16 - host[0]);
     uint64_t sum;
     std::memcpy(&sum, host + 2, sizeof(sum));
-    return sum == W->debug_sum ? BSR_OK : BSR_ERR_WORKSPACE;
+    return sum == expected ? BSR_OK : BSR_ERR_WORKSPACE;
+}
+
+bsr_status debug_check_device_arrays(const bsr_matrix* W, hipStream_t stream)
+{
+    if (!W->debug || W->R <= 0 || !W->debug_out || is_capturing(stream)) return BSR_OK;   // no synchronising inside a capture
+    hipLaunchKernelGGL(bsr_debug_clear, dim3(1), dim3(64), 0, stream, W->debug_out);
+    hipLaunchKernelGGL(bsr_debug_check, dim3(256), dim3(256), 0, stream, W->indptr, W->indices, W->row_order, W->row_desc,
+                       W->R, W->C, (int)W->nnzb, (int)W->debug_words, W->debug_out);
+    return debug_result(W, stream, W->debug_sum);
+}
+
+bsr_status debug_check_words(const bsr_matrix* W, const int32_t* dev, const std::vector<int32_t>& host, hipStream_t stream)
+{
+    if (!W->debug || !W->debug_out || is_capturing(stream)) return BSR_OK;
+    hipLaunchKernelGGL(bsr_debug_clear, dim3(1), dim3(64), 0, stream, W->debug_out);
+    hipLaunchKernelGGL(bsr_debug_sum, dim3(256), dim3(256), 0, stream, dev, host.size(), W->debug_out);
+    return debug_result(W, stream, debug_plan_sum(host.data(), host.size()));
 }

@@ -180,6 +180,8 @@ tune_opts read_tune_env();
 // Debug mode: checks index_pointer, block_indices and the plan on the device (one launch, a copy and a stream
 // synchronisation); BSR_OK when the handle is not in debug mode or the stream is being captured.
 bsr_status debug_check_device_arrays(const bsr_matrix* W, hipStream_t stream);
+// The same for words that were uploaded later: whether `dev` still holds `host` (BSR_ERR_WORKSPACE if not).
+bsr_status debug_check_words(const bsr_matrix* W, const int32_t* dev, const std::vector<int32_t>& host, hipStream_t stream);
 uint64_t debug_plan_sum(const int32_t* words, size_t n);
 
 // Each returns BSR_OK, BSR_ERR_UNSUPPORTED (shape not covered by that family) or BSR_ERR_HIP.

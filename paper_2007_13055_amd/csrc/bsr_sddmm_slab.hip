@@ -455,6 +455,8 @@ bsr_status launch_sddmm_slab(const bsr_matrix* W, int m, const void* G, const vo
         } else {
             order_after_upload(stream, W->sl.uploaded, W->sl.landed);
         }
+        const bsr_status dbg = debug_check_words(W, W->sl_base, W->sl.host, stream);   // its tile records are store offsets
+        if (dbg != BSR_OK) return dbg;
     }
     if (W->dtype == BSR_F32) return launch_types<float, float>(W, m, G, X, D, ws, ws_bytes, stream);
     if (W->dtype == BSR_F16)

@@ -78,3 +78,38 @@ def test_sampled_product_captured_first(oracle_mod, monkeypatch):
         right(D, f"replay {replay}")
         lib.bsr_sddmm(W, Gd, Xd, E)
         right(E, f"eager product after replay {replay}")
+
+
+@pytest.mark.gpu
+def test_debug_mode_checks_the_groups(oracle_mod, monkeypatch):
+    """BSR_SPMM_DEBUG=1: a word of the groups' plan damaged in device memory is reported and nothing is stored; repaired,
+    the product is the oracle's again."""
+    import torch
+    import paper_2007_13055_amd as lib
+    monkeypatch.setenv("BSR_SPMM_TUNE", "sd=2")
+    monkeypatch.setenv("BSR_SPMM_DEBUG", "1")
+    m = 300
+    p = wl.make_problem("slab", m, 19 * 32, 13 * 32, 32, 32, "f16", "f16", ("counts", np.full(13, 9)), ("normal", 1.0), ("normal", 1.0), 88)
+    G = wl.round_to_storage(np.random.default_rng(5).normal(size=(m, p.n)).astype(np.float32), "f16")
+    Do, So = oracle_mod.bsr_sddmm(G, p.X, p.block_indices, p.index_pointer, 32, 32)
+    W, Gd, Xd = lib.bsr_create(p.n, p.k, p.block_data, p.block_indices, p.index_pointer, dtype="f16"), to_device(G, "f16"), to_device(p.X, "f16")
+    D = torch.full((p.nnzb, 32, 32), 7.0, device="cuda")
+    words = W._tensors[3].view(torch.int32)
+    torch.cuda.synchronize()
+    before = words.clone()
+    lib.bsr_sddmm(W, Gd, Xd, D, d_dtype="f32")
+    torch.cuda.synchronize()
+    written = torch.nonzero(words != before).reshape(-1)
+    written = written[written >= int(written[-1]) - p.nnzb * 4]          # of those, tile records: the last that were written
+    assert written.numel() > 100
+    for at in (int(written[0]), int(written[-1])):
+        keep = int(words[at])
+        words[at] = keep ^ 1
+        D.fill_(7.0)
+        with pytest.raises(lib.BsrError) as e:
+            lib.bsr_sddmm(W, Gd, Xd, D, d_dtype="f32")
+        assert e.value.status == 7 and bool((D == 7.0).all())
+        words[at] = keep
+    lib.bsr_sddmm(W, Gd, Xd, D, d_dtype="f32")
+    torch.cuda.synchronize()
+    check(D.double().cpu().numpy().reshape(p.nnzb, -1), Do.reshape(p.nnzb, -1), So.reshape(p.nnzb, -1), p.tau, "repaired")
