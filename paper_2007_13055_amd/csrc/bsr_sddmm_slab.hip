@@ -139,14 +139,24 @@ __global__ __launch_bounds__(64 * (kWaves + kLoaders)) void bsr_sddmm_slab(const
     const int per_xcd = (int)gridDim.x / kXcds;
     const int job = (int)(blockIdx.x % (unsigned)kXcds) * per_xcd + (int)(blockIdx.x / (unsigned)kXcds);
     if (job >= n_groups * splits) return;             // whole workgroup: the grid is rounded up to 8
-    const int split = job / n_groups, group = job - split * n_groups;
+    // SPLIT: workgroups share out the rows, split by split; else (where there is no place for partial results) `splits`
+    // neighbouring ones share out a group's chunks
+    const int split = SPLIT ? job / n_groups : 0, group = SPLIT ? job - split * n_groups : job / splits;
     const int32_t* __restrict__ hdr = groups + (size_t)group * kHdr;   // uniform: scalar reads
-    const int n_slabs = hdr[0], n_g = hdr[1], first_chunk = hdr[2], n_chunks = hdr[3];
+    const int n_slabs = hdr[0], n_g = hdr[1];
+    int first_chunk = hdr[2], n_chunks = hdr[3];
+    if constexpr (!SPLIT) {
+        const int part = job - group * splits, c0 = n_chunks * part / splits, c1 = n_chunks * (part + 1) / splits;
+        if (c0 == c1) return;                         // whole workgroup
+        first_chunk += c0;
+        n_chunks = c1 - c0;
+    }
 
     const unsigned buf_bytes = (unsigned)n_slabs * kSlab, nb = (unsigned)slab_buffers(n_slabs);
     // steps [q0, q1) of 32 rows
     const unsigned n_steps = (unsigned)(m + kRows - 1) / kRows;
-    const int q0 = (int)(n_steps * (unsigned)split / (unsigned)splits), q1 = (int)(n_steps * (unsigned)(split + 1) / (unsigned)splits);
+    const int row_splits = SPLIT ? splits : 1;
+    const int q0 = (int)(n_steps * (unsigned)split / (unsigned)row_splits), q1 = (int)(n_steps * (unsigned)(split + 1) / (unsigned)row_splits);
 
     if (wave >= kWaves) {
         // ---- moving slabs: a wavefront that issues a load waits until the memory pipeline takes it, about as long as
@@ -359,11 +369,19 @@ int sddmm_slab_splits(const bsr_matrix* W, int64_t m)
     return (int)std::max<int64_t>(1, std::min<int64_t>({(int64_t)W->n_cu / std::max(W->sl.groups, 1), steps / 4, (int64_t)most}));
 }
 
+// Workgroups a group's chunks are shared out over where the rows are not split: as many as there are CUs to spare (each
+// reads all of the group's slabs; fp32 16x16, 6852 x (4800, 832), 10 %: 150 us, 242 with one for every 8 chunks).
+int sddmm_slab_parts(const bsr_matrix* W)
+{
+    return std::max(1, std::min(W->sl.most_chunks, W->n_cu / std::max(W->sl.groups, 1)));
+}
+
 template <typename T, typename O, int V, int CR, int CC, int NCH>
 bsr_status launch_shape(const bsr_matrix* W, int m, const void* G, const void* X, void* D, void* ws, size_t ws_bytes, hipStream_t stream)
 {
     int splits = sddmm_slab_splits(W, m);
-    if (splits > 1 && (!ws || ws_bytes < (size_t)splits * W->sl.n_tiles * V * V * sizeof(float))) splits = 1;
+    const bool split = splits > 1 && ws && ws_bytes >= (size_t)splits * W->sl.n_tiles * V * V * sizeof(float);
+    if (!split) splits = sddmm_slab_parts(W);
     const int64_t jobs = (int64_t)W->sl.groups * splits;
     const int grid = (int)((jobs + kXcds - 1) / kXcds * kXcds);
     const size_t lds = (size_t)W->sl.lds;
@@ -380,7 +398,7 @@ bsr_status launch_shape(const bsr_matrix* W, int m, const void* G, const void* X
                            W->bs_c, W->sl.groups, splits, W->sl.n_tiles);
         return hipGetLastError() == hipSuccess ? BSR_OK : BSR_ERR_HIP;
     };
-    if (splits == 1) return go(std::false_type{});
+    if (!split) return go(std::false_type{});
     const bsr_status st = go(std::true_type{});
     if (st != BSR_OK) return st;
     constexpr int NQ = V == 32 ? 4 : 1;
@@ -433,6 +451,19 @@ size_t sddmm_slab_workspace(const bsr_matrix* W, int64_t m)
     const int splits = sddmm_slab_splits(W, m);
     const int V = slab_shape_of(W->bs_r, W->bs_c).V;
     return splits > 1 ? (size_t)splits * W->sl.n_tiles * V * V * sizeof(float) : 0;
+}
+
+// Time in microseconds where the rows are not split (from 163 shapes, to 25 % where it matters): per 32 rows and
+// workgroup 0.4 for the slabs, or what the matrix cores take for the chunks of a SIMD, fp32 0.43, 0.85 and 1.7 a chunk of
+// four 16 x 16, two and four 32 x 32 tiles, 16-bit 0.03.
+double sddmm_slab_whole_us(const bsr_matrix* W, int64_t m)
+{
+    const slab_shape sh = slab_shape_of(W->bs_r, W->bs_c);
+    const int parts = sddmm_slab_parts(W), chunks = (W->sl.most_chunks + parts - 1) / parts, per_simd = (chunks + 3) / 4;
+    const double chunk = sh.V == 16 ? 0.43 : sh.CR == 2 ? 1.7 : 0.85;
+    const double step = W->dtype == BSR_F32 ? std::max(0.4, 0.1 + per_simd * chunk) : 0.4 + 0.03 * (per_simd - 1);
+    const int64_t steps = (m + kRows - 1) / kRows, turns = ((int64_t)W->sl.groups * parts + W->n_cu - 1) / W->n_cu;
+    return 4.0 + (double)(turns * steps) * step;
 }
 
 bsr_status launch_sddmm_slab(const bsr_matrix* W, int m, const void* G, const void* X, void* D, bsr_dtype d_dtype, void* ws,
@@ -590,7 +621,7 @@ void build_sddmm_slab_plan(const bsr_matrix* W)
     std::vector<int32_t> g_at((size_t)GS, -1), x_at((size_t)XS, -1), g_stamp((size_t)GS, -1), x_stamp((size_t)XS, -1);
     std::vector<int32_t> gl, xl;
     size_t i = 0;
-    int32_t group = 0, lds = 0;
+    int32_t group = 0, lds = 0, most_chunks = 0;
     while (i < order.size()) {
         gl.clear();
         xl.clear();
@@ -620,6 +651,7 @@ void build_sddmm_slab_plan(const bsr_matrix* W)
         }
         const int32_t ng = (int32_t)gl.size(), ns = ng + (int32_t)xl.size();
         lds = std::max(lds, slab_buffers(ns) * ns * kSlab);
+        most_chunks = std::max(most_chunks, (int32_t)(i - first));
         int32_t h[kHdr] = {ns, ng, (int32_t)(recs.size() / 4), (int32_t)(i - first)};
         for (int32_t z = 0; z < ns; ++z) h[kHdrSlabsAt + z] = (z < ng ? gl[(size_t)z] : xl[(size_t)(z - ng)]) * line;
         hdr.insert(hdr.end(), h, h + kHdr);
@@ -663,6 +695,7 @@ void build_sddmm_slab_plan(const bsr_matrix* W)
     plan.host.insert(plan.host.end(), recs.begin(), recs.end());
     plan.host.insert(plan.host.end(), tiles.begin(), tiles.end());
     plan.groups = group;
+    plan.most_chunks = most_chunks;
     plan.lds = lds;
     plan.n_tiles = (int32_t)(tiles.size() / 4);
     plan.built = true;                                // not before: whatever throws leaves it to be built again
