@@ -254,7 +254,7 @@ void build_sddmm_slab_plan(const bsr_matrix* W);                    // into W->s
 bool sddmm_slab_ready(const bsr_matrix* W);                         // builds the plan if need be; what follows needs it
 size_t sddmm_slab_plan_words(int64_t k, int32_t bs_r, int32_t bs_c, int64_t nnzb);
 size_t sddmm_slab_workspace(const bsr_matrix* W, int64_t m);        // bytes of partial results it would like
-double sddmm_slab_whole_us(const bsr_matrix* W, int64_t m);         // its time without them, estimated
+double sddmm_slab_us(const bsr_matrix* W, int64_t m, bool split);   // its time with them or without, estimated
 bsr_status launch_sddmm_slab(const bsr_matrix* W, int m, const void* G, const void* X, void* D, bsr_dtype d_dtype, void* ws,
                              size_t ws_bytes, hipStream_t stream);
 // Sampled product, 16x1 fp32 blocks in block-column order.

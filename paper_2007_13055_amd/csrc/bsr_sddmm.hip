@@ -413,10 +413,13 @@ bsr_status launch_sddmm_shape(const bsr_matrix* W, int m, const void* G, const v
 // own: 16-bit ones take the groups from 256 rows on (530 x (576, 384): 8.1 us against 11.0); fp32 ones, three
 // quarters of whose matrix-core tiles are padding, only when the lines are many.
 //
-// All that is with room for the partial results.  Without, the groups are too few to fill the chip, and what a block
-// by itself takes is held against what the groups take then (13 bf16 32x32 blocks, 5000 rows: 12.7 us against 73; fp32 32x32
-// 1003 x (4096, 4096), 10 %: 44 against 94; bf16 16x16 4096 x (3072, 768): 77 against 50).  8-wide blocks stay with the
-// groups (bf16 2178 x (512, 5632), 17 %: 29 us against 118, fp32 5317 x (5376, 640), 12 %: 197 against 393).
+// All that is for 16-bit blocks with room for the partial results.  Without, the groups are too few to fill the chip; and
+// fp32 products are bound by the matrix cores, which a block per workgroup keeps as busy and spreads more evenly.  So
+// these take the groups only if that is estimated to be quicker than the blocks by themselves as well.  Groups against
+// blocks, us: without room 13 bf16 32x32 blocks, 5000 rows 73, 12.7; bf16 16x16 4096 x (3072, 768) 50, 77; fp32
+// 32x32 1003 x (4096, 4096) 10 % 94, 44; fp32 with room 64x64 8192 x (4096, 4096) 10 % 926, 325, 32x32 716, 348,
+// 16x16 778, 1196; 64x64 7596 x (7296, 3648) 4 % 234, 282, 41 blocks of 64x64, 1601 rows 19.5, 37.8.  8-wide blocks stay with
+// the groups (bf16 2178 x (512, 5632), 17 %: 29 against 118, fp32 5317 x (5376, 640), 12 %: 197 against 393).
 bool takes_slabs(const bsr_matrix* W, int64_t m, size_t workspace_bytes)
 {
     if (!sddmm_slab_supports(W, m)) return false;
@@ -427,10 +430,14 @@ bool takes_slabs(const bsr_matrix* W, int64_t m, size_t workspace_bytes)
     const int elems = W->bs_r * W->bs_c;
     const double alone = rows / 128 * (W->dtype != BSR_F32 || elems < 1024 ? 0.6 : elems < 4096 ? 0.9 : 2.8);
     if (!(lines > 350e6 || (W->nnzb <= 256 && 3.0 + alone > (W->nnzb <= 64 ? 13.0 : 17.0))) || !sddmm_slab_ready(W)) return false;
-    if (workspace_bytes >= sddmm_slab_workspace(W, m)) return true;
-    // the blocks by themselves: one block's time, the lines of all, or (fp32) the matrix cores at 100 TFLOP/s
-    const double by_block = 3.0 + std::max({alone, lines / 16.5e6, W->dtype == BSR_F32 ? 2 * rows * W->nnzb * elems / 1e8 : 0.0});
-    return sddmm_slab_whole_us(W, m) < by_block;
+    const bool room = workspace_bytes >= sddmm_slab_workspace(W, m);
+    if (room && W->dtype != BSR_F32) return true;
+    double by_block = std::max(alone, lines / 16.5e6);
+    if (W->dtype == BSR_F32) {                        // several blocks to a CU share its matrix cores
+        const double block = elems < 1024 ? 0.45 : elems < 2048 ? 0.78 : elems < 4096 ? 1.4 : 2.6;
+        by_block = std::max(by_block, rows / 128 * (double)((W->nnzb + W->n_cu - 1) / W->n_cu) * block);
+    }
+    return sddmm_slab_us(W, m, room) < 3.0 + by_block;
 }
 
 template <typename T, typename O>

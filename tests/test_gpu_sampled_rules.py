@@ -17,6 +17,9 @@ RULES = [
     (250, 20, 30, (8, 8), "bf16", 100, "block", "block"),
     (3000, 90, 90, (8, 8), "f32", 2400, "block", "block"),           # 1.8 GB of lines
     (3500, 90, 90, (8, 8), "f32", 2400, "groups", "groups"),         # 2.2 GB
+    (1600, 20, 20, (64, 64), "f32", 40, "groups", "block"),          # fp32: few blocks, split
+    (1100, 60, 60, (32, 32), "f32", 1500, "block", "block"),         # matrix cores busy either way
+    (1100, 100, 100, (16, 16), "f32", 4000, "groups", "groups"),     # 1.1 GB of lines
 ]
 
 
