@@ -258,7 +258,8 @@ double sddmm_slab_us(const bsr_matrix* W, int64_t m, bool split);   // its time 
 bsr_status launch_sddmm_slab(const bsr_matrix* W, int m, const void* G, const void* X, void* D, bsr_dtype d_dtype, void* ws,
                              size_t ws_bytes, hipStream_t stream);
 // Sampled product, 16x1 fp32 blocks in block-column order.
-bool sddmm_thin_supports(const bsr_matrix* W, int64_t m);
+bool sddmm_thin_supports(const bsr_matrix* W, int64_t m, size_t workspace_bytes);
+bool sddmm_transposes(const bsr_matrix* W, int64_t m);              // whether scratch for a transposed copy of X is lent (and worth it)
 size_t sddmm_thin_workspace(const bsr_matrix* W, int64_t m);
 bsr_status launch_sddmm_thin(const bsr_matrix* W, int m, const void* G, const void* X, void* D, void* ws, size_t ws_bytes, hipStream_t stream);
 // XT[c][i] = X[i][c], rows of XT (m rounded up to 4) floats apart

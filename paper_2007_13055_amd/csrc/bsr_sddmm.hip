@@ -447,8 +447,7 @@ bsr_status launch_sddmm_types(const bsr_matrix* W, int m, const void* G, const v
     BSR_MFMA_SHAPES(launch_sddmm_shape, T, O, br, bc, W, m, G, X, D, stream);
     if constexpr (std::is_same<T, float>::value && std::is_same<O, float>::value) {
         // thin blocks with the caller's scratch lent: transposed copy of X, then the matrix-core kernel
-        if (mfma_thin_supports(W) && m >= 32 && W->scratch && W->scratch_bytes >= mfma_thin_scratch_bytes(W, m) &&
-            ((int64_t)m + 3) * W->k < ((int64_t)1 << 30)) {
+        if (sddmm_transposes(W, m)) {
             float* XT = static_cast<float*>(W->scratch);
             const bsr_status st = launch_transpose_f32((const float*)X, XT, m, (int)W->k, stream);
             if (st != BSR_OK) return st;
@@ -485,7 +484,7 @@ extern "C" bsr_status bsr_sddmm_workspace_size(const bsr_matrix* W, int64_t m, s
     if (!W || !bytes) return BSR_ERR_NULL;
     *bytes = 0;
     if (m < 0) return BSR_ERR_SHAPE;
-    const size_t b = takes_slabs(W, m, SIZE_MAX) ? sddmm_slab_workspace(W, m) : sddmm_thin_supports(W, m) ? sddmm_thin_workspace(W, m) : 0;
+    const size_t b = takes_slabs(W, m, SIZE_MAX) ? sddmm_slab_workspace(W, m) : sddmm_thin_supports(W, m, SIZE_MAX) ? sddmm_thin_workspace(W, m) : 0;
     *bytes = (b + 255) & ~(size_t)255;
     return BSR_OK;
 }
@@ -516,7 +515,7 @@ extern "C" bsr_status bsr_sddmm_ws(const bsr_matrix* W, int64_t m, const void* G
     const int mi = (int)m;
     if (takes_slabs(W, m, workspace_dev ? workspace_bytes : 0))
         return launch_sddmm_slab(W, mi, G_dev, X_dev, D_dev, d_dtype, workspace_dev, workspace_bytes, stream);
-    if (sddmm_thin_supports(W, m) && d_dtype == BSR_F32)
+    if (sddmm_thin_supports(W, m, workspace_dev ? workspace_bytes : 0) && d_dtype == BSR_F32)
         return launch_sddmm_thin(W, mi, G_dev, X_dev, D_dev, workspace_dev, workspace_bytes, stream);
     if (W->dtype == BSR_F32) return launch_sddmm_types<float, float>(W, mi, G_dev, X_dev, D_dev, stream);
     if (W->dtype == BSR_F16) return d_dtype == BSR_F32 ? launch_sddmm_types<_Float16, float>(W, mi, G_dev, X_dev, D_dev, stream)

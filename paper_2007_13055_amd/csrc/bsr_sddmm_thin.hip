@@ -12,7 +12,7 @@
 //
 // What bounds it: per 32 rows and workgroup 64 KiB from L2 and the last-level cache (1 us at 2864 x (4672, 3840)), about
 // as much matrix-core time (chunks that a run leaves partly empty included) and 0.6 us of LDS traffic; 1.4 us together.
-// Times: transpose_us() below.
+// Times: other_us() below.
 //
 // LDS bank conflicts.  A column's line is at index col ^ (bit 2 of col) and its eight 16-byte pieces are XORed by bits
 // 2-4 of col: 16 neighbouring lanes of a write (two pieces of 8 columns 4 apart) then fall on 16 different pieces of 256
@@ -22,6 +22,7 @@
 // Few workgroups and many rows: the rows are split, the partial results go to the caller's workspace and are added
 // in split order by a second kernel.
 #include <algorithm>
+#include <cmath>
 
 #include "bsr_mfma_common.h"
 
@@ -190,41 +191,57 @@ __global__ __launch_bounds__(256) void bsr_sddmm_thin_sum(const f32x4* __restric
 }
 
 // Time of this kernel in microseconds, and the split of the rows at which it is least (to 10 % over the shapes of
-// transpose_us(), 7 to 175 us): start and end 6; a step 0.7 and 0.5 for every chunk of blocks, a run's last one
+// other_us(), 7 to 175 us): start and end 6; a step 0.7 and 0.5 for every chunk of blocks, a run's last one
 // half full; the partial results written and read again at 6 TB/s in a second launch of 2.5.
 struct thin_plan { double us; int splits; };
-thin_plan plan_of(const bsr_matrix* W, int64_t m)
+thin_plan plan_of(const bsr_matrix* W, int64_t m, int most_splits = 16)
 {
     const int64_t ranges = W->thin_pos_stride - 1, jobs = (int64_t)((W->R + kSlots - 1) / kSlots) * ranges, steps = (m + kTile - 1) / kTile;
     const double step = 0.7 + 0.5 * ((double)W->nnzb / ((double)W->R * ranges) + 8) / 16, sum = (double)W->nnzb * 128 / 6e6;
     thin_plan best = {1e30, 1};
-    for (int s = 1; s <= 16 && s <= steps; ++s) {
+    for (int s = 1; s <= most_splits && (s == 1 || s <= steps); ++s) {
         const double t = 6 + (double)((jobs * s + W->n_cu - 1) / W->n_cu) * (1.0 + (double)((steps + s - 1) / s) * step) + (s > 1 ? 2.5 + s * sum : 0);
         if (t < best.us) best = {t, s};
     }
     return best;
 }
 
-// The other way: X^T into the workspace (4 TB/s) and a wavefront or two per slot over all rows, 0.0115 us each where
-// there are few slots, 1.4 million blocks times rows a microsecond where there are many, 13000 blocks where there are
-// few rows.  Times of that way and of this, us:
+// The kernels of bsr_sddmm.hip, one of which runs instead.
+// With scratch lent and 32 rows or more: X^T into the scratch (4 TB/s) and a wavefront or two per slot over all rows,
+// 0.0115 us each where there are few slots, 1.4 million blocks times rows a microsecond where there are many, 13000
+// blocks where there are few rows.  Times of that way and of this, us:
 //     256 x (4096, 4096) 5 %       14.1   16.9      2864 x (4672, 3840) 5.7 %   163   175     264 x (3968, 256)    9.7  12.7
-//     3394 x (544, 2880) 4.3 %     65.2   27.3      4504 x (2560, 256)  8.2 %    62    23     6 x (4352, 3264)    24.2  10.8
-//     1546 x (1632, 1152) 25 %     41.2   34.5      320 x (256, 6608)   10 %   13.5  11.6     2 x (3200, 7104)    20.6  13.3
-double transpose_us(const bsr_matrix* W, int64_t m)
+//     3394 x (544, 2880) 4.3 %     65.2   27.3      4504 x (2560, 256)  8.2 %    62    23     1546 x (1632, 1152) 41.2  34.5
+// Else a lane per block and column: a workgroup's start (200 a microsecond), and per row 0.035 or what the lines of X take
+// that the block-rows touch, 160000 a microsecond while X is 8 MB or less, 90000 beyond.  That way, this and this unsplit:
+//     6 x (4352, 3264) 10 %        10.5    6.8   6.8     8 x (8080, 2256) 2.3 %   5.0   8.4  8.6    31 x (2048, 4096) 10 %   9.2   6.3   6.3
+//     3394 x (544, 2880) 4.3 %      149     29   139     7078 x (320, 304) 27 %   248    52  716    256 x (4096, 4096) 5 %  36.8  17.8  17.7
+double other_us(const bsr_matrix* W, int64_t m)
 {
     const double rows = (double)m, blocks = (double)W->nnzb;
-    return 5 + 8 * rows * (double)W->k / 4e6 + std::max({0.0115 * rows, rows * blocks / 1.4e6, blocks / 13000});
+    if (sddmm_transposes(W, m))
+        return 5 + 8 * rows * (double)W->k / 4e6 + std::max({0.0115 * rows, rows * blocks / 1.4e6, blocks / 13000});
+    const double lines = std::ceil((double)W->k / 32), touched = W->R * lines * (1 - std::exp(-blocks / ((double)W->R * lines)));
+    const double rate = rows * (double)W->k * 4 <= 8e6 ? 160e3 : 90e3;
+    return 3.5 + (blocks / 64 + 0.5 * W->R) / 200 + rows * std::max(0.035, touched / rate);
 }
 
 }  // namespace
 
-// The longest run of a (block-row, range) has to fit the accumulators, 8 chunks of 16 blocks; and this kernel has to be
-// the quicker one, as estimated.
-bool sddmm_thin_supports(const bsr_matrix* W, int64_t m)
+bool sddmm_transposes(const bsr_matrix* W, int64_t m)
 {
-    return W->thin_pos != nullptr && W->thin_max_range <= 128 && m > 0 && W->nnzb < (1 << 26) &&
-           (W->env_tune.sd == 2 || (W->env_tune.sd != 1 && plan_of(W, m).us < 0.95 * transpose_us(W, m)));
+    return mfma_thin_supports(W) && m >= 32 && W->scratch && W->scratch_bytes >= mfma_thin_scratch_bytes(W, m) &&
+           (m + 3) * W->k < ((int64_t)1 << 30);
+}
+
+// The longest run of a (block-row, range) has to fit the accumulators, 8 chunks of 16 blocks; and this kernel has to be
+// the quicker one, as estimated, with the splits that the memory allows.
+bool sddmm_thin_supports(const bsr_matrix* W, int64_t m, size_t workspace_bytes)
+{
+    if (W->thin_pos == nullptr || W->thin_max_range > 128 || m <= 0 || W->nnzb >= (1 << 26)) return false;
+    if (W->env_tune.sd) return W->env_tune.sd == 2;
+    const bool room = workspace_bytes >= sddmm_thin_workspace(W, m);
+    return plan_of(W, m, room ? 16 : 1).us < 0.95 * other_us(W, m);
 }
 
 size_t sddmm_thin_workspace(const bsr_matrix* W, int64_t m)

@@ -20,6 +20,10 @@ RULES = [
     (1600, 20, 20, (64, 64), "f32", 40, "groups", "block"),          # fp32: few blocks, split
     (1100, 60, 60, (32, 32), "f32", 1500, "block", "block"),         # matrix cores busy either way
     (1100, 100, 100, (16, 16), "f32", 4000, "groups", "groups"),     # 1.1 GB of lines
+    (3000, 34, 2880, (16, 1), "f32", 4200, "groups", "block"),       # thin: rows split, or a lane per column
+    (6, 270, 3264, (16, 1), "f32", 88000, "groups", "groups"),       # no row to split
+    (8, 300, 2256, (16, 1), "f32", 15500, "block", "block"),
+    (100, 160, 4096, (16, 1), "f32", 33000, "block", "groups"),      # transposed copy, or turned over in LDS
 ]
 
 
