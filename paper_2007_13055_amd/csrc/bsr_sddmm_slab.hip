@@ -107,15 +107,15 @@ __device__ __forceinline__ u32x4 read_tr(const unsigned char* p, int s)
     return u32x4{a.x, a.y, b.x, b.y};
 }
 
-// Where output (a, c .. c+3) of a tile goes: the tile's quadrants (V/2 x V/2) each lie whole in one block; off[q] is
-// the element of D at quadrant q's (0, 0), or -1 where no block is stored.
+// Where output (a, c .. c+3) of a tile goes (null: nowhere): the tile's quadrants (V/2 x V/2) each lie whole in one
+// block; off[q] is the element of D at quadrant q's (0, 0), or -1 where no block is stored.
 template <typename O, int V>
-__device__ __forceinline__ void store_tile4(O* __restrict__ D, const i32x4& off, int bs_c, int a, int c, const f32x4& v)
+__device__ __forceinline__ O* tile4(O* __restrict__ D, const i32x4& off, int bs_c, int a, int c)
 {
     constexpr int H = V / 2;
     const int top = c >= H ? off.y : off.x, bottom = c >= H ? off.w : off.z;
     const int o = a >= H ? bottom : top;
-    if (o >= 0) store4<O>(D + (size_t)(unsigned)o + (a % H) * bs_c + c % H, v.x, v.y, v.z, v.w);
+    return o >= 0 ? D + (size_t)(unsigned)o + (a % H) * bs_c + c % H : nullptr;
 }
 
 template <typename T, typename O, int V, int CR, int CC, int NCH, bool SPLIT>
@@ -124,7 +124,7 @@ __global__ __launch_bounds__(64 * (kWaves + kLoaders)) void bsr_sddmm_slab(const
                                                              const i32x4* __restrict__ chunks,
                                                              const i32x4* __restrict__ tiles, O* __restrict__ D,
                                                              float* __restrict__ part, int m, int k, int n, int bs_c,
-                                                             int n_groups, int splits, int n_tiles)
+                                                             int n_groups, int splits, int n_tiles, int pieces)
 {
     constexpr bool F32 = std::is_same<T, float>::value;
     constexpr int S = (int)sizeof(T);
@@ -233,12 +233,6 @@ __global__ __launch_bounds__(64 * (kWaves + kLoaders)) void bsr_sddmm_slab(const
     const int mine = max(0, (n_chunks - wave + kWaves - 1) / kWaves);
 
     acc_t acc[NCH][NT];
-#pragma unroll
-    for (int j = 0; j < NCH; ++j)
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-#pragma unroll
-            for (int e = 0; e < 4 * NQ; ++e) acc[j][t][e] = 0.f;
 
     const unsigned lane_off = operand_lane_offset<T, V>(lane);
     // byte offsets of chunk j's tiles in a buffer: G rows, X columns
@@ -270,70 +264,89 @@ __global__ __launch_bounds__(64 * (kWaves + kLoaders)) void bsr_sddmm_slab(const
                 }
     };
 
+    // The rows in `pieces`, each summed by itself and added to what the pieces before it have left in D or among the
+    // partial results: one chain over all rows is the less exact the longer it is.  A result of 16 bits does not show it,
+    // and its kernel has no such loop (batched backward 44.1 us with one of a single piece, 41.7 without).
+    const int n_pieces = std::is_same<O, float>::value ? pieces : 1;
     unsigned buf = 0;
-    for (int q = q0; q < q1; ++q) {
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // step q has landed, step q - 1 is read
-        const unsigned at = buf * buf_bytes;
-        if constexpr (F32) {
+    for (int piece = 0; piece < n_pieces; ++piece) {
+        const int first_q = q0 + (q1 - q0) * piece / n_pieces, end_q = q0 + (q1 - q0) * (piece + 1) / n_pieces;
 #pragma unroll
-            for (int j = 0; j < NCH; ++j)
-                if (j < mine) {                       // uniform
-                    const float *ap[CR], *bp[CC];
-#pragma unroll
-                    for (int u = 0; u < CR; ++u) ap[u] = reinterpret_cast<const float*>(lds + ((at + a_off(j, u)) ^ lane_off));
-#pragma unroll
-                    for (int u = 0; u < CC; ++u) bp[u] = reinterpret_cast<const float*>(lds + ((at + b_off(j, u)) ^ lane_off));
-#pragma unroll
-                    for (int s = 0; s < STEPS; ++s) {
-                        constexpr int KS = V == 32 ? 2 : 4;
-                        float av[CR], bv[CC];
-#pragma unroll
-                        for (int u = 0; u < CR; ++u) av[u] = ap[u][s * KS * 32];
-#pragma unroll
-                        for (int u = 0; u < CC; ++u) bv[u] = bp[u][s * KS * 32];
-#pragma unroll
-                        for (int ur = 0; ur < CR; ++ur)
-#pragma unroll
-                            for (int uc = 0; uc < CC; ++uc) {
-                                if constexpr (V == 32) acc[j][ur * CC + uc] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv[uc], av[ur], acc[j][ur * CC + uc], 0, 0, 0);
-                                else                   acc[j][ur * CC + uc] = __builtin_amdgcn_mfma_f32_16x16x4f32(bv[uc], av[ur], acc[j][ur * CC + uc], 0, 0, 0);
-                            }
-                    }
-                }
-        } else {
-            // the next chunk's operands are read while one is multiplied
-            operands o[2];
-            if (mine > 0) read(o[0], 0, at);
-#pragma unroll
-            for (int j = 0; j < NCH; ++j) {
-                if (j < mine) {                       // uniform
-                    if (j + 1 < NCH && j + 1 < mine) read(o[(j + 1) & 1], j + 1 < NCH ? j + 1 : 0, at);
-                    multiply(o[j & 1], j);
-                }
-            }
-        }
-        buf = buf == nb - 1 ? 0 : buf + 1;
-    }
-
-    // lane holds, of every tile, row a = lane mod V and columns c .. c+3, c = 8 q + 4 (lane / V) (V = 16: 4 (lane / 16))
-    const int a = lane % V, c0 = 4 * (lane / V);
-#pragma unroll
-    for (int j = 0; j < NCH; ++j)
-        if (j < mine) {
-            const int t0 = rec[j].w & 0x0fffffff, live = (int)((unsigned)rec[j].w >> 28);
+        for (int j = 0; j < NCH; ++j)
 #pragma unroll
             for (int t = 0; t < NT; ++t)
-                if (t < live) {
 #pragma unroll
-                    for (int g = 0; g < NQ; ++g) {
-                        const f32x4 v = {acc[j][t][4 * g], acc[j][t][4 * g + 1], acc[j][t][4 * g + 2], acc[j][t][4 * g + 3]};
-                        if constexpr (SPLIT)
-                            *reinterpret_cast<f32x4*>(part + ((((size_t)split * n_tiles + t0 + t) * NQ + g) * 64 + lane) * 4) = v;
-                        else
-                            store_tile4<O, V>(D, tiles[t0 + t], bs_c, a, 8 * g + c0, v);
+                for (int e = 0; e < 4 * NQ; ++e) acc[j][t][e] = 0.f;
+        for (int q = first_q; q < end_q; ++q) {
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");   // step q has landed, step q - 1 is read
+            const unsigned at = buf * buf_bytes;
+            if constexpr (F32) {
+#pragma unroll
+                for (int j = 0; j < NCH; ++j)
+                    if (j < mine) {                       // uniform
+                        const float *ap[CR], *bp[CC];
+#pragma unroll
+                        for (int u = 0; u < CR; ++u) ap[u] = reinterpret_cast<const float*>(lds + ((at + a_off(j, u)) ^ lane_off));
+#pragma unroll
+                        for (int u = 0; u < CC; ++u) bp[u] = reinterpret_cast<const float*>(lds + ((at + b_off(j, u)) ^ lane_off));
+#pragma unroll
+                        for (int s = 0; s < STEPS; ++s) {
+                            constexpr int KS = V == 32 ? 2 : 4;
+                            float av[CR], bv[CC];
+#pragma unroll
+                            for (int u = 0; u < CR; ++u) av[u] = ap[u][s * KS * 32];
+#pragma unroll
+                            for (int u = 0; u < CC; ++u) bv[u] = bp[u][s * KS * 32];
+#pragma unroll
+                            for (int ur = 0; ur < CR; ++ur)
+#pragma unroll
+                                for (int uc = 0; uc < CC; ++uc) {
+                                    if constexpr (V == 32) acc[j][ur * CC + uc] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv[uc], av[ur], acc[j][ur * CC + uc], 0, 0, 0);
+                                    else                   acc[j][ur * CC + uc] = __builtin_amdgcn_mfma_f32_16x16x4f32(bv[uc], av[ur], acc[j][ur * CC + uc], 0, 0, 0);
+                                }
+                        }
+                    }
+            } else {
+                // the next chunk's operands are read while one is multiplied
+                operands o[2];
+                if (mine > 0) read(o[0], 0, at);
+#pragma unroll
+                for (int j = 0; j < NCH; ++j) {
+                    if (j < mine) {                       // uniform
+                        if (j + 1 < NCH && j + 1 < mine) read(o[(j + 1) & 1], j + 1 < NCH ? j + 1 : 0, at);
+                        multiply(o[j & 1], j);
                     }
                 }
+            }
+            buf = buf == nb - 1 ? 0 : buf + 1;
         }
+
+        // lane holds, of every tile, row a = lane mod V and columns c .. c+3, c = 8 q + 4 (lane / V) (V = 16: 4 (lane / 16))
+        const int a = lane % V, c0 = 4 * (lane / V);
+#pragma unroll
+        for (int j = 0; j < NCH; ++j)
+            if (j < mine) {
+                const int t0 = rec[j].w & 0x0fffffff, live = (int)((unsigned)rec[j].w >> 28);
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+                    if (t < live) {
+#pragma unroll
+                        for (int g = 0; g < NQ; ++g) {
+                            f32x4 v = {acc[j][t][4 * g], acc[j][t][4 * g + 1], acc[j][t][4 * g + 2], acc[j][t][4 * g + 3]};
+                            if constexpr (SPLIT) {
+                                f32x4* dst = reinterpret_cast<f32x4*>(part + ((((size_t)split * n_tiles + t0 + t) * NQ + g) * 64 + lane) * 4);
+                                if (n_pieces > 1 && piece > 0) v += *dst;
+                                *dst = v;
+                            } else if (O* dst = tile4<O, V>(D, tiles[t0 + t], bs_c, a, 8 * g + c0)) {
+                                if constexpr (std::is_same<O, float>::value) {
+                                    if (piece > 0) v += *reinterpret_cast<const f32x4*>(dst);
+                                }
+                                store4<O>(dst, v.x, v.y, v.z, v.w);
+                            }
+                        }
+                    }
+            }
+    }
 }
 
 // Sum of the S partial results of every tile, in split order.
@@ -357,7 +370,7 @@ __global__ __launch_bounds__(256) void bsr_sddmm_slab_sum(const float* __restric
         for (int j = 0; j < 8; ++j)
             if (s + j < splits) v += x[j];
     }
-    store_tile4<O, V>(D, tiles[t], bs_c, lane % V, 8 * g + 4 * (lane / V), v);
+    if (O* dst = tile4<O, V>(D, tiles[t], bs_c, lane % V, 8 * g + 4 * (lane / V))) store4<O>(dst, v.x, v.y, v.z, v.w);
 }
 
 // Splits of the rows for m rows: as many as give every CU one workgroup, each at least 4 steps (128 rows) long; at
@@ -379,9 +392,14 @@ int sddmm_slab_parts(const bsr_matrix* W)
 template <typename T, typename O, int V, int CR, int CC, int NCH>
 bsr_status launch_shape(const bsr_matrix* W, int m, const void* G, const void* X, void* D, void* ws, size_t ws_bytes, hipStream_t stream)
 {
+    constexpr bsr_dtype d_dtype = std::is_same<O, float>::value ? BSR_F32 : BSR_F16;   // or BSR_BF16: 16 bits
     int splits = sddmm_slab_splits(W, m);
     const bool split = splits > 1 && ws && ws_bytes >= (size_t)splits * W->sl.n_tiles * V * V * sizeof(float);
     if (!split) splits = sddmm_slab_parts(W);
+    // Four chains at least for a result in fp32, as a workgroup per block keeps (root mean square error of fp32
+    // 8192 x (4096, 4096): 8.1e-7, 1.62e-6 with one); rounding to 16 bits hides the difference.
+    const int chains = split ? splits : 1, steps = (m + kRows - 1) / kRows;
+    const int pieces = d_dtype == BSR_F32 ? std::max(1, std::min((4 + chains - 1) / chains, steps / chains)) : 1;
     const int64_t jobs = (int64_t)W->sl.groups * splits;
     const int grid = (int)((jobs + kXcds - 1) / kXcds * kXcds);
     const size_t lds = (size_t)W->sl.lds;
@@ -395,7 +413,7 @@ bsr_status launch_shape(const bsr_matrix* W, int m, const void* G, const void* X
         if (attr != hipSuccess) return BSR_ERR_HIP;
         hipLaunchKernelGGL((bsr_sddmm_slab<T, O, V, CR, CC, NCH, SPLIT>), dim3((unsigned)grid), dim3(64 * (kWaves + kLoaders)), lds, stream,
                            (const T*)G, (const T*)X, W->sl_base, chunks, tiles, (O*)D, (float*)ws, m, (int)W->k, (int)W->n,
-                           W->bs_c, W->sl.groups, splits, W->sl.n_tiles);
+                           W->bs_c, W->sl.groups, splits, W->sl.n_tiles, pieces);
         return hipGetLastError() == hipSuccess ? BSR_OK : BSR_ERR_HIP;
     };
     if (!split) return go(std::false_type{});
