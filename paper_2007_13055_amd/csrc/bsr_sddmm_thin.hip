@@ -135,9 +135,17 @@ __global__ __launch_bounds__(kThreads) void bsr_sddmm_thin_rows(const float* __r
     }
     const unsigned ga = kXBuf + line_of(wave * 16 + lo) + ((unsigned)(16 * g) ^ swz_of(wave * 16 + lo));
 
-    f32x4 acc[NCH];
+    // The rows' sums are kept in chains, as many as keep any kernel that this one replaces: four of a quarter of the rows,
+    // or two where the rows are split and registers are few (32 chunk registers a chain).  Unsplit and few registers: four short
+    // chains a step, added to what there is (16 vector instructions more for 8 of the matrix cores; everywhere that cost
+    // 5-10 %: 1491 x (2800, 1712) 34 % 79 to 87 us).
+    constexpr bool SHORT = NCH > 4 && !SPLIT;
+    constexpr int CH = SHORT ? 1 : NCH > 4 ? 2 : 4;
+    f32x4 acc[NCH][CH];
 #pragma unroll
-    for (int c = 0; c < NCH; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int c = 0; c < NCH; ++c)
+#pragma unroll
+        for (int e = 0; e < CH; ++e) acc[c][e] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     // Steps: t is multiplied, t + 1 goes from registers to LDS, t + 2 is fetched into them.  The loads of a step are taken
     // by the memory pipe over about as many clocks as its matrix instructions take, and a wavefront that issues them
@@ -160,10 +168,19 @@ __global__ __launch_bounds__(kThreads) void bsr_sddmm_thin_rows(const float* __r
         for (int c = 0; c < NCH; ++c)
             if (16 * c < cnt) {                       // uniform
                 const f32x4 b0 = *reinterpret_cast<const f32x4*>(buf + at[c]), b1 = *reinterpret_cast<const f32x4*>(buf + (at[c] ^ 64u));
+                if constexpr (SHORT) {
+                    f32x4 s[4];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[e], b0[e], acc[c], 0, 0, 0);
+                    for (int e = 0; e < 4; ++e) s[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[e], b0[e], f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[e], b1[e], acc[c], 0, 0, 0);
+                    for (int e = 0; e < 4; ++e) s[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[e], b1[e], s[e], 0, 0, 0);
+                    acc[c][0] += (s[0] + s[1]) + (s[2] + s[3]);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[c][e % CH] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0[e], b0[e], acc[c][e % CH], 0, 0, 0);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[c][e % CH] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1[e], b1[e], acc[c][e % CH], 0, 0, 0);
+                }
             }
         if (!is_x) advance(t);
     }
@@ -171,7 +188,12 @@ __global__ __launch_bounds__(kThreads) void bsr_sddmm_thin_rows(const float* __r
     float* out = SPLIT ? D + (size_t)split * nnzb * 16 : D;
 #pragma unroll
     for (int c = 0; c < NCH; ++c)
-        if (16 * c + lo < cnt) *reinterpret_cast<f32x4*>(out + ((size_t)first + 16 * c + lo) * 16 + 4 * g) = acc[c];
+        if (16 * c + lo < cnt) {
+            f32x4 v = acc[c][0];
+            if constexpr (CH == 2) v += acc[c][1];
+            if constexpr (CH == 4) v = (v + acc[c][1]) + (acc[c][2] + acc[c][3]);
+            *reinterpret_cast<f32x4*>(out + ((size_t)first + 16 * c + lo) * 16 + 4 * g) = v;
+        }
 }
 
 __global__ __launch_bounds__(256) void bsr_sddmm_thin_sum(const f32x4* __restrict__ part, f32x4* __restrict__ D, int splits, int quads)
