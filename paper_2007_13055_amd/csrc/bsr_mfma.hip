@@ -157,8 +157,9 @@ bool mfma_supports(const bsr_matrix* W)
 }
 
 // Which matrix-core kernel serves this product.
-//   ksplit  fewer than about 6000 (m-tile, block-row) items: the stored blocks of a block-row are spread over the
-//           wavefronts of a workgroup, otherwise most of the chip would idle
+//   ksplit  fewer than about 6000 (m-tile, block-row) items and block-rows of more than a block or two (or few items of
+//           tall blocks): the stored blocks of a block-row are spread over the wavefronts of a workgroup, otherwise
+//           most of the chip would idle
 //   tile    many rows of X and blocks at least 32 rows tall: 128 x bs_r tiles of Y, the W block and
 //           the X tile staged in LDS with coalesced reads, XCD-aware launch order
 //   stripe  16x16 blocks of a 16-bit type, many rows of X, and 64 full rows of X fit in LDS: the
@@ -173,8 +174,13 @@ bsr_status launch_mfma(const spmm_args& a, const tune_opts& tune)
         // thresholds from timed trials over many sizes (bsr_tune's candidates) on MI355X
         const int MM = a.W->bs_r >= 32 ? 32 : 16;
         const int64_t sub = (a.m + MM - 1) / MM;
-        if (sub * a.W->R < 6000 && (a.W->mean_row_blocks > 1.5 || (sub * a.W->R < 768 && mfma_ksplit_reaches(a.W))))
-            variant = 2;
+        // block-rows of a block or two are left to the direct kernel, except few items of taller blocks, which take longer
+        // where one wavefront has the whole block (1.3 blocks a row, k-split against direct, us: fp32 32x32 64 items
+        // 3.1, 4.5, 512 items 4.0, 6.8; f16 32x32 2.9, 2.8 and 3.2, 3.7; f16 64x64 3.0, 3.8 and 4.2, 8.3; 16x16 64
+        // items 2.84, 2.53, 640 items 2.93, 2.76).  768 is where the k-split kernel goes over to 32-row tiles; it is no
+        // crossing of times (f16 32x32, 1216 items: 3.7, and 4.6 direct).
+        const bool tall_few = a.W->bs_r >= 32 && sub * a.W->R < 768 && mfma_ksplit_reaches(a.W);
+        if (sub * a.W->R < 6000 && (a.W->mean_row_blocks > 1.5 || tall_few)) variant = 2;
         else if (a.W->bs_r >= 32 && a.m >= 512) variant = 3;
         else if (a.m >= 256 && mfma_stripe_supports(a.W, 16)) variant = 4;
         else if (a.W->mean_row_blocks > 4.0) variant = 2;     // 16-row blocks the tile kernel does not take

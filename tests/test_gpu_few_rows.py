@@ -51,3 +51,20 @@ def test_wide_rows_of_x_stay_accepted(oracle_mod, dtype, m, k):
     lib.bsr_spmm(W, X, Y)
     torch.cuda.synchronize()
     check(Y.double().cpu().numpy(), Yo, So, 1e-5, f"{dtype} m={m} k={k}", out_dtype=dtype)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("bs,variant", [(16, 1), (32, 2), (64, 2)])
+def test_short_block_rows(oracle_mod, monkeypatch, bs, variant):
+    """Three blocks in every second block-row, 1.5 on average: the direct kernel for 16-row blocks, the k-split kernel
+    for few items of taller ones; told by the bits of the kernel forced."""
+    import paper_2007_13055_amd as lib
+    p = wl.make_problem("short", 64, 20 * bs, 64 * bs, bs, bs, "f32", "f32", ("counts", [3, 0] * 32), ("normal", 1.0), ("normal", 1.0), 77)
+    Yo, So = oracle_mod.bsr_spmm(p.X, p.block_data, p.block_indices, p.index_pointer, p.n)
+    Y, _ = gpu_product(p)
+    check(Y, Yo, So, p.tau, f"short rows {bs}")
+    forced = {}
+    for v in (1, 2):
+        monkeypatch.setenv("BSR_SPMM_TUNE", f"variant={v}")
+        forced[v], _ = gpu_product(p, path=lib.PATH_MFMA)
+    assert not np.array_equal(forced[1], forced[2]) and np.array_equal(Y, forced[variant])
