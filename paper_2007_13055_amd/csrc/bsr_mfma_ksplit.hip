@@ -268,6 +268,10 @@ bsr_status launch_ksplit_tile(const spmm_args& a, const tune_opts& tune)
     // when every workgroup has a CU to itself (16 where the wavefront's tile is 16 rows of W), at most 4 up to four
     // workgroups per CU and 2 beyond (starting wavefronts costs time too, about 11 cycles each per XCD, and with many
     // workgroups the CUs are busy anyway), and no more than LDS has room for.  Strips carry less work each: twice that.
+    // Strips with 4, 8, 16 wavefronts, us: 64 of them (16 x (3072, 1024), 64x64 fp32, a few long block-rows) 6.3, 5.6, 5.5;
+    // 256 (4096^2, likewise) 11.5, 9.4, 8.9; 384 (fp32 32x32, even) 6.1, 5.7, 6.8; 1024 (even: fp32 64x64 8.1, 9.5, 12.7; with
+    // long block-rows 24.6, 19.5, 23.7); 4096 (even 18.7, 24.0, 38.6; with long block-rows 25.8, 28.6, 49.1 -- there, at
+    // 256 rows, 4 would be the quicker, at 128 rows and 1024 of them f16 12.3, 12.0, 16.4).
     const int64_t tiles = (m + MM - 1) / MM;
     int64_t blocks = tiles * R;
     int per = tune.a > 0 ? tune.a : (STR == 4 && std::is_same<T, float>::value ? 1 : 2);

@@ -124,7 +124,9 @@ bsr_status launch_generic(const spmm_args& a, const tune_opts& tune)
     // aligned, so every piece is aligned), single elements otherwise
     constexpr int V16 = 16 / (int)sizeof(T);
     // rows of X per wavefront: 8 amortise the reads of W best when there are many rows; up to m = 8
-    // the wavefronts are few and short, and 4 rows each (twice the wavefronts) finish sooner
+    // the wavefronts are few and short, and 4 rows each (twice the wavefronts) finish sooner.  3 rows take one wavefront of 4
+    // (against two of 2, us: (1024, 1024) 16x16 fp32 2.8, 2.6; (4096, 4096) 32x32 f16 3.7, 4.0; (2048, 8192) 64x64
+    // bf16 4.5, 4.8); 2 rows one of 2 (4096^2: 3.3, with one of 4 3.6)
     const int rows = tune.mt > 0 ? tune.mt : (m > 8 ? 8 : (m >= 3 ? 4 : m));
     auto with_tm = [&](auto vec_tag) -> bsr_status {
         if (rows >= 8) return go(std::integral_constant<int, 8>{}, vec_tag);
