@@ -28,9 +28,12 @@
 //
 // Measured (MI355X, operands in the last-level cache or beyond): bf16 16x16, 4096 x (3072, 768), 1843 blocks: 21.1 us
 // (15 + 6 for the sum of 6 splits) where a workgroup per 64 x 64 columns took 37.2; bf16 32x32, 4096 x (4096, 4096),
-// 10 %: 42.8 against 99; fp16 64x64, 8192^3, 819 blocks by a power law: 110 against 151.  A step of 32 rows takes
-// 0.18 us plus 0.12 us per round of chunks, which is what the LDS reads of the chunks take (5 KiB for up to 4 tiles);
-// the loads alone run at the rate of the last-level cache (7.4 TB/s for what is not in an XCD's L2).
+// 10 %: 42.8 against 99; fp16 64x64, 8192^3, 819 blocks by a power law: 103 (94 + 9) against 151.  A step of 32 rows takes
+// 0.18 us plus 0.12 us per round of chunks.  Counters: on the bf16 product the matrix cores are busy 14 % and the LDS 18 % of
+// the time and 3.3 TB/s come from beyond L2: a step's chain from barrier over LDS reads to the last product is what
+// takes it, two multiplying wavefronts a SIMD deep.  The fp16 one waits for slabs, 456 MB from beyond L2 (62 us at the 7.4 TB/s
+// that such loads reach at best).  fp32 products are bound by the matrix cores and mostly left to a workgroup per block
+// (takes_slabs() in bsr_sddmm.hip).
 #include <algorithm>
 #include <numeric>
 #include <cmath>
