@@ -418,7 +418,8 @@ bsr_status launch_sddmm_shape(const bsr_matrix* W, int m, const void* G, const v
 // these take the groups only if that is estimated to be quicker than the blocks by themselves as well.  Groups against
 // blocks, us: without room 13 bf16 32x32 blocks, 5000 rows 73, 12.7; bf16 16x16 4096 x (3072, 768) 50, 77; fp32
 // 32x32 1003 x (4096, 4096) 10 % 94, 44; fp32 with room 64x64 8192 x (4096, 4096) 10 % 926, 325, 32x32 716, 348,
-// 16x16 778, 1196; 64x64 7596 x (7296, 3648) 4 % 234, 282, 41 blocks of 64x64, 1601 rows 19.5, 37.8.  8-wide blocks stay with
+// 16x16 798, 1170, 64x16 7778 x (3520, 6976) 15 % 1150, 712; 64x64 7596 x (7296, 3648) 4 % 234, 282, 41 blocks of
+// 64x64, 1601 rows 19.5, 37.8, 75 of 64x16, 5869 rows 26, 60.  8-wide blocks stay with
 // the groups (bf16 2178 x (512, 5632), 17 %: 29 against 118, fp32 5317 x (5376, 640), 12 %: 197 against 393).
 bool takes_slabs(const bsr_matrix* W, int64_t m, size_t workspace_bytes)
 {
@@ -434,8 +435,12 @@ bool takes_slabs(const bsr_matrix* W, int64_t m, size_t workspace_bytes)
     if (room && W->dtype != BSR_F32) return true;
     double by_block = std::max(alone, lines / 16.5e6);
     if (W->dtype == BSR_F32) {                        // several blocks to a CU share its matrix cores
-        const double block = elems < 1024 ? 0.45 : elems < 2048 ? 0.78 : elems < 4096 ? 1.4 : 2.6;
-        by_block = std::max(by_block, rows / 128 * (double)((W->nnzb + W->n_cu - 1) / W->n_cu) * block);
+        // us for 128 rows of a block: 16-row or -column blocks of 256, 512 and 1024 elements, others of 1024, 2048, 4096;
+        // half as much again (narrow), or a seventh, where a block has a CU to itself
+        const bool narrow = std::min(W->bs_r, W->bs_c) == 16;
+        const double block = narrow ? (elems < 512 ? 0.45 : elems < 1024 ? 0.52 : 0.85) : (elems < 2048 ? 0.78 : elems < 4096 ? 1.4 : 2.6);
+        const int64_t per_cu = (W->nnzb + W->n_cu - 1) / W->n_cu;
+        by_block = std::max(by_block, rows / 128 * block * (per_cu > 1 ? (double)per_cu : narrow ? 1.5 : 1.15));
     }
     return sddmm_slab_us(W, m, room) < 3.0 + by_block;
 }

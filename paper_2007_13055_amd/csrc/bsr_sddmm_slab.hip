@@ -474,7 +474,7 @@ size_t sddmm_slab_workspace(const bsr_matrix* W, int64_t m)
     return splits > 1 ? (size_t)splits * W->sl.n_tiles * V * V * sizeof(float) : 0;
 }
 
-// Estimated time in microseconds (from 200 shapes, to 25 % where it matters): per 32 rows and workgroup 0.4 for the slabs,
+// Estimated time in microseconds (from 250 shapes, to 30 % where it matters): per 32 rows and workgroup 0.4 for the slabs,
 // or what the matrix cores take for the chunks of a SIMD, fp32 0.43, 0.85 and 1.7 a chunk of four 16 x 16, two and four
 // 32 x 32 tiles, 16-bit 0.03; the partial results written and read again at 6 TB/s in a second launch.
 double sddmm_slab_us(const bsr_matrix* W, int64_t m, bool split)
@@ -485,10 +485,11 @@ double sddmm_slab_us(const bsr_matrix* W, int64_t m, bool split)
     auto step = [&](double per_simd) { return W->dtype == BSR_F32 ? std::max(0.4, 0.1 + per_simd * chunk) : 0.4 + 0.03 * (per_simd - 1); };
     const int64_t jobs = (int64_t)W->sl.groups * splits * parts, turns = (jobs + W->n_cu - 1) / W->n_cu;
     const double most = std::ceil(std::ceil((double)W->sl.most_chunks / parts) / 4);
-    const double mean = std::max(1.0, (double)(W->sl.tiles_at - W->sl.chunks_at) / 4 / W->sl.groups / parts / 4);
+    const double mean = std::ceil((double)(W->sl.tiles_at - W->sl.chunks_at) / 4 / W->sl.groups / parts / 4);
     const int64_t steps = ((m + kRows - 1) / kRows + splits - 1) / splits;
     const double us = (double)steps * std::max(step(most), (double)turns * step(mean));   // the fullest group, or all in turn
-    return 4.0 + us + (splits > 1 ? 4.0 + splits * (double)W->nnzb * W->bs_r * W->bs_c * 8 / 6e6 : 0.0);
+    const double pass = (double)W->nnzb * W->bs_r * W->bs_c * 8 / 6e6;   // all results written and read again
+    return 4.0 + us + (splits > 1 ? 4.0 + splits * pass : W->dtype == BSR_F32 ? 3 * pass : 0.0);   // whole rows: in four pieces
 }
 
 bsr_status launch_sddmm_slab(const bsr_matrix* W, int m, const void* G, const void* X, void* D, bsr_dtype d_dtype, void* ws,

@@ -19,6 +19,8 @@ RULES = [
     (3500, 90, 90, (8, 8), "f32", 2400, "groups", "groups"),         # 2.2 GB
     (1600, 20, 20, (64, 64), "f32", 40, "groups", "block"),          # fp32: few blocks, split
     (1100, 60, 60, (32, 32), "f32", 1500, "block", "block"),         # matrix cores busy either way
+    (1100, 30, 100, (64, 16), "f32", 1500, "block", "block"),
+    (5800, 13, 20, (64, 16), "f32", 75, "groups", "block"),
     (1100, 100, 100, (16, 16), "f32", 4000, "groups", "groups"),     # 1.1 GB of lines
     (3000, 34, 2880, (16, 1), "f32", 4200, "groups", "block"),       # thin: rows split, or a lane per column
     (6, 270, 3264, (16, 1), "f32", 88000, "groups", "groups"),       # no row to split
