@@ -50,6 +50,7 @@ size_t plan_bytes(int64_t R, int64_t nnzb, int32_t bs_r, int32_t bs_c, int64_t k
     // blocks of one row: the pairs by block-column and their range positions
     b += sizeof(int32_t) * wide_plan_words(R, k, nnzb, bs_r, bs_c);
     b += sizeof(int32_t) * sddmm_slab_plan_words(k, bs_r, bs_c, nnzb);
+    b += sizeof(int32_t) * sweep_plan_words(R * bs_r, k, bs_r, bs_c, nnzb);
     b += 256;                                         // debug mode's result words
     return (b + 255) & ~(size_t)255;
 }
@@ -300,6 +301,7 @@ bsr_status bsr_create(bsr_matrix** out, int64_t n, int64_t k, int32_t bs_r, int3
     std::vector<int32_t> cnt((size_t)R);
     for (int64_t r = 0; r < R; ++r) cnt[(size_t)r] = index_pointer_host[r + 1] - index_pointer_host[r];
     const size_t order_words = (((size_t)R * 4 + 255) & ~(size_t)255) / 4;   // row_order, padded to 256 B
+    W->staging.reserve(plan_bytes(R, nnzb, bs_r, bs_c, k) / sizeof(int32_t));   // address space only: pages come as they are written
     W->staging.assign(order_words + (size_t)R * kRowDescWords + 64, 0);
     std::iota(W->staging.begin(), W->staging.begin() + R, 0);
     // Block-rows whose outputs fill whole 128-byte lines of Y by themselves have nothing to gain from their
@@ -387,22 +389,29 @@ bsr_status bsr_create(bsr_matrix** out, int64_t n, int64_t k, int32_t bs_r, int3
     const bool small = (bs_r == 8 || bs_r == 16) && (bs_c == 8 || bs_c == 16) && !(bs_r == 16 && bs_c == 16) &&
                        n % 16 == 0 && k % 16 == 0 && nnzb > 0 &&
                        nnzb * bs_r * bs_c * (dtype == BSR_F32 ? 4 : 2) < ((int64_t)1 << 31);
-    if (small) {
+    if (small) W->sb_rows = (int32_t)(n / 16);
+    if (small && (dtype == BSR_F32 || small_blocks_16bit(W, 16))) {
         const int SR = 16 / bs_r, SC = 16 / bs_c;
         const int64_t TR = n / 16;
         const int32_t blk_bytes = bs_r * bs_c * (dtype == BSR_F32 ? 4 : 2);
         struct entry { int32_t tc; int32_t off[4]; };
         std::vector<std::vector<entry>> rows((size_t)TR);
         size_t n_entries = 0;
+        std::vector<int32_t> from((size_t)(k / 16));   // the tile-row's first entry of each tile-column
         for (int64_t tr = 0; tr < TR; ++tr) {
             auto& list = rows[(size_t)tr];
+            std::fill(from.begin(), from.end(), -1);
             for (int qa = 0; qa < SR; ++qa) {
                 const int64_t r = tr * SR + qa;
                 for (int32_t p = index_pointer_host[r]; p < index_pointer_host[r + 1]; ++p) {
                     const int32_t tc = block_indices_host[p] / SC, pos = qa * SC + block_indices_host[p] % SC;
                     entry* slot = nullptr;
-                    for (auto& e : list)
-                        if (e.tc == tc && e.off[pos] == INT32_MIN) { slot = &e; break; }
+                    if (from[(size_t)tc] >= 0) {
+                        for (size_t i = (size_t)from[(size_t)tc]; i < list.size() && !slot; ++i)
+                            if (list[i].tc == tc && list[i].off[pos] == INT32_MIN) slot = &list[i];
+                    } else {
+                        from[(size_t)tc] = (int32_t)list.size();
+                    }
                     if (!slot) {
                         list.push_back(entry{tc, {INT32_MIN, INT32_MIN, INT32_MIN, INT32_MIN}});
                         slot = &list.back();
@@ -437,7 +446,6 @@ bsr_status bsr_create(bsr_matrix** out, int64_t n, int64_t k, int32_t bs_r, int3
         W->sb_desc = W->row_order + desc_at;
         W->sb_entries = W->row_order + ent_at;
         W->sb_cols = W->row_order + col_at;
-        W->sb_rows = (int32_t)TR;
         words = (col_at + n_entries + 63) & ~(size_t)63;
     }
     if (nnzb > 0) {                                   // block-row of every stored block
@@ -451,6 +459,7 @@ bsr_status bsr_create(bsr_matrix** out, int64_t n, int64_t k, int32_t bs_r, int3
     build_group_plan(W, index_pointer_host, block_indices_host, &words);
     build_thinrow_plan(W, index_pointer_host, block_indices_host, &words);
     build_wide_plan(W, index_pointer_host, block_indices_host, &words);
+    build_sweep_plan(W, index_pointer_host, block_indices_host, &words);
     size_t upload_words = words;
     {   // the per-m tables sit behind everything else, 256-byte aligned
         W->item_desc = const_cast<int32_t*>(W->row_order) + words;
@@ -531,6 +540,17 @@ static bsr_path auto_path(const bsr_matrix* W, int64_t m, bsr_dtype y_dtype)
     return BSR_PATH_WAVE;
 }
 
+// 8-wide blocks whose n or k is no multiple of 16 have no 16x16 tiles, so a caller that asks for the matrix cores is
+// refused.  The library's own choice takes the sweep kernel all the same where the wavefront kernels would start many
+// wavefronts (us, bf16 8x8, wavefront kernels and sweep: 64 x (504, 520), 4032 wavefronts 4.7, 4.8; 32 x (520, 4104), 10 %,
+// 2080 wavefronts 5.5, 6.0, 64 rows 7.7, 6.0; 16 x (4104, 1032), 5 %, 8208 wavefronts 6.9, 4.4; 1000 rows 269, 9.7) and the
+// result is rounded to 16 bits: in fp32 it would show that 64 partial sums are more exact than 2 to 8 (fp32, m = 400,
+// (512, 8192), 30 %: 1.3e-7 against 3.2e-7).
+static bool sweeps_odd_sizes(const bsr_matrix* W, int64_t m, bsr_dtype y_dtype)
+{
+    return y_dtype != BSR_F32 && m >= 16 && W->n * ((m + 7) / 8) >= 4000 && !mfma_small_supports(W) && mfma_sweep_supports(W);
+}
+
 bsr_status bsr_query_path(const bsr_matrix* W, int64_t m, bsr_path* path_out)
 {
     if (!W || !path_out) return BSR_ERR_NULL;
@@ -584,6 +604,7 @@ bsr_status run_product(const spmm_args& a, bsr_path path, const tune_opts& t)
     if (path == BSR_PATH_MFMA) {
         if (mfma_thin_supports(a.W)) return launch_mfma_thin(a, t);
         if (mfma_small_supports(a.W)) return launch_mfma_small(a, t);
+        if (t.variant == 6) return launch_mfma_sweep(a, t);
         if (mfma_wide_supports(a.W) && a.y_dtype == BSR_F32) return launch_mfma_wide(a, t);
         if (!mfma_supports(a.W)) return BSR_ERR_UNSUPPORTED;
         return launch_mfma(a, t);
@@ -610,7 +631,11 @@ bsr_status bsr_spmm_ex(const bsr_matrix* W, int64_t m, const void* X_dev, void* 
         // a remembered thin-block choice needs its scratch still lent
         if (tuned && path == BSR_PATH_MFMA && mfma_thin_supports(W) && !(t.variant == 2 && mfma_thinrow_supports(W)) &&
             (!W->scratch || W->scratch_bytes < mfma_thin_scratch_bytes(W, m))) tuned = false;
-        if (!tuned) { path = auto_path(W, m, y_dtype); if (!t.from_env) t = tune_opts{}; }
+        if (!tuned) {
+            path = auto_path(W, m, y_dtype);
+            if (!t.from_env) t = tune_opts{};
+            if (path == BSR_PATH_WAVE && !t.from_env && sweeps_odd_sizes(W, m, y_dtype)) { path = BSR_PATH_MFMA; t.variant = 6; }
+        }
     }
     return run_product(spmm_args{W, m, X_dev, Y_dev, y_dtype, (hipStream_t)hip_stream}, path, t);
 }
@@ -631,10 +656,13 @@ static std::vector<tuned_choice> tune_candidates(const bsr_matrix* W, int64_t m)
             add(BSR_PATH_MFMA, 2, 0, 0, 0, 0);
         if (W->scratch && W->scratch_bytes >= mfma_thin_scratch_bytes(W, m) && m >= 16)
             for (int a : {4, 6, 8, 10, 12, 14, 16}) add(BSR_PATH_MFMA, 1, 0, 0, a, 0);
-    } else if (mfma_small_supports(W)) {
-        if (m >= 8)
+    } else if (mfma_small_supports(W) || mfma_sweep_supports(W)) {
+        if (m >= 8 && mfma_small_supports(W) && W->dtype == BSR_F32)
             for (int nw : {2, 4, 8})
-                for (int per : {1, 2, 4}) add(BSR_PATH_MFMA, 0, nw, 0, per, 0);
+                for (int per : {1, 2, 4}) add(BSR_PATH_MFMA, 7, nw, 0, per, 0);
+        if (m >= 8 && (mfma_small_supports(W) || sweeps_odd_sizes(W, m, W->dtype)))
+            for (int mt : {1, 2, 4})
+                for (int quads : {1, 2, 4, 8}) add(BSR_PATH_MFMA, 6, quads, mt, 0, 0);
     } else if (mfma_supports(W) && m >= 8) {
         add(BSR_PATH_MFMA, 0, 0, 0, 0, 0);                                  // the library's own choice
         for (int mt : {1, 2}) {

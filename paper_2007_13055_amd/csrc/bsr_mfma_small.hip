@@ -1,4 +1,4 @@
-// Matrix-core kernel for blocks smaller than an MFMA tile: bs_r, bs_c in {8, 16}, not both 16.
+// Matrix-core kernel for blocks smaller than an MFMA tile, few rows of X: bs_r, bs_c in {8, 16}, not both 16.
 //
 // The paper's own shape grid includes 8x8 blocks, below the 16x16 minimum of the matrix cores.  The
 // plan groups the stored blocks into 16x16 TILES of W (2x2, 2x1 or 1x2 blocks; a position without a
@@ -209,20 +209,20 @@ bsr_status launch_small_types(const spmm_args& a, const tune_opts& t)
 
 }  // namespace
 
-bool mfma_small_supports(const bsr_matrix* W)
-{
-    const bool shape = (W->bs_r == 8 || W->bs_r == 16) && (W->bs_c == 8 || W->bs_c == 16) && !(W->bs_r == 16 && W->bs_c == 16);
-    return shape && W->sb_desc != nullptr && W->sb_rows > 0;
-}
+bool mfma_small_supports(const bsr_matrix* W) { return W->sb_rows > 0; }
 
+// Many rows, and most products of 16-bit blocks, go to the sweep kernel, which reads X once for 64 to 512 outputs instead
+// of 16 (microseconds of this kernel and that one, 8x8 blocks: bf16 17 x (512, 512) 3.9, 3.8; 260 x (512, 4096), 10 %
+// 9.6, 5.8; 2000 x (6016, 640), 20 % 82, 20.  fp32 waits for the matrix cores in both: 100 x (512, 512) 4.0, 5.2;
+// 260 x (512, 4096), 10 % 13.8, 13.0; 700 x the same 23.5, 19.6; 2000 x (4096, 1024), 5 % 50, 34).
 bsr_status launch_mfma_small(const spmm_args& a, const tune_opts& t)
 {
     const bsr_matrix* W = a.W;
     if (!mfma_small_supports(W)) return BSR_ERR_UNSUPPORTED;
+    const bool sweep = t.variant == 6 || (t.variant != 7 && (W->dtype == BSR_F32 ? a.m >= kSweepRowsF32 : !small_blocks_16bit(W, a.m)));
+    if (!W->sb_desc || (sweep && mfma_sweep_supports(W))) return launch_mfma_sweep(a, t);
     if (W->dtype == BSR_F32) return launch_small_types<float, float>(a, t);
     if (W->dtype == BSR_F16) return a.y_dtype == BSR_F32 ? launch_small_types<_Float16, float>(a, t)
                                                          : launch_small_types<_Float16, _Float16>(a, t);
-    if (W->dtype == BSR_BF16) return a.y_dtype == BSR_F32 ? launch_small_types<__bf16, float>(a, t)
-                                                          : launch_small_types<__bf16, __bf16>(a, t);
-    return BSR_ERR_UNSUPPORTED;
+    return a.y_dtype == BSR_F32 ? launch_small_types<__bf16, float>(a, t) : launch_small_types<__bf16, __bf16>(a, t);
 }

@@ -1,0 +1,452 @@
+// Matrix-core kernel for blocks with sides 8 or 16 (not both 16), swept over the columns of X.
+//
+// A stored 8x8 block touches 16 bytes of a row of X, so a kernel that fetches X block by block moves whole lines for a
+// fraction of them, once per 16 outputs.  Here a workgroup takes TM = 16 * SUB rows of X and a few QUADS (64 outputs, four
+// groups of 16 rows of W each).  It sweeps over the columns in WINDOWS of kSlabs * 128 bytes per row: the rows of X come in
+// once, in whole lines, and stay in LDS while all of the workgroup's stored blocks of the window are multiplied; the sums
+// stay in registers from the first window to the last.
+//
+//   granule  16 bytes of a row of X (8 16-bit or 4 fp32 columns), what a lane feeds to an MFMA step
+//   entry    one group of 16 rows of W times four granules, anywhere in the window: one v_mfma_f32_16x16x32 (fp32: four
+//            16x16x4) per 16 rows of X.  Blocks of 8 rows come two block-rows to an entry: of the 16 x 4 granules 55 % hold
+//            stored values at 20 % density, where 16x16 tiles of W hold 34 %.
+//   round    an entry for each of a quad's four groups.  Its record holds, for each granule and half of the 16 rows, {byte
+//            offset of the values in block_data, place of the granule in the window}; what is not stored has an offset
+//            past the end of W (read as zeros), a granule that is not there the place of a granule of zeros.  A group that
+//            has fewer entries in a window than the others multiplies zeros (fp32: is left out).
+//   list     a quad's rounds by window: one run of records from end to end, so that records are read two rounds and values
+//            one round ahead whatever the windows hold.
+//
+// Twelve wavefronts: eight multiply, each a quad or every KS-th round of one (the shares are added in fixed order at the
+// end), four only move X into a ring of two windows (loads that write LDS directly, one barrier per window).
+//
+// What bounds it: the LDS reads of X (16 KiB a round and wavefront; 832 of the 1000-1180 clocks that a round of eight
+// wavefronts takes, counters: LDS busy 38 %, matrix cores 32 % of a whole 16-bit product); fp32 the matrix cores.  Windows
+// of 512 columns rather than 256: 54 against 63 us, values two rounds ahead 55, progress words polled in LDS in place of
+// the barrier 56, twelve multiplying wavefronts 54 (bf16 8x8, 5889 x (1216, 5184), 21.8 %).
+// Measured (us, with the kernel of 16x16 tiles and now): that product 432, 54; fp16 8x8, 2662 x (832, 6528), 19.3 % 181,
+// 32; fp16, 2285 x (6016, 1536), 15.6 %, power law 163, 37; fp32 8x8, 3607 x (320, 5056), 7.3 % 83, 47.
+#include <algorithm>
+#include <cmath>
+#include <numeric>
+
+#include "bsr_mfma_common.h"
+
+using namespace bsr_dev;
+
+namespace {
+
+constexpr int kSlabs = 8;                             // 128-byte slabs of a window
+constexpr int kRing = 2;                              // windows in LDS
+constexpr int kWaves = 8;                             // wavefronts that multiply
+constexpr int kLoaders = 4;                           // wavefronts that move X
+constexpr int kMine = kSlabs / kLoaders;              // slabs each of them moves
+constexpr int kPitch = kSlabs * 2048 + 128;           // bytes of 16 rows of a window, and behind them the granule of zeros
+constexpr int kZeroAt = kSlabs * 2048;
+constexpr int kNone = 0xFFFF;                         // place of the granule of zeros
+constexpr int kXcds = 8;
+constexpr int kRowsOut = 32;                          // rows of Y per pass of the epilogue
+constexpr int kLdOut = 64 + 4;                        // floats of a row there
+
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+
+template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+// 16 bytes per lane from buffer `rsrc` at the lane's offset to LDS bytes [lds_base, + 1024) in lane order.
+__device__ __forceinline__ void load_to_lds(const i32x4& rsrc, unsigned offset, unsigned lds_base)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_base), "v"(offset), "s"(rsrc) : "memory");
+}
+// The 16-byte pieces of row r of a slab are stored XOR turn(r): sixteen rows' pieces of one column fill all banks once
+// (measured: 6.4 clocks a read, as contiguous ones; 8.2 with r mod 8, 16 unturned).
+__device__ __forceinline__ constexpr unsigned turn(unsigned r) { return (r >> 1) & 7; }
+__device__ __forceinline__ void window_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+template <typename T, typename O, int SUB>
+__global__ __launch_bounds__(64 * (kWaves + kLoaders), 3) void bsr_mfma_sweep(
+    const T* __restrict__ X, const T* __restrict__ data, unsigned w_bytes, const i32x4* __restrict__ recs,
+    const int32_t* __restrict__ win_ptr, const i32x4* __restrict__ quads, O* __restrict__ Y, int m, int k, int n,
+    int n_tiles, int tiles_padded, int n_quads, int n_win, int q_log, int bs_r, int row_bytes)
+{
+    constexpr int S = (int)sizeof(T);
+    constexpr int CH = 16 / S;                        // columns of a granule
+    constexpr int BUF = SUB * kPitch;
+    extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];   // [kRing][SUB][kPitch], then the epilogue's tiles
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // group by group (the longest quads first), the tiles of a group side by side: where the tiles are padded to a
+    // multiple of 8, all groups of a tile share an XCD and its L2 copy of the rows
+    const int group = (int)(blockIdx.x / (unsigned)tiles_padded), tile = (int)(blockIdx.x % (unsigned)tiles_padded);
+    if (tile >= n_tiles) return;                      // whole workgroup
+    const int i_base = tile * 16 * SUB;
+    const int Q = 1 << q_log, KS = kWaves / Q;
+
+    __shared__ int column[kWaves];                    // first output of each of the workgroup's quads
+    const int li = lane & 15, h = lane >> 4;
+    f32x4 acc[4][SUB];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int s = 0; s < SUB; ++s) acc[j][s] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    if (wave >= kWaves) {
+        const int slab = (wave - kWaves) * kMine;
+        const unsigned x_row = (unsigned)k * S;
+        const unsigned r8 = (unsigned)lane >> 3;
+        unsigned src[2 * SUB];
+#pragma unroll
+        for (int o = 0; o < 2 * SUB; ++o)
+            src[o] = (o * 8 + r8) * x_row + slab * 128 + ((((unsigned)lane & 7) ^ turn(r8 + 8 * (o & 1))) << 4);
+        const unsigned lds0 = (unsigned)(unsigned long long)(__attribute__((address_space(3))) unsigned char*)lds + slab * 2048;
+        unsigned long long xa = reinterpret_cast<unsigned long long>(X) + (unsigned long long)i_base * x_row;
+        long long left = (long long)(m - i_base) * x_row;   // bytes of X from here on
+        int windows = n_win;                          // still to issue
+        auto issue = [&](unsigned buf) {
+            i32x4 r;
+            r.x = (int)(unsigned)xa; r.y = (int)((unsigned)(xa >> 32) & 0xFFFFu);
+            r.z = windows <= 0 || left <= 0 ? 0 : left > 0x7fffffffll ? 0x7fffffff : (int)left; r.w = 0x00020000;
+#pragma unroll
+            for (int o = 0; o < 2 * SUB; ++o)
+#pragma unroll
+                for (int u = 0; u < kMine; ++u)
+                    load_to_lds(r, src[o] + u * 128, lds0 + buf * BUF + (o >> 1) * kPitch + (o & 1) * 1024 + u * 2048);
+            xa += kSlabs * 128;
+            left -= kSlabs * 128;
+            --windows;
+        };
+#pragma unroll
+        for (int b = 0; b < kRing - 1; ++b) issue((unsigned)b);
+        unsigned buf = 0;
+        for (int w = 0; w < n_win; ++w) {
+            wait_vm<(kRing - 2) * 2 * SUB * kMine>();         // this wavefront's share of window w has landed
+            asm volatile("s_barrier" ::: "memory");   // everybody's has, and everybody has read window w - 1
+            issue(buf == 0 ? kRing - 1 : buf - 1);
+            buf = buf == kRing - 1 ? 0 : buf + 1;
+        }
+        wait_vm<0>();                                 // nothing may land in the epilogue's tiles
+    } else {
+        if (tid < kRing * SUB) *reinterpret_cast<u32x4*>(lds + tid * kPitch + kZeroAt) = u32x4{0u, 0u, 0u, 0u};
+        const int slot = (group << q_log) + wave / KS, ks = wave % KS;
+        const i32x4 desc = quads[min(slot, n_quads - 1)];   // {quad, first round, end of the rounds, 0}
+        const __amdgpu_buffer_rsrc_t wrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(data), 0, (int)w_bytes, 0x00020000);
+        const int32_t* __restrict__ wq = win_ptr + (size_t)min(slot, n_quads - 1) * (n_win + 1);
+        int w = -1;
+        const int e_first = desc.y, e_last = slot < n_quads ? desc.z : e_first;
+        if (lane == 0 && ks == 0) column[wave / KS] = slot < n_quads ? desc.x * 64 : n;
+        if (e_first + ks < e_last) {
+            const unsigned lane_w = (unsigned)((li & (bs_r - 1)) * row_bytes + (h & (row_bytes / 16 - 1)) * 16);
+            const unsigned lane_x = (unsigned)(li * 128 + turn(li) * 16);
+            const i32x4* __restrict__ rl = recs + (h * 2 + (li >> 3)) * 2;
+            const int e_max = e_first + ks + (e_last - 1 - e_first - ks) / KS * KS;   // this wavefront's last round
+            struct record { i32x4 a, b; };            // {offset, place} of the round's four entries
+            auto load_rec = [&](int e) {
+                const i32x4* p = rl + (size_t)min(e, e_max) * 16;
+                return record{p[0], p[1]};
+            };
+            auto offset = [](const record& r, int j) { return j == 0 ? r.a.x : j == 1 ? r.a.z : j == 2 ? r.b.x : r.b.z; };
+            auto place = [](const record& r, int j) { return (unsigned)(j == 0 ? r.a.y : j == 1 ? r.a.w : j == 2 ? r.b.y : r.b.w); };
+            auto load_w = [&](int off) { return __builtin_amdgcn_raw_buffer_load_b128(wrsrc, off + (int)lane_w, 0, 0); };
+            u32x4 wv[4];
+            record now = load_rec(e_first + ks), next = load_rec(e_first + ks + KS), after = load_rec(e_first + ks + 2 * KS);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) wv[j] = load_w(offset(now, j));
+
+            int w_end = e_first, w_next = wq[min(1, n_win)];
+            unsigned base = (unsigned)(kRing - 1) * BUF;   // of the window in LDS
+            for (int e = e_first + ks; e <= e_max; e += KS) {
+                while (e >= w_end) {                  // on to the next window
+                    window_barrier();
+                    ++w;
+                    w_end = w_next;
+                    w_next = wq[min(w + 2, n_win)];
+                    base = base == (unsigned)(kRing - 1) * BUF ? 0u : base + BUF;
+                }
+                if constexpr (S == 2) {
+                    Frag<T, CH> wf[4], xf[4][SUB];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const unsigned char* xp = lds + base + min(place(now, j) ^ lane_x, (unsigned)kZeroAt);
+                        wf[j].w[0] = wv[j].x; wf[j].w[1] = wv[j].y; wf[j].w[2] = wv[j].z; wf[j].w[3] = wv[j].w;
+#pragma unroll
+                        for (int s = 0; s < SUB; ++s) xf[j][s].load(reinterpret_cast<const T*>(xp + s * kPitch));
+                        if (j > 0) {
+                            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                            for (int s = 0; s < SUB; ++s) mfma_frag<T, 16, CH>(acc[j - 1][s], wf[j - 1], xf[j - 1][s]);
+                            wv[j - 1] = load_w(offset(next, j - 1));
+                        }
+                    }
+#pragma unroll
+                    for (int s = 0; s < SUB; ++s) mfma_frag<T, 16, CH>(acc[3][s], wf[3], xf[3][s]);
+                    wv[3] = load_w(offset(next, 3));
+                } else {                              // fp32: a multiplication saved is worth the branch
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const unsigned at = place(now, j);
+                    if (__builtin_amdgcn_readfirstlane(at) != kNone) {   // uniform: this group of 16 rows has an entry left
+                        const unsigned char* xp = lds + base + min(at ^ lane_x, (unsigned)kZeroAt);
+                        Frag<T, CH> wf, xf[SUB];
+                        wf.w[0] = wv[j].x; wf.w[1] = wv[j].y; wf.w[2] = wv[j].z; wf.w[3] = wv[j].w;
+#pragma unroll
+                        for (int s = 0; s < SUB; ++s) xf[s].load(reinterpret_cast<const T*>(xp + s * kPitch));
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int s = 0; s < SUB; ++s) mfma_frag<T, 16, CH>(acc[j][s], wf, xf[s]);
+                    }
+                    wv[j] = load_w(offset(next, j));
+                }
+                }
+                now = next;
+                next = after;
+                after = load_rec(e + 3 * KS);
+            }
+        }
+        for (; w < n_win - 1; ++w) window_barrier();
+    }
+
+    // The wavefronts' sums through LDS: added over a quad's wavefronts in order, stored as whole lines of Y.
+    constexpr int RP = SUB >= 2 ? kRowsOut : 16;      // rows per pass
+    constexpr int EPT = 16 / (int)sizeof(O);          // outputs a thread stores
+    constexpr int TPR = 64 / EPT;
+    float* tiles = reinterpret_cast<float*>(lds);
+#pragma unroll
+    for (int p = 0; p < 16 * SUB / RP; ++p) {
+        __syncthreads();
+        if (wave < kWaves) {
+            float* mine = tiles + (size_t)wave * RP * kLdOut;
+#pragma unroll
+            for (int ss = 0; ss < RP / 16; ++ss)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    *reinterpret_cast<f32x4*>(mine + (ss * 16 + li) * kLdOut + j * 16 + 4 * h) = acc[j][p * (RP / 16) + ss];
+        }
+        __syncthreads();
+        for (int t = tid; t < Q * RP * TPR; t += 64 * (kWaves + kLoaders)) {
+            const int qi = t / (RP * TPR), row = t / TPR % RP, c = t % TPR * EPT;
+            const int i = i_base + p * RP + row, col = column[qi] + c;
+            if (col >= n || i >= m) continue;
+            const float* src = tiles + ((size_t)(qi * KS) * RP + row) * kLdOut + c;
+            float v[EPT];
+#pragma unroll
+            for (int e = 0; e < EPT; ++e) v[e] = src[e];
+            for (int s = 1; s < KS; ++s) {
+                src += RP * kLdOut;
+#pragma unroll
+                for (int e = 0; e < EPT; ++e) v[e] += src[e];
+            }
+            O* dst = Y + (size_t)i * (size_t)n + col;
+            if constexpr (EPT == 4) {
+                *reinterpret_cast<f32x4*>(dst) = f32x4{v[0], v[1], v[2], v[3]};
+            } else {
+                typedef O o8 __attribute__((ext_vector_type(8)));
+                o8 r;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) r[e] = from_f32<O>(v[e]);
+                *reinterpret_cast<o8*>(dst) = r;
+            }
+        }
+    }
+}
+
+// Byte offsets into the rows of X of a workgroup are 32-bit, with the top bit left for what is not there.
+bool reaches(const bsr_matrix* W, int sub) { return (int64_t)16 * sub * W->k * (W->dtype == BSR_F32 ? 4 : 2) < ((int64_t)1 << 31); }
+
+// Rows of X and quads of a workgroup: the quickest by an estimate, fitted to bf16 and fp32 8x8 products of 17 to 2000
+// rows by (512 .. 6016, 512 .. 4096), 5 to 25 % (within 3 % of the quickest of the twelve shapes, fp32 within 16 %).
+// Microseconds: what a workgroup takes before its first and after its last round, a window, and a round.
+struct sweep_shape_t { int sub, q_log; };
+sweep_shape_t choose(const bsr_matrix* W, int64_t m, int q_most)
+{
+    const bool f32 = W->dtype == BSR_F32;
+    sweep_shape_t best{1, 0};
+    double best_us = 1e30;
+    for (int sub : {1, 2, 4}) {
+        if (sub > 1 && !reaches(W, sub)) break;
+        for (int q_log = 0; (1 << q_log) <= q_most; ++q_log) {
+            const int Q = 1 << q_log, KS = kWaves / Q;
+            if (q_log > 0 && (1 << (q_log - 1)) >= W->sw_quads) break;   // wavefronts without a quad
+            const double wgs = (double)((m + 16 * sub - 1) / (16 * sub)) * ((W->sw_quads + Q - 1) / Q);
+            const double start = sub == 4 ? 4.0 : sub == 2 ? 2.4 : 1.5;
+            const double round = f32 ? 0.15 + 0.42 * sub : sub == 4 ? 0.40 : 0.32;
+            auto us = [&](double rounds) { return start + W->sw_windows * 0.12 * sub + round * (rounds / KS + (KS > 1 ? 0.4 : 0.0) * W->sw_windows); };
+            const double p = wgs / 256, passes = p <= 1 ? 1 : p <= 4 ? std::ceil(p) : p + 0.5;
+            const double t = std::max(us((double)W->sw_longest), passes * us((double)W->sw_rounds / W->sw_quads));
+            if (t < best_us) { best_us = t; best = {sub, q_log}; }
+        }
+    }
+    return best;
+}
+
+template <typename T, typename O, int SUB>
+bsr_status launch_sub(const spmm_args& a, int q_log)
+{
+    const bsr_matrix* W = a.W;
+    const int m = (int)a.m, TM = 16 * SUB;
+    const int n_tiles = (m + TM - 1) / TM, Q = 1 << q_log;
+    const int n_groups = (W->sw_quads + Q - 1) / Q;
+    // tiles that would leave an XCD without are dealt out as they come: evenly over the XCDs comes first
+    const int eight = (n_tiles + kXcds - 1) / kXcds * kXcds, padded = 5 * eight <= 6 * n_tiles ? eight : n_tiles;
+    const int64_t blocks = (int64_t)padded * n_groups;
+    if (blocks >= ((int64_t)1 << 31)) return BSR_ERR_SHAPE;
+    constexpr size_t ring = (size_t)kRing * SUB * kPitch, out = (size_t)kWaves * (SUB >= 2 ? kRowsOut : 16) * kLdOut * sizeof(float);
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&bsr_mfma_sweep<T, O, SUB>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)std::max(ring, out));
+    if (attr != hipSuccess) return BSR_ERR_HIP;
+    hipLaunchKernelGGL((bsr_mfma_sweep<T, O, SUB>), dim3((unsigned)blocks), dim3(64 * (kWaves + kLoaders)), std::max(ring, out), a.stream,
+                       (const T*)a.X, (const T*)W->data, (unsigned)(W->nnzb * W->bs_r * W->bs_c * sizeof(T)),
+                       reinterpret_cast<const i32x4*>(W->sw_recs), W->sw_win_ptr, reinterpret_cast<const i32x4*>(W->sw_desc), (O*)a.Y, m, (int)W->k, (int)W->n,
+                       n_tiles, padded, W->sw_quads, W->sw_windows, q_log, W->bs_r, W->bs_c * (int)sizeof(T));
+    return hipGetLastError() == hipSuccess ? BSR_OK : BSR_ERR_HIP;
+}
+
+template <typename T, typename O>
+bsr_status launch_types(const spmm_args& a, const tune_opts& tune)
+{
+    // A result in fp32 keeps as many chains of additions as the kernel of 16x16 tiles gives it: 8 where that starts few
+    // workgroups, at least 2 (root mean square error, fp32 8x8, m = 1000, (1024, 1024), 30 %: both 2.3e-7).
+    const int64_t items = ((a.m + 15) / 16) * ((a.W->n + 15) / 16);
+    const int q_most = !std::is_same<O, float>::value ? kWaves : items > 1024 ? kWaves / 2 : items > 256 ? kWaves / 4 : 1;
+    const sweep_shape_t c = choose(a.W, a.m, q_most);
+    int sub = c.sub, q_log = c.q_log;
+    if ((tune.mt == 1 || tune.mt == 2 || tune.mt == 4) && reaches(a.W, tune.mt)) sub = tune.mt;
+    if (tune.nw == 1 || tune.nw == 2 || tune.nw == 4 || tune.nw == 8)
+        for (q_log = 0; (1 << q_log) < std::min(tune.nw, q_most);) ++q_log;
+    if (sub == 4) return launch_sub<T, O, 4>(a, q_log);
+    if (sub == 2) return launch_sub<T, O, 2>(a, q_log);
+    return launch_sub<T, O, 1>(a, q_log);
+}
+
+}  // namespace
+
+bool mfma_sweep_supports(const bsr_matrix* W) { return W->sw_recs != nullptr; }
+
+bsr_status launch_mfma_sweep(const spmm_args& a, const tune_opts& t)
+{
+    const bsr_matrix* W = a.W;
+    if (!mfma_sweep_supports(W)) return BSR_ERR_UNSUPPORTED;
+    if (W->dtype == BSR_F32) return launch_types<float, float>(a, t);
+    if (W->dtype == BSR_F16) return a.y_dtype == BSR_F32 ? launch_types<_Float16, float>(a, t) : launch_types<_Float16, _Float16>(a, t);
+    return a.y_dtype == BSR_F32 ? launch_types<__bf16, float>(a, t) : launch_types<__bf16, __bf16>(a, t);
+}
+
+// Blocks of 8 rows or columns: smaller than an MFMA step takes.  Larger ones have kernels that stage them one by one.
+static bool sweep_shape(int32_t bs_r, int32_t bs_c)
+{
+    return (bs_r == 8 || bs_r == 16) && (bs_c == 8 || bs_c == 16) && !(bs_r == 16 && bs_c == 16);
+}
+
+// Words of the plan: {quad, rounds} and the windows' first rounds per quad, and the rounds' records.  A window has as many
+// rounds as the longest of a quad's groups has entries: at worst all of its blocks are in that one.  fp32 makes the most of
+// both: windows of 256 columns, entries of 16.
+size_t sweep_plan_words(int64_t n, int64_t k, int32_t bs_r, int32_t bs_c, int64_t nnzb)
+{
+    if (!sweep_shape(bs_r, bs_c) || nnzb == 0) return 0;
+    const size_t quads = (size_t)(n + 63) / 64, windows = (size_t)(k + 255) / 256;
+    const size_t rounds = std::min((size_t)nnzb, (size_t)nnzb / (16 / bs_c) + quads * windows);
+    return 4 * quads + quads * (windows + 1) + 64 * rounds + 2 * 64;
+}
+
+void build_sweep_plan(bsr_matrix* W, const int32_t* indptr, const int32_t* indices, size_t* words)
+{
+    const int bs_r = W->bs_r, bs_c = W->bs_c, S = W->dtype == BSR_F32 ? 4 : 2;
+    const int64_t row_bytes = (int64_t)bs_c * S, block = bs_r * row_bytes;
+    if (!sweep_shape(bs_r, bs_c) || W->nnzb == 0 || W->nnzb * block >= ((int64_t)1 << 31) || !reaches(W, 1)) return;
+    const int gran = (int)(row_bytes / 16);           // granules of a block's row: 1, 2 or 4
+    const int per_entry = 4 / gran;                   // block-columns of an entry
+    const int win_cols = kSlabs * 128 / S, n_win = (int)((W->k + win_cols - 1) / win_cols);
+    const int n_groups = (int)((W->n + 15) / 16), n_quads = (n_groups + 3) / 4;
+    struct slot { int32_t col; int32_t off[2]; };     // first column, byte offset of the values for rows 0-7 and 8-15
+    std::vector<slot> rows[4];
+    std::vector<int32_t>& plan = W->staging;
+    const size_t desc_at = *words, win_at = desc_at + (4 * (size_t)n_quads + 63) / 64 * 64;
+    const size_t recs_at = win_at + ((size_t)n_quads * (n_win + 1) + 63) / 64 * 64;
+    plan.resize(recs_at, 0);
+    auto rounds_so_far = [&] { return (int32_t)((plan.size() - recs_at) / 64); };
+    std::vector<int32_t> ptr((size_t)n_quads * (n_win + 1));
+    std::vector<int32_t> load((size_t)n_quads);
+    struct stored { int32_t col, at; };               // block-column, number of the stored block
+    std::vector<stored> sorted[2];
+    auto sorted_row = [&](int64_t r, std::vector<stored>& v) {
+        const int32_t first = r < W->R ? indptr[r] : 0, count = r < W->R ? indptr[r + 1] - first : 0;
+        v.resize((size_t)count);
+        bool in_order = true;
+        for (int32_t i = 0; i < count; ++i) {
+            v[(size_t)i] = {indices[first + i], first + i};
+            in_order = in_order && (i == 0 || indices[first + i - 1] <= indices[first + i]);
+        }
+        if (!in_order) std::stable_sort(v.begin(), v.end(), [](const stored& a, const stored& b) { return a.col < b.col; });
+    };
+    for (int q = 0; q < n_quads; ++q) {
+        for (int j = 0; j < 4; ++j) {
+            auto& list = rows[j];
+            list.clear();
+            const int64_t g = (int64_t)q * 4 + j;
+            sorted_row(bs_r == 8 ? 2 * g : g, sorted[0]);
+            if (bs_r == 16) {
+                for (const auto& b : sorted[0]) list.push_back({b.col * bs_c, {(int32_t)(b.at * block), (int32_t)(b.at * block)}});
+                continue;
+            }
+            sorted_row(2 * g + 1, sorted[1]);         // two block-rows, by column; a block stored twice opens a second slot
+            size_t a = 0, b = 0;
+            while (a < sorted[0].size() || b < sorted[1].size()) {
+                const int32_t ca = a < sorted[0].size() ? sorted[0][a].col : INT32_MAX;
+                const int32_t cb = b < sorted[1].size() ? sorted[1][b].col : INT32_MAX;
+                const int32_t c = std::min(ca, cb);
+                slot s{c * bs_c, {INT32_MIN, INT32_MIN}};
+                if (ca == c) s.off[0] = (int32_t)(sorted[0][a++].at * block);
+                if (cb == c) s.off[1] = (int32_t)(sorted[1][b++].at * block);
+                list.push_back(s);
+            }
+        }
+        size_t at[4] = {0, 0, 0, 0}, end[4];
+        const int32_t first = rounds_so_far();
+        for (int w = 0; w < n_win; ++w) {
+            ptr[(size_t)q * (n_win + 1) + w] = rounds_so_far();
+            size_t rounds = 0;
+            for (int j = 0; j < 4; ++j) {
+                const auto& list = rows[j];
+                end[j] = at[j];
+                while (end[j] < list.size() && list[end[j]].col < (w + 1) * win_cols) ++end[j];
+                rounds = std::max(rounds, (end[j] - at[j] + per_entry - 1) / per_entry);
+            }
+            const size_t here = plan.size();
+            plan.resize(here + rounds * 64);
+            int32_t* r = plan.data() + here;
+            for (size_t i = 0; i < rounds * 32; ++i) { r[2 * i] = INT32_MIN; r[2 * i + 1] = kNone; }
+            for (int j = 0; j < 4; ++j) {
+                for (size_t i = at[j]; i < end[j]; ++i) {
+                    const slot& s = rows[j][i];
+                    const size_t rd = (i - at[j]) / (size_t)per_entry, u = (i - at[j]) % (size_t)per_entry;
+                    const int byte = (s.col - w * win_cols) * S, place = byte / 128 * 2048 + byte % 128;   // a block's granules share a slab
+                    int32_t* e = r + rd * 64 + u * (size_t)gran * 16 + j * 2;
+                    for (int v = 0; v < gran; ++v, e += 16) {
+                        e[0] = s.off[0]; e[8] = s.off[1];
+                        e[1] = e[9] = place + v * 16;
+                    }
+                }
+                at[j] = end[j];
+            }
+        }
+        ptr[(size_t)q * (n_win + 1) + n_win] = rounds_so_far();
+        load[(size_t)q] = rounds_so_far() - first;
+    }
+    std::vector<int32_t> order((size_t)n_quads);
+    std::iota(order.begin(), order.end(), 0);
+    std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return load[(size_t)a] > load[(size_t)b]; });
+    for (int s = 0; s < n_quads; ++s) {
+        const int32_t* p = ptr.data() + (size_t)order[(size_t)s] * (n_win + 1);
+        int32_t* d = plan.data() + desc_at + 4 * (size_t)s;
+        d[0] = order[(size_t)s];
+        d[1] = p[0];
+        d[2] = p[n_win];
+        std::copy(p, p + n_win + 1, plan.begin() + (ptrdiff_t)(win_at + (size_t)s * (n_win + 1)));
+    }
+    W->sw_desc = W->row_order + desc_at;
+    W->sw_win_ptr = W->row_order + win_at;
+    W->sw_recs = W->row_order + recs_at;
+    W->sw_rounds = rounds_so_far();
+    *words = plan.size();                             // rounds are 64 words
+    W->sw_quads = n_quads;
+    W->sw_windows = n_win;
+    W->sw_longest = n_quads ? load[(size_t)order[0]] : 0;
+}

@@ -1,0 +1,75 @@
+"""The sweep kernel: blocks of 8 rows or columns, many rows of X, swept in windows of 1 KiB of a row."""
+import numpy as np
+import pytest
+
+import workloads as wl
+from gpu_util import check, gpu_product
+
+pytestmark = pytest.mark.gpu
+
+
+def _problem(m, R, C, bs, dtype, out, seed):
+    """Block-rows empty, full, of one block and ordinary ones; columns in any order, some stored twice."""
+    rng = np.random.default_rng(seed)
+    counts = rng.integers(0, max(2, C // 4), size=R)
+    counts[0], counts[-1], counts[R // 2] = 0, 1, C
+    p = wl.make_problem("sweep", m, C * bs[1], R * bs[0], bs[0], bs[1], dtype, out, ("counts", counts), ("normal", 1.0), ("normal", 1.0), seed)
+    for r in range(R):
+        a, b = int(p.index_pointer[r]), int(p.index_pointer[r + 1])
+        if r % 3 == 1:
+            p.block_indices[a:b] = rng.permutation(p.block_indices[a:b])
+        if r % 4 == 2 and b - a > 2:
+            p.block_indices[a] = p.block_indices[b - 1]
+    return p
+
+
+@pytest.mark.parametrize("dtype,out", [("f32", "f32"), ("f16", "f16"), ("bf16", "bf16"), ("bf16", "f32")])
+@pytest.mark.parametrize("bs", [(8, 8), (8, 16), (16, 8)])
+@pytest.mark.parametrize("tune", ["variant=6,mt=4,nw=8", "variant=6,mt=4,nw=1", "variant=6,mt=2,nw=4", "variant=6,mt=1,nw=2"])
+def test_forced_shapes(oracle_mod, monkeypatch, dtype, out, bs, tune):
+    """Every workgroup shape on both sides of a tile's rows; three windows and a ragged fourth, one window, a row of one
+    slab; a last quad with one, two and four groups of 16 rows."""
+    import paper_2007_13055_amd as lib
+    monkeypatch.setenv("BSR_SPMM_TUNE", tune)
+    cols = 256 if dtype == "f32" else 512
+    for i, (m, C, rows) in enumerate([(16, cols // bs[1], 80), (65, (3 * cols + 16) // bs[1], 144), (127, 16 // bs[1], 64), (130, (cols + 48) // bs[1], 608)]):
+        p = _problem(m, rows // bs[0], C, bs, dtype, out, 700 + i)
+        Yo, So = oracle_mod.bsr_spmm(p.X, p.block_data, p.block_indices, p.index_pointer, p.n)
+        Y, W = gpu_product(p, path=lib.PATH_MFMA)
+        check(Y, Yo, So, p.tau, f"{bs} {dtype}->{out} m={m} k={p.k} n={p.n} {tune}", out_dtype=out)
+        assert np.array_equal(Y, gpu_product(p, path=lib.PATH_MFMA, W=W)[0])
+
+
+@pytest.mark.parametrize("dtype,out,m,R,sweeps", [("f16", "f16", 15, 501, False), ("f16", "f16", 16, 247, False), ("f16", "f16", 16, 251, True),
+                                                  ("bf16", "bf16", 200, 21, True), ("bf16", "f32", 200, 21, False), ("f32", "f32", 400, 67, False)])
+@pytest.mark.parametrize("C", [33, 67])
+def test_sizes_without_whole_tiles(oracle_mod, dtype, out, m, R, sweeps, C):
+    """n or k an odd multiple of 8: the library's own choice on both sides of where it takes the sweep kernel, told by the
+    bits of both; a caller that asks for the matrix cores is refused as before."""
+    import paper_2007_13055_amd as lib
+    p = _problem(m, R, C, (8, 8), dtype, out, 40 + m)
+    Yo, So = oracle_mod.bsr_spmm(p.X, p.block_data, p.block_indices, p.index_pointer, p.n)
+    Y, W = gpu_product(p)
+    check(Y, Yo, So, p.tau, f"{dtype}->{out} m={m} R={R} C={C}", out_dtype=out)
+    wave, _ = gpu_product(p, path=lib.PATH_WAVE, W=W)
+    assert np.array_equal(Y, wave) == (not sweeps)
+    assert lib.bsr_query_path(W, m) == lib.PATH_WAVE
+    with pytest.raises(lib.BsrError):
+        gpu_product(p, path=lib.PATH_MFMA, W=W)
+
+
+@pytest.mark.parametrize("dtype,m,R,C,tiles", [("f32", 383, 24, 60, True), ("f32", 384, 24, 60, False), ("f16", 64, 64, 256, True),
+                                               ("f16", 65, 64, 256, False), ("bf16", 64, 64, 254, False), ("bf16", 64, 64, 700, False)])
+def test_which_kernel(oracle_mod, monkeypatch, dtype, m, R, C, tiles):
+    """Both sides of the rules between the sweep kernel and the one of 16x16 tiles, told by the bits."""
+    import paper_2007_13055_amd as lib
+    p = _problem(m, R, C, (8, 8), dtype, "f32", 9)
+    Yo, So = oracle_mod.bsr_spmm(p.X, p.block_data, p.block_indices, p.index_pointer, p.n)
+    Y, _ = gpu_product(p)
+    check(Y, Yo, So, p.tau, f"{dtype} m={m}")
+    forced = {}
+    for v in (6, 7):
+        monkeypatch.setenv("BSR_SPMM_TUNE", f"variant={v}")
+        forced[v], _ = gpu_product(p, path=lib.PATH_MFMA)
+    assert np.array_equal(Y, forced[7 if tiles else 6])
+    assert dtype != "f32" or not np.array_equal(forced[6], forced[7])
