@@ -656,7 +656,7 @@ static std::vector<tuned_choice> tune_candidates(const bsr_matrix* W, int64_t m)
             add(BSR_PATH_MFMA, 2, 0, 0, 0, 0);
         if (W->scratch && W->scratch_bytes >= mfma_thin_scratch_bytes(W, m) && m >= 16)
             for (int a : {4, 6, 8, 10, 12, 14, 16}) add(BSR_PATH_MFMA, 1, 0, 0, a, 0);
-    } else if (mfma_small_supports(W) || mfma_sweep_supports(W)) {
+    } else if (mfma_small_supports(W) || (mfma_sweep_supports(W) && !mfma_supports(W))) {
         if (m >= 8 && mfma_small_supports(W) && W->dtype == BSR_F32)
             for (int nw : {2, 4, 8})
                 for (int per : {1, 2, 4}) add(BSR_PATH_MFMA, 7, nw, 0, per, 0);
@@ -677,6 +677,7 @@ static std::vector<tuned_choice> tune_candidates(const bsr_matrix* W, int64_t m)
         }
         for (int tm : {1, 2, 4})
             if (m >= 16 * tm && mfma_stripe_supports(W, 16 * tm)) add(BSR_PATH_MFMA, 4, 0, tm, 0, 0);
+        if (mfma_sweep_supports(W)) add(BSR_PATH_MFMA, 6, 0, 0, 0, 0);
         add(BSR_PATH_MFMA, 1, 0, 0, 0, 0);
         if (W->bs_r >= 32) add(BSR_PATH_MFMA, 1, 4, 2, 0, 0);
     }

@@ -33,7 +33,7 @@ constexpr int kItemSlots = 4;                     // k-split work-item tables a 
 //            started first; stripe a = block-row groups; thin a = groups of 4 blocks in flight
 //            thin blocks: variant 1 = transposed copy in scratch + gather, 2 = rows of X staged in LDS
 //            (a = slots per wavefront)
-//            8-wide blocks: variant 6 = sweep (mt = 16-row tiles, nw = quads per workgroup), 7 = 16x16 tiles (fp32)
+//            8-wide blocks and 16-bit 16x16: variant 6 = sweep (mt = 16-row tiles, nw = quads per workgroup); 8-wide: 7 = 16x16 tiles (fp32)
 //   sd       sampled product: 1 a workgroup per block (thin: X transposed), 2 groups of blocks that share slabs (thin: turned over in LDS)
 struct tune_opts {
     int variant = 0, nw = 0, mt = 0, a = 0, b = 0, sd = 0;
@@ -114,7 +114,7 @@ struct bsr_matrix {
     const int32_t* wide_chunks = nullptr;
     const int32_t* wide_chunk_ptr = nullptr;
     int32_t wide_nq = 0;
-    // Sweep kernel (bsr_mfma_sweep.hip; block sides 8 or 16, not both 16): the quads (64 outputs) by rounds, longest
+    // Sweep kernel (bsr_mfma_sweep.hip; block sides 8 or 16): the quads (64 outputs) by rounds, longest
     // first, {quad, first round, end of its rounds, 0}; per quad the first round of each window and the end,
     // [sw_quads][sw_windows + 1]; per round 64 words, {byte offset of the values, place of the granule in the window}
     // for (granule, half of the rows, group of 16 rows).
@@ -270,6 +270,7 @@ inline bool small_blocks_16bit(const bsr_matrix* W, int64_t m)
 // be any multiples of 8.
 bsr_status launch_mfma_sweep(const spmm_args& a, const tune_opts& t);
 bool mfma_sweep_supports(const bsr_matrix* W);
+bool sweep_is_quicker(const bsr_matrix* W, int64_t m, bsr_dtype y_dtype, bool than_stripes);   // 16x16 blocks
 void build_sweep_plan(bsr_matrix* W, const int32_t* index_pointer_host, const int32_t* block_indices_host, size_t* words);
 size_t sweep_plan_words(int64_t n, int64_t k, int32_t bs_r, int32_t bs_c, int64_t nnzb);
 size_t mfma_thin_scratch_bytes(const bsr_matrix* W, int64_t m);   // bytes of the transposed copy of X

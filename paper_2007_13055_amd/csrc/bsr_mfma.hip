@@ -164,6 +164,8 @@ bool mfma_supports(const bsr_matrix* W)
 //           the X tile staged in LDS with coalesced reads, XCD-aware launch order
 //   stripe  16x16 blocks of a 16-bit type, many rows of X, and 64 full rows of X fit in LDS: the
 //           stripe is copied to LDS once and many block-rows are multiplied against it
+//   sweep   16x16 blocks of a 16-bit type where neither of the two above reads X often enough from LDS: a stripe that is
+//           short for want of LDS, or none, and more items than the k-split kernel's loads from L2 keep up with
 //   direct  everything else: block-rows of a block or two, where writing Y is most of the work
 //           (operands straight from global memory)
 bsr_status launch_mfma(const spmm_args& a, const tune_opts& tune)
@@ -185,6 +187,7 @@ bsr_status launch_mfma(const spmm_args& a, const tune_opts& tune)
         else if (a.m >= 256 && mfma_stripe_supports(a.W, 16)) variant = 4;
         else if (a.W->mean_row_blocks > 4.0) variant = 2;     // 16-row blocks the tile kernel does not take
         else variant = 1;
+        if ((variant == 2 || variant == 4) && sweep_is_quicker(a.W, a.m, a.y_dtype, variant == 4)) variant = 6;
         // 64x64 16-bit blocks with a few block-rows that hold much of W: those rows in row groups (their X
         // tiles shared through LDS), the rest through the tile kernel (112 against 135 us on the 8192^3
         // power-law workload, 403 instead of 825 MB fetched)
@@ -222,5 +225,6 @@ bsr_status launch_mfma(const spmm_args& a, const tune_opts& tune)
     if (variant == 2) return launch_mfma_ksplit(a, t);
     if (variant == 3) return launch_mfma_tile(a, t);
     if (variant == 4) return launch_mfma_stripe(a, t);
+    if (variant == 6) return launch_mfma_sweep(a, t);
     return launch_mfma_direct(a, t);
 }

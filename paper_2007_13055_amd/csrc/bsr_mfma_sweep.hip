@@ -1,4 +1,4 @@
-// Matrix-core kernel for blocks with sides 8 or 16 (not both 16), swept over the columns of X.
+// Matrix-core kernel for blocks with sides 8 or 16 (both 16: 16-bit types only), swept over the columns of X.
 //
 // A stored 8x8 block touches 16 bytes of a row of X, so a kernel that fetches X block by block moves whole lines for a
 // fraction of them, once per 16 outputs.  Here a workgroup takes TM = 16 * SUB rows of X and a few QUADS (64 outputs, four
@@ -254,12 +254,11 @@ bool reaches(const bsr_matrix* W, int sub) { return (int64_t)16 * sub * W->k * (
 // Rows of X and quads of a workgroup: the quickest by an estimate, fitted to bf16 and fp32 8x8 products of 17 to 2000
 // rows by (512 .. 6016, 512 .. 4096), 5 to 25 % (within 3 % of the quickest of the twelve shapes, fp32 within 16 %).
 // Microseconds: what a workgroup takes before its first and after its last round, a window, and a round.
-struct sweep_shape_t { int sub, q_log; };
+struct sweep_shape_t { int sub, q_log; double us; };
 sweep_shape_t choose(const bsr_matrix* W, int64_t m, int q_most)
 {
     const bool f32 = W->dtype == BSR_F32;
-    sweep_shape_t best{1, 0};
-    double best_us = 1e30;
+    sweep_shape_t best{1, 0, 1e30};
     for (int sub : {1, 2, 4}) {
         if (sub > 1 && !reaches(W, sub)) break;
         for (int q_log = 0; (1 << q_log) <= q_most; ++q_log) {
@@ -271,7 +270,7 @@ sweep_shape_t choose(const bsr_matrix* W, int64_t m, int q_most)
             auto us = [&](double rounds) { return start + W->sw_windows * 0.12 * sub + round * (rounds / KS + (KS > 1 ? 0.4 : 0.0) * W->sw_windows); };
             const double p = wgs / 256, passes = p <= 1 ? 1 : p <= 4 ? std::ceil(p) : p + 0.5;
             const double t = std::max(us((double)W->sw_longest), passes * us((double)W->sw_rounds / W->sw_quads));
-            if (t < best_us) { best_us = t; best = {sub, q_log}; }
+            if (t < best.us) best = {sub, q_log, t};
         }
     }
     return best;
@@ -299,13 +298,18 @@ bsr_status launch_sub(const spmm_args& a, int q_log)
     return hipGetLastError() == hipSuccess ? BSR_OK : BSR_ERR_HIP;
 }
 
+// A result in fp32 keeps as many chains of additions as the kernel of 16x16 tiles gives it: 8 where that starts few
+// workgroups, at least 2 (root mean square error, fp32 8x8, m = 1000, (1024, 1024), 30 %: both 2.3e-7).
+int most_quads(const bsr_matrix* W, int64_t m, bool f32_out)
+{
+    const int64_t items = ((m + 15) / 16) * ((W->n + 15) / 16);
+    return !f32_out ? kWaves : items > 1024 ? kWaves / 2 : items > 256 ? kWaves / 4 : 1;
+}
+
 template <typename T, typename O>
 bsr_status launch_types(const spmm_args& a, const tune_opts& tune)
 {
-    // A result in fp32 keeps as many chains of additions as the kernel of 16x16 tiles gives it: 8 where that starts few
-    // workgroups, at least 2 (root mean square error, fp32 8x8, m = 1000, (1024, 1024), 30 %: both 2.3e-7).
-    const int64_t items = ((a.m + 15) / 16) * ((a.W->n + 15) / 16);
-    const int q_most = !std::is_same<O, float>::value ? kWaves : items > 1024 ? kWaves / 2 : items > 256 ? kWaves / 4 : 1;
+    const int q_most = most_quads(a.W, a.m, std::is_same<O, float>::value);
     const sweep_shape_t c = choose(a.W, a.m, q_most);
     int sub = c.sub, q_log = c.q_log;
     if ((tune.mt == 1 || tune.mt == 2 || tune.mt == 4) && reaches(a.W, tune.mt)) sub = tune.mt;
@@ -320,6 +324,23 @@ bsr_status launch_types(const spmm_args& a, const tune_opts& tune)
 
 bool mfma_sweep_supports(const bsr_matrix* W) { return W->sw_recs != nullptr; }
 
+// The choice for 16x16 blocks between this kernel and the one that would run else, from estimates in microseconds fitted to
+// 225 bf16 products (16 .. 8192 rows, sides 128 .. 8192, 3 to 30 %, uniform and power law).  Half of the estimates are
+// within 5 % (this kernel), 8 % (k-split) and 9 % (stripes) of the time and nine tenths within 16, 31 and 36 %, so this
+// kernel is taken only where its own is lower by a quarter, against stripes by three tenths: of those and 268 other products
+// 65 are, up to 5 times quicker and none slower (a fifth lower: 96, five of them 4 to 28 % slower).
+bool sweep_is_quicker(const bsr_matrix* W, int64_t m, bsr_dtype y_dtype, bool than_stripes)
+{
+    if (W->bs_r != 16 || W->bs_c != 16 || !mfma_sweep_supports(W)) return false;
+    const double tiles = (double)((m + 15) / 16);
+    const double sweep = 2.8 + 1.03 * choose(W, m, most_quads(W, m, y_dtype == BSR_F32)).us + 2.1e-6 * tiles * (double)W->n;
+    // stripes: X staged, Y stored, products, and a term for the rows' length; k-split: stored blocks and block-rows of every
+    // tile of 16 rows (its X comes from L2 or beyond once per stored block), and the longest block-row
+    const double other = than_stripes ? 4.6 + 6.3e-7 * (double)(m * W->k) + 4.7e-7 * (double)(m * W->n) + 2.3e-5 * tiles * (double)W->nnzb + 2.9e-3 * (double)W->k
+                                      : 4.1 + 0.84e-4 * tiles * (double)W->nnzb + 3.7e-4 * tiles * W->R + 2.7e-2 * W->max_row_blocks;
+    return sweep < (than_stripes ? 0.7 : 0.75) * other;
+}
+
 bsr_status launch_mfma_sweep(const spmm_args& a, const tune_opts& t)
 {
     const bsr_matrix* W = a.W;
@@ -329,20 +350,20 @@ bsr_status launch_mfma_sweep(const spmm_args& a, const tune_opts& t)
     return a.y_dtype == BSR_F32 ? launch_types<__bf16, float>(a, t) : launch_types<__bf16, __bf16>(a, t);
 }
 
-// Blocks of 8 rows or columns: smaller than an MFMA step takes.  Larger ones have kernels that stage them one by one.
-static bool sweep_shape(int32_t bs_r, int32_t bs_c)
-{
-    return (bs_r == 8 || bs_r == 16) && (bs_c == 8 || bs_c == 16) && !(bs_r == 16 && bs_c == 16);
-}
+// Blocks of 8 rows or columns are smaller than an MFMA step takes, and 16x16 blocks of a 16-bit type touch 32 bytes of a row
+// of X each.  Larger ones have kernels that stage them one by one and gain little here (bf16, kernels of staged tiles and
+// this one, us: 32x32 3876 x (5824, 704), 17 %, power law 65, 52, but 4096 x (768, 3072), 20 % 17, 23; 64x64 4096 x
+// (6016, 1536), 20 % 45, 63); 16x16 blocks of fp32 wait for the matrix cores wherever they are.
+static bool sweep_shape(int32_t bs_r, int32_t bs_c) { return (bs_r == 8 || bs_r == 16) && (bs_c == 8 || bs_c == 16); }
 
 // Words of the plan: {quad, rounds} and the windows' first rounds per quad, and the rounds' records.  A window has as many
 // rounds as the longest of a quad's groups has entries: at worst all of its blocks are in that one.  fp32 makes the most of
-// both: windows of 256 columns, entries of 16.
+// both: windows of 256 columns, entries of 16; 16x16 blocks are always of a 16-bit type, two to an entry.
 size_t sweep_plan_words(int64_t n, int64_t k, int32_t bs_r, int32_t bs_c, int64_t nnzb)
 {
     if (!sweep_shape(bs_r, bs_c) || nnzb == 0) return 0;
     const size_t quads = (size_t)(n + 63) / 64, windows = (size_t)(k + 255) / 256;
-    const size_t rounds = std::min((size_t)nnzb, (size_t)nnzb / (16 / bs_c) + quads * windows);
+    const size_t rounds = std::min((size_t)nnzb, (size_t)nnzb / (bs_r == 16 && bs_c == 16 ? 2 : 16 / bs_c) + quads * windows);
     return 4 * quads + quads * (windows + 1) + 64 * rounds + 2 * 64;
 }
 
@@ -350,7 +371,7 @@ void build_sweep_plan(bsr_matrix* W, const int32_t* indptr, const int32_t* indic
 {
     const int bs_r = W->bs_r, bs_c = W->bs_c, S = W->dtype == BSR_F32 ? 4 : 2;
     const int64_t row_bytes = (int64_t)bs_c * S, block = bs_r * row_bytes;
-    if (!sweep_shape(bs_r, bs_c) || W->nnzb == 0 || W->nnzb * block >= ((int64_t)1 << 31) || !reaches(W, 1)) return;
+    if (!sweep_shape(bs_r, bs_c) || (bs_r == 16 && bs_c == 16 && S == 4) || W->nnzb == 0 || W->nnzb * block >= ((int64_t)1 << 31) || !reaches(W, 1)) return;
     const int gran = (int)(row_bytes / 16);           // granules of a block's row: 1, 2 or 4
     const int per_entry = 4 / gran;                   // block-columns of an entry
     const int win_cols = kSlabs * 128 / S, n_win = (int)((W->k + win_cols - 1) / win_cols);

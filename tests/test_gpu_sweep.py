@@ -1,4 +1,4 @@
-"""The sweep kernel: blocks of 8 rows or columns, many rows of X, swept in windows of 1 KiB of a row."""
+"""The sweep kernel: blocks with sides 8 or 16, many rows of X, swept in windows of 1 KiB of a row."""
 import numpy as np
 import pytest
 
@@ -24,13 +24,17 @@ def _problem(m, R, C, bs, dtype, out, seed):
 
 
 @pytest.mark.parametrize("dtype,out", [("f32", "f32"), ("f16", "f16"), ("bf16", "bf16"), ("bf16", "f32")])
-@pytest.mark.parametrize("bs", [(8, 8), (8, 16), (16, 8)])
+@pytest.mark.parametrize("bs", [(8, 8), (8, 16), (16, 8), (16, 16)])
 @pytest.mark.parametrize("tune", ["variant=6,mt=4,nw=8", "variant=6,mt=4,nw=1", "variant=6,mt=2,nw=4", "variant=6,mt=1,nw=2"])
 def test_forced_shapes(oracle_mod, monkeypatch, dtype, out, bs, tune):
     """Every workgroup shape on both sides of a tile's rows; three windows and a ragged fourth, one window, a row of one
     slab; a last quad with one, two and four groups of 16 rows."""
     import paper_2007_13055_amd as lib
     monkeypatch.setenv("BSR_SPMM_TUNE", tune)
+    if bs == (16, 16) and dtype == "f32":             # no plan for these
+        with pytest.raises(lib.BsrError):
+            gpu_product(_problem(16, 4, 4, bs, dtype, out, 700), path=lib.PATH_MFMA)
+        return
     cols = 256 if dtype == "f32" else 512
     for i, (m, C, rows) in enumerate([(16, cols // bs[1], 80), (65, (3 * cols + 16) // bs[1], 144), (127, 16 // bs[1], 64), (130, (cols + 48) // bs[1], 608)]):
         p = _problem(m, rows // bs[0], C, bs, dtype, out, 700 + i)
@@ -73,3 +77,20 @@ def test_which_kernel(oracle_mod, monkeypatch, dtype, m, R, C, tiles):
         forced[v], _ = gpu_product(p, path=lib.PATH_MFMA)
     assert np.array_equal(Y, forced[7 if tiles else 6])
     assert dtype != "f32" or not np.array_equal(forced[6], forced[7])
+
+
+@pytest.mark.parametrize("dtype,out", [("f16", "f16"), ("bf16", "f32")])
+@pytest.mark.parametrize("m,R,C,count,other,sweeps", [(600, 96, 376, 40, 2, True), (16, 96, 376, 40, 2, False),
+                                                      (300, 400, 128, 40, 4, True), (300, 400, 32, 5, 4, False)])
+def test_which_kernel_16x16(oracle_mod, monkeypatch, dtype, out, m, R, C, count, other, sweeps):
+    """16x16 blocks: both sides of the rules against the k-split and the stripe kernel, told by the bits of fp32 results."""
+    import paper_2007_13055_amd as lib
+    p = wl.make_problem("which", m, C * 16, R * 16, 16, 16, dtype, out, ("counts", np.full(R, count)), ("normal", 1.0), ("normal", 1.0), 11)
+    Yo, So = oracle_mod.bsr_spmm(p.X, p.block_data, p.block_indices, p.index_pointer, p.n)
+    Y, _ = gpu_product(p)
+    check(Y, Yo, So, p.tau, f"{dtype}->{out} m={m} R={R} C={C}", out_dtype=out)
+    monkeypatch.setenv("BSR_SPMM_TUNE", f"variant={6 if sweeps else other}")
+    assert np.array_equal(Y, gpu_product(p, path=lib.PATH_MFMA)[0])
+    if out == "f32":
+        monkeypatch.setenv("BSR_SPMM_TUNE", f"variant={other if sweeps else 6}")
+        assert not np.array_equal(Y, gpu_product(p, path=lib.PATH_MFMA)[0])
