@@ -166,7 +166,7 @@ bool mfma_supports(const bsr_matrix* W)
 //           stripe is copied to LDS once and many block-rows are multiplied against it
 //   sweep   16x16 blocks of a 16-bit type where neither of the two above reads X often enough from LDS: a stripe that is
 //           short for want of LDS, or none, and more items than the k-split kernel's loads from L2 keep up with
-//   direct  everything else: block-rows of a block or two, where writing Y is most of the work
+//   direct  everything else: block-rows of a block or two and none of many, where writing Y is most of the work
 //           (operands straight from global memory)
 bsr_status launch_mfma(const spmm_args& a, const tune_opts& tune)
 {
@@ -185,7 +185,11 @@ bsr_status launch_mfma(const spmm_args& a, const tune_opts& tune)
         if (sub * a.W->R < 6000 && (a.W->mean_row_blocks > 1.5 || tall_few)) variant = 2;
         else if (a.W->bs_r >= 32 && a.m >= 512) variant = 3;
         else if (a.m >= 256 && mfma_stripe_supports(a.W, 16)) variant = 4;
-        else if (a.W->mean_row_blocks > 4.0) variant = 2;     // 16-row blocks the tile kernel does not take
+        // 16-row blocks the tile kernel does not take; and where one block-row is long beside short ones, a wavefront of the
+        // direct kernel that walks it alone decides (1.2 to 3 blocks a row on average, longest row, direct against k-split,
+        // us: bf16 32x32 442 x (896, 7552) 28, 15.9, 8.0; fp32 16x16 892 x (832, 2928) 52, 24.2, 16.2, 6663 x (960, 3648)
+        // 60, 90, 74; 1609 x (320, 3520) 20, 20.2, 19.5; 24 x (256, 1024) 16, 5.3, 4.9; but 219 x (368, 1584) 12, 4.7, 5.2)
+        else if (a.W->mean_row_blocks > 4.0 || (a.W->max_row_blocks >= 16 && mfma_ksplit_reaches(a.W))) variant = 2;
         else variant = 1;
         if ((variant == 2 || variant == 4) && sweep_is_quicker(a.W, a.m, a.y_dtype, variant == 4)) variant = 6;
         // 64x64 16-bit blocks with a few block-rows that hold much of W: those rows in row groups (their X

@@ -25,3 +25,23 @@ def test_strips_of_blocks(oracle_mod, monkeypatch, dtype, out, bs, tune):
         check(Y, Yo, So, p.tau, f"strips {bs} {dtype}->{out} m={m} {tune}", out_dtype=out)
         Y2, _ = gpu_product(p, path=lib.PATH_MFMA if tune else lib.PATH_AUTO, W=W)
         assert np.array_equal(Y, Y2)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,bs", [("f32", 16), ("f32", 32), ("bf16", 32)])
+@pytest.mark.parametrize("longest", [15, 16])
+def test_one_long_row_beside_short_ones(oracle_mod, monkeypatch, dtype, bs, longest):
+    """Both sides of the rule between the direct and the k-split kernel, told by the bits of fp32 results."""
+    import paper_2007_13055_amd as lib
+    counts = np.ones(400, dtype=np.int64)
+    counts[7] = longest
+    p = wl.make_problem("long", 100, 40 * bs, 400 * bs, bs, bs, dtype, "f32", ("counts", counts), ("normal", 1.0), ("normal", 1.0), 5)
+    Yo, So = oracle_mod.bsr_spmm(p.X, p.block_data, p.block_indices, p.index_pointer, p.n)
+    Y, _ = gpu_product(p)
+    check(Y, Yo, So, p.tau, f"{dtype} {bs} longest={longest}", out_dtype="f32")
+    forced = {}
+    for v in (1, 2):
+        monkeypatch.setenv("BSR_SPMM_TUNE", f"variant={v}")
+        forced[v], _ = gpu_product(p, path=lib.PATH_MFMA)
+    assert np.array_equal(Y, forced[2 if longest >= 16 else 1])
+    assert not np.array_equal(forced[1], forced[2])
