@@ -640,8 +640,8 @@ bsr_status bsr_spmm_ex(const bsr_matrix* W, int64_t m, const void* X_dev, void* 
     return run_product(spmm_args{W, m, X_dev, Y_dev, y_dtype, (hipStream_t)hip_stream}, path, t);
 }
 
-// Candidate settings per kernel family for this W and m (the search space of bsr_tune).
-static std::vector<tuned_choice> tune_candidates(const bsr_matrix* W, int64_t m)
+// Candidate settings per kernel family for this W, m and type of result (the search space of bsr_tune).
+static std::vector<tuned_choice> tune_candidates(const bsr_matrix* W, int64_t m, bsr_dtype y_dtype)
 {
     std::vector<tuned_choice> c;
     auto add = [&](bsr_path path, int variant, int nw, int mt, int a, int b) {
@@ -660,7 +660,7 @@ static std::vector<tuned_choice> tune_candidates(const bsr_matrix* W, int64_t m)
         if (m >= 8 && mfma_small_supports(W) && W->dtype == BSR_F32)
             for (int nw : {2, 4, 8})
                 for (int per : {1, 2, 4}) add(BSR_PATH_MFMA, 7, nw, 0, per, 0);
-        if (m >= 8 && (mfma_small_supports(W) || sweeps_odd_sizes(W, m, W->dtype)))
+        if (m >= 8 && (mfma_small_supports(W) || sweeps_odd_sizes(W, m, y_dtype)))
             for (int mt : {1, 2, 4})
                 for (int quads : {1, 2, 4, 8}) add(BSR_PATH_MFMA, 6, quads, mt, 0, 0);
     } else if (mfma_supports(W) && m >= 8) {
@@ -704,7 +704,7 @@ bsr_status bsr_tune(bsr_matrix* W, int64_t m, const void* X_dev, void* Y_dev, bs
     int tried = 0;
     const bool verbose = std::getenv("BSR_TUNE_VERBOSE") != nullptr;   // one line per candidate on stderr
     bsr_status result = BSR_OK;
-    for (tuned_choice cand : tune_candidates(W, m)) {
+    for (tuned_choice cand : tune_candidates(W, m, y_dtype)) {
         bsr_status s = BSR_OK;
         for (int i = 0; i < 2 && s == BSR_OK; ++i) s = run_product(a, cand.path, cand.opts);     // warm-up
         if (s == BSR_ERR_UNSUPPORTED || s == BSR_ERR_WORKSPACE) continue;                         // not for this shape

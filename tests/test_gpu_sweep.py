@@ -62,6 +62,22 @@ def test_sizes_without_whole_tiles(oracle_mod, dtype, out, m, R, sweeps, C):
         gpu_product(p, path=lib.PATH_MFMA, W=W)
 
 
+@pytest.mark.parametrize("out", ["bf16", "f32"])
+def test_tuning_of_sizes_without_whole_tiles(oracle_mod, out):
+    """The trials offer the sweep kernel only for results rounded to 16 bits: an fp32 result keeps the wavefront kernels' 64
+    partial sums, whatever was remembered."""
+    import paper_2007_13055_amd as lib
+    from gpu_util import to_device
+    p = _problem(400, 67, 67, (8, 8), "bf16", out, 3)
+    W = lib.bsr_create(p.n, p.k, p.block_data, p.block_indices, p.index_pointer, dtype="bf16")
+    lib.bsr_tune(W, to_device(p.X, "bf16"), y_dtype=out, trials=3)
+    r = lib.bsr_tune_result(W, p.m, out)
+    assert (r["path"], r["variant"]) == ((lib.PATH_MFMA, 6) if out == "bf16" else (lib.PATH_WAVE, 0))
+    Yo, So = oracle_mod.bsr_spmm(p.X, p.block_data, p.block_indices, p.index_pointer, p.n)
+    Y, _ = gpu_product(p, W=W)
+    check(Y, Yo, So, p.tau, f"tuned {out}", out_dtype=out)
+
+
 @pytest.mark.parametrize("dtype,m,R,C,tiles", [("f32", 383, 24, 60, True), ("f32", 384, 24, 60, False), ("f16", 64, 64, 256, True),
                                                ("f16", 65, 64, 256, False), ("bf16", 64, 64, 254, False), ("bf16", 64, 64, 700, False)])
 def test_which_kernel(oracle_mod, monkeypatch, dtype, m, R, C, tiles):
