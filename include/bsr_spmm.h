@@ -140,7 +140,9 @@ void bsr_destroy(bsr_matrix* W);
  * or its workspace lives).  Otherwise it is recorded without one: the same result, less evenly spread over the CUs.
  * NaN or Inf in X: kernels that fill their last, partial group of blocks with zero-valued dummy
  * blocks multiply those zeros by real entries of X (the thin-block kernels: by column 0 of X), so a
- * non-finite entry there can reach outputs it does not belong to.  Finite inputs are unaffected.
+ * non-finite entry there can reach outputs it does not belong to; so do kernels that multiply blocks of 8 rows or columns
+ * in 16x16 tiles or two block-rows at a time (n and k multiples of 16: for other sizes such outputs are summed again from
+ * their own blocks).  Finite inputs are unaffected.
  * Errors: NULL, SHAPE (m < 0 or m*max(k,n) >= 2^31), DTYPE, ALIGN, HIP.
  */
 bsr_status bsr_spmm(const bsr_matrix* W, int64_t m, const void* X_dev, void* Y_dev,

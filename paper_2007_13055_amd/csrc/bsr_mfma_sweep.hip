@@ -65,7 +65,8 @@ template <typename T, typename O, int SUB>
 __global__ __launch_bounds__(64 * (kWaves + kLoaders), 3) void bsr_mfma_sweep(
     const T* __restrict__ X, const T* __restrict__ data, unsigned w_bytes, const i32x4* __restrict__ recs,
     const int32_t* __restrict__ win_ptr, const i32x4* __restrict__ quads, O* __restrict__ Y, int m, int k, int n,
-    int n_tiles, int tiles_padded, int n_quads, int n_win, int q_log, int bs_r, int row_bytes)
+    int n_tiles, int tiles_padded, int n_quads, int n_win, int q_log, int bs_r, int row_bytes,
+    const int32_t* __restrict__ indptr, const int32_t* __restrict__ indices)
 {
     constexpr int S = (int)sizeof(T);
     constexpr int CH = 16 / S;                        // columns of a granule
@@ -234,6 +235,27 @@ __global__ __launch_bounds__(64 * (kWaves + kLoaders), 3) void bsr_mfma_sweep(
 #pragma unroll
                 for (int e = 0; e < EPT; ++e) v[e] += src[e];
             }
+            // An entry of two block-rows multiplies the zeros of the one that does not store the column: an infinity or a
+            // NaN there is no part of its outputs.  Those that came out as NaN are summed again from their own blocks.
+            if (indptr) {                             // uniform
+                bool again = false;
+#pragma unroll
+                for (int e = 0; e < EPT; ++e) again = again || v[e] != v[e];
+                if (again) {
+                    const int bs_c = row_bytes / S;
+                    const T* x = X + (size_t)i * (size_t)k;
+                    const T* w = data + (size_t)(col & 7) * bs_c;
+                    float own[EPT] = {};
+                    for (int b = indptr[col >> 3]; b < indptr[(col >> 3) + 1]; ++b)
+                        for (int u = 0; u < bs_c; ++u) {
+                            const float xv = (float)x[(size_t)indices[b] * bs_c + u];
+#pragma unroll
+                            for (int e = 0; e < EPT; ++e) own[e] += xv * (float)w[((size_t)b * 8 + e) * bs_c + u];
+                        }
+#pragma unroll
+                    for (int e = 0; e < EPT; ++e) v[e] = v[e] != v[e] ? own[e] : v[e];
+                }
+            }
             O* dst = Y + (size_t)i * (size_t)n + col;
             if constexpr (EPT == 4) {
                 *reinterpret_cast<f32x4*>(dst) = f32x4{v[0], v[1], v[2], v[3]};
@@ -291,10 +313,13 @@ bsr_status launch_sub(const spmm_args& a, int q_log)
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&bsr_mfma_sweep<T, O, SUB>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)std::max(ring, out));
     if (attr != hipSuccess) return BSR_ERR_HIP;
+    // where the wavefront kernels would run else, which keep every output to its own blocks
+    const bool own_blocks = W->bs_r == 8 && !mfma_small_supports(W);
     hipLaunchKernelGGL((bsr_mfma_sweep<T, O, SUB>), dim3((unsigned)blocks), dim3(64 * (kWaves + kLoaders)), std::max(ring, out), a.stream,
                        (const T*)a.X, (const T*)W->data, (unsigned)(W->nnzb * W->bs_r * W->bs_c * sizeof(T)),
                        reinterpret_cast<const i32x4*>(W->sw_recs), W->sw_win_ptr, reinterpret_cast<const i32x4*>(W->sw_desc), (O*)a.Y, m, (int)W->k, (int)W->n,
-                       n_tiles, padded, W->sw_quads, W->sw_windows, q_log, W->bs_r, W->bs_c * (int)sizeof(T));
+                       n_tiles, padded, W->sw_quads, W->sw_windows, q_log, W->bs_r, W->bs_c * (int)sizeof(T),
+                       own_blocks ? W->indptr : nullptr, W->indices);
     return hipGetLastError() == hipSuccess ? BSR_OK : BSR_ERR_HIP;
 }
 

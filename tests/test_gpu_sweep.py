@@ -62,6 +62,34 @@ def test_sizes_without_whole_tiles(oracle_mod, dtype, out, m, R, sweeps, C):
         gpu_product(p, path=lib.PATH_MFMA, W=W)
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("bs", [(8, 8), (8, 16), (16, 8)])
+def test_infinities_stay_with_their_blocks(oracle_mod, monkeypatch, dtype, bs):
+    """Sizes without whole tiles, infinities and NaN in X: an output is not finite exactly where one of its own stored
+    blocks reads such an entry, and the others are those of an X without them."""
+    import paper_2007_13055_amd as lib
+    p = _problem(203, 67, 67, bs, dtype, dtype, 8)
+    rng = np.random.default_rng(1)
+    bad = np.zeros(p.X.shape, dtype=bool)
+    bad[rng.integers(0, p.m, 40), rng.integers(0, p.k, 40)] = True
+    bad[202, -1] = bad[0, 0] = True                   # the last row and column, the first
+    p.X[bad] = 0.0
+    Yo, So = oracle_mod.bsr_spmm(p.X, p.block_data, p.block_indices, p.index_pointer, p.n)
+    reads = np.zeros((p.n, p.k), dtype=bool)          # the columns of X that an output's blocks select
+    for r in range(67):
+        for c in p.block_indices[p.index_pointer[r]:p.index_pointer[r + 1]]:
+            reads[r * bs[0]:(r + 1) * bs[0], c * bs[1]:(c + 1) * bs[1]] = True
+    hit = (bad.astype(np.int64) @ reads.T.astype(np.int64)) > 0
+    p.X[bad] = rng.choice([np.inf, -np.inf, np.nan], size=int(bad.sum()))
+    Y, W = gpu_product(p)
+    assert np.array_equal(np.isfinite(Y), ~hit)
+    check(np.where(hit, Yo, Y), Yo, So, p.tau, f"{bs} {dtype}", out_dtype=dtype)
+    wave, _ = gpu_product(p, path=lib.PATH_WAVE, W=W)
+    assert np.array_equal(np.isnan(Y), np.isnan(wave))
+    monkeypatch.setenv("BSR_SPMM_TUNE", "variant=6")
+    assert np.array_equal(Y, gpu_product(p, path=lib.PATH_MFMA)[0], equal_nan=True)   # the sweep kernel did run
+
+
 @pytest.mark.parametrize("out", ["bf16", "f32"])
 def test_tuning_of_sizes_without_whole_tiles(oracle_mod, out):
     """The trials offer the sweep kernel only for results rounded to 16 bits: an fp32 result keeps the wavefront kernels' 64
