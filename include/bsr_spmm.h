@@ -171,7 +171,7 @@ bsr_status bsr_set_scratch(bsr_matrix* W, void* scratch_dev, size_t bytes);
 /*
  * As bsr_spmm() with the kernel family fixed.  BSR_PATH_MFMA needs bs_r and bs_c in {16, 32, 64};
  * or bs_r and bs_c in {8, 16} with n and k multiples of 16 (the blocks are grouped into 16x16
- * tiles); or the thin shape bs_c == 1 with bs_r == 16 and fp32; or its transpose, bs_r == 1 with bs_c == 16,
+ * tiles), with other n and k where bsr_query_path() answers BSR_PATH_MFMA for this m; or the thin shape bs_c == 1 with bs_r == 16 and fp32; or its transpose, bs_r == 1 with bs_c == 16,
  * fp32, fp32 output and no block stored twice; otherwise BSR_ERR_UNSUPPORTED.
  * BSR_PATH_WAVE takes any shape.
  */
@@ -205,8 +205,9 @@ bsr_status bsr_tune(bsr_matrix* W, int64_t m, const void* X_dev, void* Y_dev, bs
 bsr_status bsr_tune_result(const bsr_matrix* W, int64_t m, bsr_dtype y_dtype, int32_t settings_out[6], float* us_out);
 
 /* The path BSR_PATH_AUTO resolves to for this handle, m and an output of W's type (never AUTO; what bsr_tune()
- * remembered is not consulted).  Below 16 rows a 16-bit W may resolve to another one for a BSR_F32 output, whose sums
- * are kept as exact as the wavefront-reduction kernels'.  Errors: NULL. */
+ * remembered is not consulted).  Below 16 rows, and with 8-wide blocks where n or k is no multiple of 16, a 16-bit W may
+ * resolve to another one for a BSR_F32 output, whose sums are kept as exact as the wavefront-reduction kernels'.
+ * Errors: NULL. */
 bsr_status bsr_query_path(const bsr_matrix* W, int64_t m, bsr_path* path_out);
 
 /*

@@ -516,6 +516,17 @@ void bsr_destroy(bsr_matrix* W)
     delete W;
 }
 
+// 8-wide blocks whose n or k is no multiple of 16 have no 16x16 tiles.  The sweep kernel takes them where the wavefront
+// kernels would start many wavefronts (us, bf16 8x8, wavefront kernels and sweep: 64 x (504, 520), 4032 wavefronts 4.7, 4.8;
+// 32 x (520, 4104), 10 %, 2080 wavefronts 5.5, 6.0, 64 rows 7.7, 6.0; 16 x (4104, 1032), 5 %, 8208 wavefronts 6.9, 4.4;
+// 1000 rows 269, 9.7) and the result is rounded to 16 bits: in fp32 it would show that 64 partial sums are more exact than 2
+// to 8 (fp32, m = 400, (512, 8192), 30 %: 1.3e-7 against 3.2e-7).  A caller that asks for the matrix cores by name gets it
+// for the same sizes, and is refused for the others.
+static bool sweeps_odd_sizes(const bsr_matrix* W, int64_t m, bsr_dtype y_dtype)
+{
+    return y_dtype != BSR_F32 && m >= 16 && W->n * ((m + 7) / 8) >= 4000 && !mfma_small_supports(W) && !mfma_supports(W) && mfma_sweep_supports(W);
+}
+
 // Matrix-core tiles are 16 rows of X tall: below that most of a tile is padding, and the wavefront-reduction
 // kernels (the paper's own regime, m <= 8) stream W once instead.  They start a wavefront per output column and
 // group of rows, though, at about 11 cycles each per XCD, while the k-split kernel takes the same 3-5 us whatever m
@@ -531,6 +542,7 @@ static bsr_path auto_path(const bsr_matrix* W, int64_t m, bsr_dtype y_dtype)
     if (mfma_supports(W) && (m >= 16 || (y_dtype != BSR_F32 && (m >= 9 || waves >= 6000) && mfma_ksplit_reaches(W))))
         return BSR_PATH_MFMA;
     if (mfma_small_supports(W) && m >= 16) return BSR_PATH_MFMA;
+    if (sweeps_odd_sizes(W, m, y_dtype)) return BSR_PATH_MFMA;
     // Thin 16x1 fp32 blocks take the matrix-core path when the caller has lent enough scratch for
     // the transposed copy of X, or when their block-rows are stored in block-column order (one launch,
     // no scratch).
@@ -538,17 +550,6 @@ static bsr_path auto_path(const bsr_matrix* W, int64_t m, bsr_dtype y_dtype)
     if (mfma_thinrow_supports(W) && m >= 16) return BSR_PATH_MFMA;   // no scratch: rows of X staged in LDS
     if (mfma_wide_supports(W) && m >= 16) return BSR_PATH_MFMA;      // 1x16 blocks, by block-column
     return BSR_PATH_WAVE;
-}
-
-// 8-wide blocks whose n or k is no multiple of 16 have no 16x16 tiles, so a caller that asks for the matrix cores is
-// refused.  The library's own choice takes the sweep kernel all the same where the wavefront kernels would start many
-// wavefronts (us, bf16 8x8, wavefront kernels and sweep: 64 x (504, 520), 4032 wavefronts 4.7, 4.8; 32 x (520, 4104), 10 %,
-// 2080 wavefronts 5.5, 6.0, 64 rows 7.7, 6.0; 16 x (4104, 1032), 5 %, 8208 wavefronts 6.9, 4.4; 1000 rows 269, 9.7) and the
-// result is rounded to 16 bits: in fp32 it would show that 64 partial sums are more exact than 2 to 8 (fp32, m = 400,
-// (512, 8192), 30 %: 1.3e-7 against 3.2e-7).
-static bool sweeps_odd_sizes(const bsr_matrix* W, int64_t m, bsr_dtype y_dtype)
-{
-    return y_dtype != BSR_F32 && m >= 16 && W->n * ((m + 7) / 8) >= 4000 && !mfma_small_supports(W) && mfma_sweep_supports(W);
 }
 
 bsr_status bsr_query_path(const bsr_matrix* W, int64_t m, bsr_path* path_out)
@@ -604,7 +605,7 @@ bsr_status run_product(const spmm_args& a, bsr_path path, const tune_opts& t)
     if (path == BSR_PATH_MFMA) {
         if (mfma_thin_supports(a.W)) return launch_mfma_thin(a, t);
         if (mfma_small_supports(a.W)) return launch_mfma_small(a, t);
-        if (t.variant == 6) return launch_mfma_sweep(a, t);
+        if (t.variant == 6 || sweeps_odd_sizes(a.W, a.m, a.W->dtype)) return launch_mfma_sweep(a, t);
         if (mfma_wide_supports(a.W) && a.y_dtype == BSR_F32) return launch_mfma_wide(a, t);
         if (!mfma_supports(a.W)) return BSR_ERR_UNSUPPORTED;
         return launch_mfma(a, t);
@@ -631,11 +632,7 @@ bsr_status bsr_spmm_ex(const bsr_matrix* W, int64_t m, const void* X_dev, void* 
         // a remembered thin-block choice needs its scratch still lent
         if (tuned && path == BSR_PATH_MFMA && mfma_thin_supports(W) && !(t.variant == 2 && mfma_thinrow_supports(W)) &&
             (!W->scratch || W->scratch_bytes < mfma_thin_scratch_bytes(W, m))) tuned = false;
-        if (!tuned) {
-            path = auto_path(W, m, y_dtype);
-            if (!t.from_env) t = tune_opts{};
-            if (path == BSR_PATH_WAVE && !t.from_env && sweeps_odd_sizes(W, m, y_dtype)) { path = BSR_PATH_MFMA; t.variant = 6; }
-        }
+        if (!tuned) { path = auto_path(W, m, y_dtype); if (!t.from_env) t = tune_opts{}; }
     }
     return run_product(spmm_args{W, m, X_dev, Y_dev, y_dtype, (hipStream_t)hip_stream}, path, t);
 }

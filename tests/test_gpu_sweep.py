@@ -49,7 +49,8 @@ def test_forced_shapes(oracle_mod, monkeypatch, dtype, out, bs, tune):
 @pytest.mark.parametrize("C", [33, 67])
 def test_sizes_without_whole_tiles(oracle_mod, dtype, out, m, R, sweeps, C):
     """n or k an odd multiple of 8: the library's own choice on both sides of where it takes the sweep kernel, told by the
-    bits of both; a caller that asks for the matrix cores is refused as before."""
+    bits of both; what bsr_query_path() answers for a result of W's type is what runs; a caller that asks for the matrix
+    cores gets the sweep kernel for these sizes, and is refused for the others."""
     import paper_2007_13055_amd as lib
     p = _problem(m, R, C, (8, 8), dtype, out, 40 + m)
     Yo, So = oracle_mod.bsr_spmm(p.X, p.block_data, p.block_indices, p.index_pointer, p.n)
@@ -57,9 +58,15 @@ def test_sizes_without_whole_tiles(oracle_mod, dtype, out, m, R, sweeps, C):
     check(Y, Yo, So, p.tau, f"{dtype}->{out} m={m} R={R} C={C}", out_dtype=out)
     wave, _ = gpu_product(p, path=lib.PATH_WAVE, W=W)
     assert np.array_equal(Y, wave) == (not sweeps)
-    assert lib.bsr_query_path(W, m) == lib.PATH_WAVE
-    with pytest.raises(lib.BsrError):
-        gpu_product(p, path=lib.PATH_MFMA, W=W)
+    by_name = sweeps or (dtype, out) == ("bf16", "f32")   # where a result of W's type is swept
+    assert lib.bsr_query_path(W, m) == (lib.PATH_MFMA if by_name else lib.PATH_WAVE)
+    if not by_name:
+        with pytest.raises(lib.BsrError):
+            gpu_product(p, path=lib.PATH_MFMA, W=W)
+        return
+    named, _ = gpu_product(p, path=lib.PATH_MFMA, W=W)
+    check(named, Yo, So, p.tau, f"by name, {dtype}->{out} m={m} R={R} C={C}", out_dtype=out)
+    assert np.array_equal(Y, named) == sweeps
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
