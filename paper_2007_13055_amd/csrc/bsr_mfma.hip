@@ -14,6 +14,8 @@
 // one, so a lane's operand is a contiguous run of CH elements of a block row / an X row.  The
 // lane groups split the bs_c columns of a block into 64/MM contiguous runs; W and X use the same
 // split, so the sum over c is complete whatever order the instruction takes its k in.
+#include <numeric>
+
 #include "bsr_mfma_common.h"
 
 using namespace bsr_dev;
@@ -156,6 +158,28 @@ bool mfma_supports(const bsr_matrix* W)
     return r_ok && c_ok && W->R > 0;
 }
 
+// Whether the k-split kernel is the quicker one for short block-rows of which at least one has 16 blocks or more.  The direct
+// kernel waits for the wavefront that walks the longest; the k-split kernel pays a workgroup per (block-row, 16 rows) item
+// with a block or two.  Blocks of 32 and 64 rows come here below 512 rows only: k-split took 0.21 to 0.91 of the direct
+// kernel's time in 88 products.  16-row blocks: up to the items its work lists hold it was never the slower one (457
+// products, fp32 and 16-bit, 0.27 to 0.99), beyond that the estimates below decide, in microseconds, fitted to 710 of 1396
+// products (16 to 8192 rows, 8 to 512 block-rows of half a block to 3 on average, longest row 16 to 160; half of the estimates
+// within 10 % of the time, nine tenths within 30 %).  With a margin of a tenth, 9 of 1368 products are more than 3 % slower than
+// the direct kernel would be, and of 618 further ones 6, at most 13 %; with k-split for every one of the 1368 it was 165, up
+// to 2.1 times as slow (fp32 16x16, longest row, direct and k-split, us: 6908 rows by 437 block-rows 16, 49, 101; 4422 by 315
+// 22, 32, 51; but 6569 by 66 90, 59, 33; 490 by 439 98, 31, 20).
+static bool long_row_by_ksplit(const bsr_matrix* W, int64_t m)
+{
+    const double tiles = (double)((m + 15) / 16), items = tiles * W->R;
+    if (W->bs_r >= 32 || items <= kMaxKsplitItems) return true;
+    const double wide = W->bs_c * (W->dtype == BSR_F32 ? 4 : 2) / 64.0, blocks = wide * tiles * (double)W->nnzb, longest = wide * W->max_row_blocks;
+    // the tiles of one block-row start R workgroups apart: on 8 / gcd(R, 8) of the XCDs
+    const double xcds = 8.0 / std::gcd(W->R, 8);
+    const double direct = 2.5 + 1.7e-4 * items + 1.67e-4 * blocks + 9e-4 * tiles * longest / xcds + (m > 1008 ? 0.264 : 0.132) * longest;
+    const double ksplit = 2.85 + 5.3e-4 * items + 8.25e-5 * blocks + 0.0424 * longest;
+    return ksplit < 0.9 * direct;
+}
+
 // Which matrix-core kernel serves this product.
 //   ksplit  fewer than about 6000 (m-tile, block-row) items and block-rows of more than a block or two (or few items of
 //           tall blocks): the stored blocks of a block-row are spread over the wavefronts of a workgroup, otherwise
@@ -166,7 +190,7 @@ bool mfma_supports(const bsr_matrix* W)
 //           stripe is copied to LDS once and many block-rows are multiplied against it
 //   sweep   16x16 blocks of a 16-bit type where neither of the two above reads X often enough from LDS: a stripe that is
 //           short for want of LDS, or none, and more items than the k-split kernel's loads from L2 keep up with
-//   direct  everything else: block-rows of a block or two and none of many, where writing Y is most of the work
+//   direct  everything else: block-rows of a block or two and none that decides, where writing Y is most of the work
 //           (operands straight from global memory)
 bsr_status launch_mfma(const spmm_args& a, const tune_opts& tune)
 {
@@ -181,17 +205,17 @@ bsr_status launch_mfma(const spmm_args& a, const tune_opts& tune)
         // 3.1, 4.5, 512 items 4.0, 6.8; f16 32x32 2.9, 2.8 and 3.2, 3.7; f16 64x64 3.0, 3.8 and 4.2, 8.3; 16x16 64
         // items 2.84, 2.53, 640 items 2.93, 2.76).  768 is where the k-split kernel goes over to 32-row tiles; it is no
         // crossing of times (f16 32x32, 1216 items: 3.7, and 4.6 direct).
+        bool long_row = false;
         const bool tall_few = a.W->bs_r >= 32 && sub * a.W->R < 768 && mfma_ksplit_reaches(a.W);
         if (sub * a.W->R < 6000 && (a.W->mean_row_blocks > 1.5 || tall_few)) variant = 2;
         else if (a.W->bs_r >= 32 && a.m >= 512) variant = 3;
         else if (a.m >= 256 && mfma_stripe_supports(a.W, 16)) variant = 4;
-        // 16-row blocks the tile kernel does not take; and where one block-row is long beside short ones, a wavefront of the
-        // direct kernel that walks it alone decides (1.2 to 3 blocks a row on average, longest row, direct against k-split,
-        // us: bf16 32x32 442 x (896, 7552) 28, 15.9, 8.0; fp32 16x16 892 x (832, 2928) 52, 24.2, 16.2, 6663 x (960, 3648)
-        // 60, 90, 74; 1609 x (320, 3520) 20, 20.2, 19.5; 24 x (256, 1024) 16, 5.3, 4.9; but 219 x (368, 1584) 12, 4.7, 5.2)
-        else if (a.W->mean_row_blocks > 4.0 || (a.W->max_row_blocks >= 16 && mfma_ksplit_reaches(a.W))) variant = 2;
-        else variant = 1;
+        // 16-row blocks the tile kernel does not take
+        else if (a.W->mean_row_blocks > 4.0) variant = 2;
+        // one block-row long beside short ones, which a wavefront of the direct kernel would walk alone
+        else variant = (long_row = a.W->max_row_blocks >= 16 && mfma_ksplit_reaches(a.W)) ? 2 : 1;
         if ((variant == 2 || variant == 4) && sweep_is_quicker(a.W, a.m, a.y_dtype, variant == 4)) variant = 6;
+        if (variant == 2 && long_row && !long_row_by_ksplit(a.W, a.m)) variant = 1;
         // 64x64 16-bit blocks with a few block-rows that hold much of W: those rows in row groups (their X
         // tiles shared through LDS), the rest through the tile kernel (112 against 135 us on the 8192^3
         // power-law workload, 403 instead of 825 MB fetched)

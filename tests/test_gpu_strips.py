@@ -45,3 +45,19 @@ def test_one_long_row_beside_short_ones(oracle_mod, monkeypatch, dtype, bs, long
         forced[v], _ = gpu_product(p, path=lib.PATH_MFMA)
     assert np.array_equal(Y, forced[2 if longest >= 16 else 1])
     assert not np.array_equal(forced[1], forced[2])
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("R,longest,variant", [(300, 20, 1), (66, 90, 2)])
+def test_long_row_of_many_items(oracle_mod, monkeypatch, R, longest, variant):
+    """More (block-row, 16 rows) items than a work list holds: both sides of the estimate between the two kernels."""
+    import paper_2007_13055_amd as lib
+    counts = np.ones(R, dtype=np.int64)
+    counts[7] = longest
+    p = wl.make_problem("long", 2100, 90 * 16, R * 16, 16, 16, "f32", "f32", ("counts", counts), ("normal", 1.0), ("normal", 1.0), 6)
+    Yo, So = oracle_mod.bsr_spmm(p.X, p.block_data, p.block_indices, p.index_pointer, p.n)
+    Y, _ = gpu_product(p)
+    check(Y, Yo, So, p.tau, f"R={R} longest={longest}")
+    for v in (1, 2):
+        monkeypatch.setenv("BSR_SPMM_TUNE", f"variant={v}")
+        assert np.array_equal(Y, gpu_product(p, path=lib.PATH_MFMA)[0]) == (v == variant)
