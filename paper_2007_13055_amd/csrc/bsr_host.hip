@@ -390,17 +390,16 @@ bsr_status bsr_create(bsr_matrix** out, int64_t n, int64_t k, int32_t bs_r, int3
                        n % 16 == 0 && k % 16 == 0 && nnzb > 0 &&
                        nnzb * bs_r * bs_c * (dtype == BSR_F32 ? 4 : 2) < ((int64_t)1 << 31);
     if (small) W->sb_rows = (int32_t)(n / 16);
-    if (small && (dtype == BSR_F32 || small_blocks_16bit(W, 16))) {
+    if (small && (dtype == BSR_F32 || small_blocks_16bit(W, 16) || !sweep_takes(W))) {
         const int SR = 16 / bs_r, SC = 16 / bs_c;
         const int64_t TR = n / 16;
         const int32_t blk_bytes = bs_r * bs_c * (dtype == BSR_F32 ? 4 : 2);
         struct entry { int32_t tc; int32_t off[4]; };
         std::vector<std::vector<entry>> rows((size_t)TR);
         size_t n_entries = 0;
-        std::vector<int32_t> from((size_t)(k / 16));   // the tile-row's first entry of each tile-column
+        std::vector<int32_t> from((size_t)(k / 16), -1);   // the tile-row's first entry of each tile-column
         for (int64_t tr = 0; tr < TR; ++tr) {
             auto& list = rows[(size_t)tr];
-            std::fill(from.begin(), from.end(), -1);
             for (int qa = 0; qa < SR; ++qa) {
                 const int64_t r = tr * SR + qa;
                 for (int32_t p = index_pointer_host[r]; p < index_pointer_host[r + 1]; ++p) {
@@ -419,6 +418,7 @@ bsr_status bsr_create(bsr_matrix** out, int64_t n, int64_t k, int32_t bs_r, int3
                     slot->off[pos] = p * blk_bytes;
                 }
             }
+            for (const auto& e : list) from[(size_t)e.tc] = -1;
             std::stable_sort(list.begin(), list.end(), [](const entry& a, const entry& b) { return a.tc < b.tc; });
             n_entries += list.size();
         }

@@ -132,7 +132,7 @@ struct bsr_matrix {
     int device = 0;                          // that device
     tune_opts env_tune;                      // BSR_SPMM_TUNE as it was when the handle was created
     // Blocks smaller than an MFMA tile (bs_r, bs_c in {8,16}, not both 16; n and k multiples of 16; 16-bit types: only
-    // where small_blocks_16bit() may want it), grouped into 16x16 tiles of W (see bsr_create): descriptors of the tile-rows, longest first,
+    // where small_blocks_16bit() may want it or the sweep kernel does not take W), grouped into 16x16 tiles of W (see bsr_create): descriptors of the tile-rows, longest first,
     // [sb_rows][kRowDescWords] = {tile-row, first entry, entries, 0, first tile-columns}; per entry the
     // byte offsets of the tile's blocks in block_data, [entries][4] (2^31: no block there), and its
     // tile-column, [entries].
@@ -271,6 +271,7 @@ inline bool small_blocks_16bit(const bsr_matrix* W, int64_t m)
 bsr_status launch_mfma_sweep(const spmm_args& a, const tune_opts& t);
 bool mfma_sweep_supports(const bsr_matrix* W);
 bool sweep_is_quicker(const bsr_matrix* W, int64_t m, bsr_dtype y_dtype, bool than_stripes);   // 16x16 blocks
+bool sweep_takes(const bsr_matrix* W);              // by its shape, type and sizes
 void build_sweep_plan(bsr_matrix* W, const int32_t* index_pointer_host, const int32_t* block_indices_host, size_t* words);
 size_t sweep_plan_words(int64_t n, int64_t k, int32_t bs_r, int32_t bs_c, int64_t nnzb);
 size_t mfma_thin_scratch_bytes(const bsr_matrix* W, int64_t m);   // bytes of the transposed copy of X

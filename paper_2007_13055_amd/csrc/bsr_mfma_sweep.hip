@@ -388,15 +388,25 @@ size_t sweep_plan_words(int64_t n, int64_t k, int32_t bs_r, int32_t bs_c, int64_
 {
     if (!sweep_shape(bs_r, bs_c) || nnzb == 0) return 0;
     const size_t quads = (size_t)(n + 63) / 64, windows = (size_t)(k + 255) / 256;
+    // the table of first rounds must not outgrow the blocks (256 KiB are always fine); where most windows of a quad hold none,
+    // moving all of X through LDS is no gain either
+    if (quads * (windows + 1) > 4 * (size_t)nnzb + 65536) return 0;
     const size_t rounds = std::min((size_t)nnzb, (size_t)nnzb / (bs_r == 16 && bs_c == 16 ? 2 : 16 / bs_c) + quads * windows);
     return 4 * quads + quads * (windows + 1) + 64 * rounds + 2 * 64;
+}
+
+bool sweep_takes(const bsr_matrix* W)
+{
+    const int S = W->dtype == BSR_F32 ? 4 : 2;
+    return sweep_plan_words(W->n, W->k, W->bs_r, W->bs_c, W->nnzb) > 0 && !(W->bs_r == 16 && W->bs_c == 16 && S == 4) &&
+           W->nnzb * W->bs_r * W->bs_c * S < ((int64_t)1 << 31) && reaches(W, 1);
 }
 
 void build_sweep_plan(bsr_matrix* W, const int32_t* indptr, const int32_t* indices, size_t* words)
 {
     const int bs_r = W->bs_r, bs_c = W->bs_c, S = W->dtype == BSR_F32 ? 4 : 2;
     const int64_t row_bytes = (int64_t)bs_c * S, block = bs_r * row_bytes;
-    if (!sweep_shape(bs_r, bs_c) || (bs_r == 16 && bs_c == 16 && S == 4) || W->nnzb == 0 || W->nnzb * block >= ((int64_t)1 << 31) || !reaches(W, 1)) return;
+    if (!sweep_takes(W)) return;
     const int gran = (int)(row_bytes / 16);           // granules of a block's row: 1, 2 or 4
     const int per_entry = 4 / gran;                   // block-columns of an entry
     const int win_cols = kSlabs * 128 / S, n_win = (int)((W->k + win_cols - 1) / win_cols);

@@ -55,6 +55,13 @@ def test_workspace_size(lib):
         lib.bsr_workspace_size(3072, 3071, 32, 32, 922)
 
 
+def test_workspace_follows_rows_and_blocks(lib):
+    """A W of few blocks and many rows and columns: no part of the plan grows with rows times columns (per block-row of 8
+    it is below 400 bytes)."""
+    for size in (1 << 20, 1 << 22):
+        assert lib.bsr_workspace_size(size, size, 8, 8, 10000) < size // 8 * 400 + (16 << 20)
+
+
 def test_status_strings(lib):
     seen = {lib.bsr_status_string(s) for s in range(11)}
     assert len(seen) == 11 and lib.bsr_status_string(0) == "ok"

@@ -145,3 +145,17 @@ def test_which_kernel_16x16(oracle_mod, monkeypatch, dtype, out, m, R, C, count,
     if out == "f32":
         monkeypatch.setenv("BSR_SPMM_TUNE", f"variant={other if sweeps else 6}")
         assert not np.array_equal(Y, gpu_product(p, path=lib.PATH_MFMA)[0])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_too_sparse_to_sweep(oracle_mod, monkeypatch, dtype):
+    """A plan of windows would be larger than W by far: no such plan, and the kernel of 16x16 tiles for any m."""
+    counts = np.zeros(4096, dtype=np.int64)
+    counts[[5, 6, 2000, 4095]] = 16
+    p = wl.make_problem("sparse", 400, 1 << 15, 1 << 15, 8, 8, dtype, "f32", ("counts", counts), ("normal", 1.0), ("normal", 1.0), 2)
+    Yo, So = oracle_mod.bsr_spmm(p.X, p.block_data, p.block_indices, p.index_pointer, p.n)
+    Y, _ = gpu_product(p)
+    check(Y, Yo, So, p.tau, dtype)
+    for v in (6, 7):
+        monkeypatch.setenv("BSR_SPMM_TUNE", f"variant={v}")
+        assert np.array_equal(Y, gpu_product(p)[0])
