@@ -27,8 +27,8 @@
  * re-checks, on the device and before every product (bsr_spmm, bsr_spmm_ex, bsr_spmm_static, bsr_sddmm,
  * bsr_sddmm_ws), the arrays every kernel address derives from: index_pointer and block_indices as they are in device
  * memory at that moment (BSR_ERR_INDPTR, BSR_ERR_INDEX) and the plan in the workspace
- * (BSR_ERR_WORKSPACE when it no longer holds what bsr_create() wrote, or the first sampled product of its own).  On a failure nothing else is
- * launched.  The check waits for the stream (one extra launch, a 16-byte copy, a synchronisation), so
+ * (BSR_ERR_WORKSPACE when it no longer holds what bsr_create() wrote, or the first product that wanted more of
+ * it).  On a failure nothing else is launched.  The check waits for the stream (one extra launch, a 16-byte copy, a synchronisation), so
  * such a call is NOT asynchronous; it is skipped while the stream is being captured into a graph.
  */
 #ifndef BSR_SPMM_H
@@ -138,6 +138,9 @@ void bsr_destroy(bsr_matrix* W);
  * A product recorded into a graph uses such a list only if an eager product of that m has uploaded it before and the
  * upload is over; the list is then kept for the graph's replays (up to 3 values of m per handle, as long as the handle
  * or its workspace lives).  Otherwise it is recorded without one: the same result, less evenly spread over the CUs.
+ * Likewise the kernel that sweeps blocks with sides of 8 or 16 has a plan that the first product that wants it builds (host
+ * time: 0.05 ms for 3000 stored blocks, 0.7 ms for 50000) and uploads; a product recorded before that runs on another kernel.
+ * (16-bit blocks with one side of 8, n and k multiples of 16: built by bsr_create().)
  * NaN or Inf in X: kernels that fill their last, partial group of blocks with zero-valued dummy
  * blocks multiply those zeros by real entries of X (the thin-block kernels: by column 0 of X), so a
  * non-finite entry there can reach outputs it does not belong to; so do kernels that multiply blocks of 8 rows or columns

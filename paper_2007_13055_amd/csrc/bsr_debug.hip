@@ -4,7 +4,7 @@
 //   - every block_indices entry lies in [0, k/bs_c) (the paper's three BSR arrays, Background);
 //   - every row descriptor of the plan still names its block-row's range of index_pointer;
 //   - the plan in the caller's workspace still holds what bsr_create() wrote (a position-weighted sum); before a sampled
-//     product by groups of blocks also that product's own plan, which its first call wrote.
+//     product by groups of blocks, or one of the sweep kernel, also that product's own plan, which its first call wrote.
 // Together with the host checks of m, k, n, alignment and types this bounds every address a kernel forms:
 // rows of X and Y come from m and the launch grid, columns from block_indices and the plan.  The check
 // costs one extra launch, a 16-byte copy and a stream synchronisation per product; it is skipped while the

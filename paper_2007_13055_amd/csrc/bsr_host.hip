@@ -301,7 +301,10 @@ bsr_status bsr_create(bsr_matrix** out, int64_t n, int64_t k, int32_t bs_r, int3
     std::vector<int32_t> cnt((size_t)R);
     for (int64_t r = 0; r < R; ++r) cnt[(size_t)r] = index_pointer_host[r + 1] - index_pointer_host[r];
     const size_t order_words = (((size_t)R * 4 + 255) & ~(size_t)255) / 4;   // row_order, padded to 256 B
-    W->staging.reserve(plan_bytes(R, nnzb, bs_r, bs_c, k) / sizeof(int32_t));   // address space only: pages come as they are written
+    // address space only (pages come as they are written), and none for what is built later or may be
+    const size_t later = kItemSlots * item_table_bytes(R) / sizeof(int32_t) + sddmm_slab_plan_words(k, bs_r, bs_c, nnzb) +
+                         (dtype == BSR_F32 || (bs_r == 16 && bs_c == 16) ? sweep_plan_words(n, k, bs_r, bs_c, nnzb) : 0);
+    W->staging.reserve(plan_bytes(R, nnzb, bs_r, bs_c, k) / sizeof(int32_t) - later);
     W->staging.assign(order_words + (size_t)R * kRowDescWords + 64, 0);
     std::iota(W->staging.begin(), W->staging.begin() + R, 0);
     // Block-rows whose outputs fill whole 128-byte lines of Y by themselves have nothing to gain from their
@@ -459,7 +462,18 @@ bsr_status bsr_create(bsr_matrix** out, int64_t n, int64_t k, int32_t bs_r, int3
     build_group_plan(W, index_pointer_host, block_indices_host, &words);
     build_thinrow_plan(W, index_pointer_host, block_indices_host, &words);
     build_wide_plan(W, index_pointer_host, block_indices_host, &words);
-    build_sweep_plan(W, index_pointer_host, block_indices_host, &words);
+    if (sweep_takes(W)) {
+        W->sw_words = sweep_plan_words(n, k, bs_r, bs_c, nnzb);
+        W->sw_quads = (int32_t)((n + 63) / 64);
+        W->sw_windows = sweep_windows(W);
+        W->sw_created = small && !W->sb_desc;         // nothing else stands in for it
+        if (W->sw_created) {
+            W->sw_base = const_cast<int32_t*>(W->row_order) + words;
+            W->staging.resize(words);
+            build_sweep_plan(W, index_pointer_host, block_indices_host, W->staging);
+            words = W->staging.size();                // records of 64 words end it
+        }
+    }
     size_t upload_words = words;
     {   // the per-m tables sit behind everything else, 256-byte aligned
         W->item_desc = const_cast<int32_t*>(W->row_order) + words;
@@ -472,6 +486,12 @@ bsr_status bsr_create(bsr_matrix** out, int64_t n, int64_t k, int32_t bs_r, int3
         if (W->sl_words) {
             W->sl_base = const_cast<int32_t*>(W->row_order) + words;
             words += W->sl_words;
+        }
+        if (W->sw_words && !W->sw_created) {
+            W->sw_base = const_cast<int32_t*>(W->row_order) + words;
+            words += W->sw_words;
+        }
+        if (W->sl_words || W->sw_words) {
             W->sl_indptr.assign(index_pointer_host, index_pointer_host + R + 1);
             W->sl_indices.assign(block_indices_host, block_indices_host + nnzb);
         }
@@ -505,7 +525,7 @@ bsr_status bsr_create(bsr_matrix** out, int64_t n, int64_t k, int32_t bs_r, int3
 void bsr_destroy(bsr_matrix* W)
 {
     if (!W) return;
-    std::vector<hipEvent_t> events{W->plan_uploaded, W->sl.uploaded};
+    std::vector<hipEvent_t> events{W->plan_uploaded, W->sl.uploaded, W->sw.uploaded};
     for (const auto& t : W->item_tables) events.push_back(t.uploaded);
     for (hipEvent_t e : events) {                     // uploads read the handle's host buffers
         if (!e) continue;
@@ -605,10 +625,12 @@ bsr_status run_product(const spmm_args& a, bsr_path path, const tune_opts& t)
     if (path == BSR_PATH_MFMA) {
         if (mfma_thin_supports(a.W)) return launch_mfma_thin(a, t);
         if (mfma_small_supports(a.W)) return launch_mfma_small(a, t);
-        if (t.variant == 6 || sweeps_odd_sizes(a.W, a.m, a.W->dtype)) return launch_mfma_sweep(a, t);
         if (mfma_wide_supports(a.W) && a.y_dtype == BSR_F32) return launch_mfma_wide(a, t);
-        if (!mfma_supports(a.W)) return BSR_ERR_UNSUPPORTED;
-        return launch_mfma(a, t);
+        if (mfma_supports(a.W)) return launch_mfma(a, t);
+        if (t.variant != 6 && !sweeps_odd_sizes(a.W, a.m, a.W->dtype)) return BSR_ERR_UNSUPPORTED;
+        const bsr_status st = launch_mfma_sweep(a, t);
+        if (st != BSR_ERR_UNSUPPORTED || !mfma_sweep_supports(a.W)) return st;
+        return launch_wave(a, tune_opts{});           // its plan is not there: nothing was launched
     }
     return launch_wave(a, t);
 }

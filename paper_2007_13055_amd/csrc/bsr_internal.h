@@ -114,15 +114,27 @@ struct bsr_matrix {
     const int32_t* wide_chunks = nullptr;
     const int32_t* wide_chunk_ptr = nullptr;
     int32_t wide_nq = 0;
-    // Sweep kernel (bsr_mfma_sweep.hip; block sides 8 or 16): the quads (64 outputs) by rounds, longest
-    // first, {quad, first round, end of its rounds, 0}; per quad the first round of each window and the end,
-    // [sw_quads][sw_windows + 1]; per round 64 words, {byte offset of the values, place of the granule in the window}
-    // for (granule, half of the rows, group of 16 rows).
-    const int32_t* sw_desc = nullptr;
-    const int32_t* sw_win_ptr = nullptr;
-    const int32_t* sw_recs = nullptr;        // null when the kernel cannot take this W
+    // Sweep kernel (bsr_mfma_sweep.hip; block sides 8 or 16).  Its plan: the quads (64 outputs) by rounds, longest
+    // first, {quad, first round, end of its rounds, 0}; at win_at per quad the first round of each window and the end,
+    // [sw_quads][sw_windows + 1]; at recs_at per round 64 words, {byte offset of the values, place of the granule in the
+    // window} for (granule, half of the rows, group of 16 rows).  Where another kernel can stand in for it the first
+    // product that wants it builds it, from the pattern below (an fp32 W of 8-wide blocks that only sees few rows never
+    // pays for it); else bsr_create does, as part of what it uploads.
+    int32_t* sw_base = nullptr;              // device; null when the kernel cannot take this W
+    size_t sw_words = 0;                     // of the workspace
     int32_t sw_quads = 0, sw_windows = 0;
-    int64_t sw_rounds = 0, sw_longest = 0;   // rounds of all quads, of the longest
+    bool sw_created = false;                 // bsr_create has built and sent it
+    struct sweep_plan {
+        bool built = false, sent = false;
+        std::vector<int32_t> host;           // kept for the asynchronous upload
+        size_t win_at = 0, recs_at = 0;      // words
+        std::atomic<bool> counted{false};
+        int64_t rounds = 0, longest = 0;     // of all quads, of the longest: what the choice of kernel asks for
+        hipEvent_t uploaded = nullptr;
+        std::atomic<bool> landed{false};
+    };
+    mutable std::mutex sw_mu;
+    mutable sweep_plan sw;
     // Debug mode (BSR_SPMM_DEBUG=1 at bsr_create, bsr_debug.hip): the device arrays are re-checked before every product
     bool debug = false;
     size_t debug_words = 0;                  // words of the plan that never change after bsr_create
@@ -143,7 +155,7 @@ struct bsr_matrix {
     // which its four quadrants start (-1: not stored).
     // Built by the first sampled product that wants it (a handle that only multiplies never pays for it), from host
     // copies of the pattern, into sl_words words of the workspace that bsr_create set aside.
-    std::vector<int32_t> sl_indptr, sl_indices;
+    std::vector<int32_t> sl_indptr, sl_indices;   // the sweep kernel's plan is built from them, too
     int32_t* sl_base = nullptr;              // device
     size_t sl_words = 0;
     struct slab_plan {
@@ -267,12 +279,17 @@ inline bool small_blocks_16bit(const bsr_matrix* W, int64_t m)
     return (m + 15) / 16 * tile_rows <= 128 && W->k >= 2048 && W->nnzb <= 80 * tile_rows;
 }
 // The same blocks, many rows of X: swept in windows of columns that a workgroup's outputs share through LDS.  n and k may
-// be any multiples of 8.
+// be any multiples of 8.  BSR_ERR_UNSUPPORTED without a launch where sweep_ready() is false.
 bsr_status launch_mfma_sweep(const spmm_args& a, const tune_opts& t);
 bool mfma_sweep_supports(const bsr_matrix* W);
 bool sweep_is_quicker(const bsr_matrix* W, int64_t m, bsr_dtype y_dtype, bool than_stripes);   // 16x16 blocks
 bool sweep_takes(const bsr_matrix* W);              // by its shape, type and sizes
-void build_sweep_plan(bsr_matrix* W, const int32_t* index_pointer_host, const int32_t* block_indices_host, size_t* words);
+// Appends the plan to `out` and fills W->sw; may throw.
+void build_sweep_plan(const bsr_matrix* W, const int32_t* index_pointer_host, const int32_t* block_indices_host, std::vector<int32_t>& out);
+// Whether the plan is there for what `stream` is given next: builds it and queues its upload if need be.  A stream that is
+// being captured takes it only once it has landed (what is recorded cannot wait for it).
+bool sweep_ready(const bsr_matrix* W, hipStream_t stream);
+int32_t sweep_windows(const bsr_matrix* W);
 size_t sweep_plan_words(int64_t n, int64_t k, int32_t bs_r, int32_t bs_c, int64_t nnzb);
 size_t mfma_thin_scratch_bytes(const bsr_matrix* W, int64_t m);   // bytes of the transposed copy of X
 // Sampled product by groups of stored blocks that share 128-byte wide slabs of G and X.

@@ -196,6 +196,12 @@ bsr_status launch_mfma(const spmm_args& a, const tune_opts& tune)
 {
     tune_opts t = tune;
     int variant = t.variant;
+    if (variant == 6) {
+        const bsr_status st = launch_mfma_sweep(a, t);
+        if (st != BSR_ERR_UNSUPPORTED || !mfma_sweep_supports(a.W)) return st;
+        t = tune_opts{};                              // its plan is not there: nothing was launched
+        variant = 0;
+    }
     if (variant == 0) {
         // thresholds from timed trials over many sizes (bsr_tune's candidates) on MI355X
         const int MM = a.W->bs_r >= 32 ? 32 : 16;
@@ -214,7 +220,10 @@ bsr_status launch_mfma(const spmm_args& a, const tune_opts& tune)
         else if (a.W->mean_row_blocks > 4.0) variant = 2;
         // one block-row long beside short ones, which a wavefront of the direct kernel would walk alone
         else variant = (long_row = a.W->max_row_blocks >= 16 && mfma_ksplit_reaches(a.W)) ? 2 : 1;
-        if ((variant == 2 || variant == 4) && sweep_is_quicker(a.W, a.m, a.y_dtype, variant == 4)) variant = 6;
+        if ((variant == 2 || variant == 4) && sweep_is_quicker(a.W, a.m, a.y_dtype, variant == 4)) {
+            const bsr_status st = launch_mfma_sweep(a, t);
+            if (st != BSR_ERR_UNSUPPORTED) return st; // else its plan is not there
+        }
         if (variant == 2 && long_row && !long_row_by_ksplit(a.W, a.m)) variant = 1;
         // 64x64 16-bit blocks with a few block-rows that hold much of W: those rows in row groups (their X
         // tiles shared through LDS), the rest through the tile kernel (112 against 135 us on the 8192^3
@@ -253,6 +262,5 @@ bsr_status launch_mfma(const spmm_args& a, const tune_opts& tune)
     if (variant == 2) return launch_mfma_ksplit(a, t);
     if (variant == 3) return launch_mfma_tile(a, t);
     if (variant == 4) return launch_mfma_stripe(a, t);
-    if (variant == 6) return launch_mfma_sweep(a, t);
     return launch_mfma_direct(a, t);
 }

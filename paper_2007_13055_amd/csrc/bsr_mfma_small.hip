@@ -215,12 +215,17 @@ bool mfma_small_supports(const bsr_matrix* W) { return W->sb_rows > 0; }
 // of 16 (microseconds of this kernel and that one, 8x8 blocks: bf16 17 x (512, 512) 3.9, 3.8; 260 x (512, 4096), 10 %
 // 9.6, 5.8; 2000 x (6016, 640), 20 % 82, 20.  fp32 waits for the matrix cores in both: 100 x (512, 512) 4.0, 5.2;
 // 260 x (512, 4096), 10 % 13.8, 13.0; 700 x the same 23.5, 19.6; 2000 x (4096, 1024), 5 % 50, 34).
-bsr_status launch_mfma_small(const spmm_args& a, const tune_opts& t)
+bsr_status launch_mfma_small(const spmm_args& a, const tune_opts& tune)
 {
     const bsr_matrix* W = a.W;
+    tune_opts t = tune;
     if (!mfma_small_supports(W)) return BSR_ERR_UNSUPPORTED;
     const bool sweep = t.variant == 6 || (t.variant != 7 && (W->dtype == BSR_F32 ? a.m >= kSweepRowsF32 : !small_blocks_16bit(W, a.m)));
-    if (!W->sb_desc || (sweep && mfma_sweep_supports(W))) return launch_mfma_sweep(a, t);
+    if (!W->sb_desc || (sweep && mfma_sweep_supports(W))) {
+        const bsr_status st = launch_mfma_sweep(a, t);
+        if (st != BSR_ERR_UNSUPPORTED || !W->sb_desc) return st;
+        if (t.variant == 6) t = tune_opts{};          // its plan is not there: nothing was launched
+    }
     if (W->dtype == BSR_F32) return launch_small_types<float, float>(a, t);
     if (W->dtype == BSR_F16) return a.y_dtype == BSR_F32 ? launch_small_types<_Float16, float>(a, t)
                                                          : launch_small_types<_Float16, _Float16>(a, t);

@@ -277,7 +277,7 @@ bool reaches(const bsr_matrix* W, int sub) { return (int64_t)16 * sub * W->k * (
 // rows by (512 .. 6016, 512 .. 4096), 5 to 25 % (within 3 % of the quickest of the twelve shapes, fp32 within 16 %).
 // Microseconds: what a workgroup takes before its first and after its last round, a window, and a round.
 struct sweep_shape_t { int sub, q_log; double us; };
-sweep_shape_t choose(const bsr_matrix* W, int64_t m, int q_most)
+sweep_shape_t choose(const bsr_matrix* W, int64_t m, int q_most, int64_t all_rounds, int64_t longest)
 {
     const bool f32 = W->dtype == BSR_F32;
     sweep_shape_t best{1, 0, 1e30};
@@ -291,7 +291,7 @@ sweep_shape_t choose(const bsr_matrix* W, int64_t m, int q_most)
             const double round = f32 ? 0.15 + 0.42 * sub : sub == 4 ? 0.40 : 0.32;
             auto us = [&](double rounds) { return start + W->sw_windows * 0.12 * sub + round * (rounds / KS + (KS > 1 ? 0.4 : 0.0) * W->sw_windows); };
             const double p = wgs / 256, passes = p <= 1 ? 1 : p <= 4 ? std::ceil(p) : p + 0.5;
-            const double t = std::max(us((double)W->sw_longest), passes * us((double)W->sw_rounds / W->sw_quads));
+            const double t = std::max(us((double)longest), passes * us((double)all_rounds / W->sw_quads));
             if (t < best.us) best = {sub, q_log, t};
         }
     }
@@ -317,7 +317,8 @@ bsr_status launch_sub(const spmm_args& a, int q_log)
     const bool own_blocks = W->bs_r == 8 && !mfma_small_supports(W);
     hipLaunchKernelGGL((bsr_mfma_sweep<T, O, SUB>), dim3((unsigned)blocks), dim3(64 * (kWaves + kLoaders)), std::max(ring, out), a.stream,
                        (const T*)a.X, (const T*)W->data, (unsigned)(W->nnzb * W->bs_r * W->bs_c * sizeof(T)),
-                       reinterpret_cast<const i32x4*>(W->sw_recs), W->sw_win_ptr, reinterpret_cast<const i32x4*>(W->sw_desc), (O*)a.Y, m, (int)W->k, (int)W->n,
+                       reinterpret_cast<const i32x4*>(W->sw_base + W->sw.recs_at), W->sw_base + W->sw.win_at,
+                       reinterpret_cast<const i32x4*>(W->sw_base), (O*)a.Y, m, (int)W->k, (int)W->n,
                        n_tiles, padded, W->sw_quads, W->sw_windows, q_log, W->bs_r, W->bs_c * (int)sizeof(T),
                        own_blocks ? W->indptr : nullptr, W->indices);
     return hipGetLastError() == hipSuccess ? BSR_OK : BSR_ERR_HIP;
@@ -335,7 +336,7 @@ template <typename T, typename O>
 bsr_status launch_types(const spmm_args& a, const tune_opts& tune)
 {
     const int q_most = most_quads(a.W, a.m, std::is_same<O, float>::value);
-    const sweep_shape_t c = choose(a.W, a.m, q_most);
+    const sweep_shape_t c = choose(a.W, a.m, q_most, a.W->sw.rounds, a.W->sw.longest);
     int sub = c.sub, q_log = c.q_log;
     if ((tune.mt == 1 || tune.mt == 2 || tune.mt == 4) && reaches(a.W, tune.mt)) sub = tune.mt;
     if (tune.nw == 1 || tune.nw == 2 || tune.nw == 4 || tune.nw == 8)
@@ -347,7 +348,41 @@ bsr_status launch_types(const spmm_args& a, const tune_opts& tune)
 
 }  // namespace
 
-bool mfma_sweep_supports(const bsr_matrix* W) { return W->sw_recs != nullptr; }
+bool mfma_sweep_supports(const bsr_matrix* W) { return W->sw_base != nullptr; }
+
+// Rounds of all quads and of the longest of a W of 16x16 blocks, without its plan: a window has as many as half of the
+// blocks of the block-row with the most, rounded up.
+static bool count_rounds(const bsr_matrix* W)
+{
+    if (W->sw.counted.load(std::memory_order_acquire)) return true;
+    std::lock_guard<std::mutex> lock(W->sw_mu);
+    if (W->sw.counted.load(std::memory_order_relaxed)) return true;
+    const int per_window = kSlabs * 128 / 2 / 16;     // block-columns
+    std::vector<int32_t> most, mine;
+    try {
+        most.resize((size_t)W->sw_windows);
+        mine.resize((size_t)W->sw_windows);
+    } catch (const std::bad_alloc&) {
+        return false;
+    }
+    int64_t all = 0, longest = 0;
+    for (int32_t q = 0; q < W->sw_quads; ++q) {
+        std::fill(most.begin(), most.end(), 0);
+        for (int32_t r = 4 * q; r < std::min(4 * q + 4, W->R); ++r) {
+            std::fill(mine.begin(), mine.end(), 0);
+            for (int32_t p = W->sl_indptr[(size_t)r]; p < W->sl_indptr[(size_t)r + 1]; ++p) ++mine[(size_t)(W->sl_indices[(size_t)p] / per_window)];
+            for (size_t w = 0; w < mine.size(); ++w) most[w] = std::max(most[w], mine[w]);
+        }
+        int64_t rounds = 0;
+        for (int32_t c : most) rounds += (c + 1) / 2;
+        all += rounds;
+        longest = std::max(longest, rounds);
+    }
+    W->sw.rounds = all;
+    W->sw.longest = longest;
+    W->sw.counted.store(true, std::memory_order_release);
+    return true;
+}
 
 // The choice for 16x16 blocks between this kernel and the one that would run else, from estimates in microseconds fitted to
 // 225 bf16 products (16 .. 8192 rows, sides 128 .. 8192, 3 to 30 %, uniform and power law).  Half of the estimates are
@@ -358,18 +393,26 @@ bool sweep_is_quicker(const bsr_matrix* W, int64_t m, bsr_dtype y_dtype, bool th
 {
     if (W->bs_r != 16 || W->bs_c != 16 || !mfma_sweep_supports(W)) return false;
     const double tiles = (double)((m + 15) / 16);
-    const double sweep = 2.8 + 1.03 * choose(W, m, most_quads(W, m, y_dtype == BSR_F32)).us + 2.1e-6 * tiles * (double)W->n;
     // stripes: X staged, Y stored, products, and a term for the rows' length; k-split: stored blocks and block-rows of every
     // tile of 16 rows (its X comes from L2 or beyond once per stored block), and the longest block-row
     const double other = than_stripes ? 4.6 + 6.3e-7 * (double)(m * W->k) + 4.7e-7 * (double)(m * W->n) + 2.3e-5 * tiles * (double)W->nnzb + 2.9e-3 * (double)W->k
                                       : 4.1 + 0.84e-4 * tiles * (double)W->nnzb + 3.7e-4 * tiles * W->R + 2.7e-2 * W->max_row_blocks;
-    return sweep < (than_stripes ? 0.7 : 0.75) * other;
+    auto quicker = [&](int64_t rounds, int64_t longest) {
+        const double sweep = 2.8 + 1.03 * choose(W, m, most_quads(W, m, y_dtype == BSR_F32), rounds, longest).us + 2.1e-6 * tiles * (double)W->n;
+        return sweep < (than_stripes ? 0.7 : 0.75) * other;
+    };
+    // with as few rounds as that many blocks can have; only then are they counted
+    return quicker((W->nnzb + 7) / 8, (W->max_row_blocks + 1) / 2) && count_rounds(W) && quicker(W->sw.rounds, W->sw.longest);
 }
 
 bsr_status launch_mfma_sweep(const spmm_args& a, const tune_opts& t)
 {
     const bsr_matrix* W = a.W;
-    if (!mfma_sweep_supports(W)) return BSR_ERR_UNSUPPORTED;
+    if (!mfma_sweep_supports(W) || !sweep_ready(W, a.stream)) return BSR_ERR_UNSUPPORTED;
+    if (!W->sw_created) {
+        const bsr_status dbg = debug_check_words(W, W->sw_base, W->sw.host, a.stream);
+        if (dbg != BSR_OK) return dbg;
+    }
     if (W->dtype == BSR_F32) return launch_types<float, float>(a, t);
     if (W->dtype == BSR_F16) return a.y_dtype == BSR_F32 ? launch_types<_Float16, float>(a, t) : launch_types<_Float16, _Float16>(a, t);
     return a.y_dtype == BSR_F32 ? launch_types<__bf16, float>(a, t) : launch_types<__bf16, __bf16>(a, t);
@@ -395,6 +438,12 @@ size_t sweep_plan_words(int64_t n, int64_t k, int32_t bs_r, int32_t bs_c, int64_
     return 4 * quads + quads * (windows + 1) + 64 * rounds + 2 * 64;
 }
 
+int32_t sweep_windows(const bsr_matrix* W)
+{
+    const int cols = kSlabs * 128 / (W->dtype == BSR_F32 ? 4 : 2);
+    return (int32_t)((W->k + cols - 1) / cols);
+}
+
 bool sweep_takes(const bsr_matrix* W)
 {
     const int S = W->dtype == BSR_F32 ? 4 : 2;
@@ -402,19 +451,17 @@ bool sweep_takes(const bsr_matrix* W)
            W->nnzb * W->bs_r * W->bs_c * S < ((int64_t)1 << 31) && reaches(W, 1);
 }
 
-void build_sweep_plan(bsr_matrix* W, const int32_t* indptr, const int32_t* indices, size_t* words)
+void build_sweep_plan(const bsr_matrix* W, const int32_t* indptr, const int32_t* indices, std::vector<int32_t>& plan)
 {
     const int bs_r = W->bs_r, bs_c = W->bs_c, S = W->dtype == BSR_F32 ? 4 : 2;
     const int64_t row_bytes = (int64_t)bs_c * S, block = bs_r * row_bytes;
-    if (!sweep_takes(W)) return;
     const int gran = (int)(row_bytes / 16);           // granules of a block's row: 1, 2 or 4
     const int per_entry = 4 / gran;                   // block-columns of an entry
-    const int win_cols = kSlabs * 128 / S, n_win = (int)((W->k + win_cols - 1) / win_cols);
-    const int n_groups = (int)((W->n + 15) / 16), n_quads = (n_groups + 3) / 4;
+    const int win_cols = kSlabs * 128 / S, n_win = W->sw_windows;
+    const int n_quads = W->sw_quads;
     struct slot { int32_t col; int32_t off[2]; };     // first column, byte offset of the values for rows 0-7 and 8-15
     std::vector<slot> rows[4];
-    std::vector<int32_t>& plan = W->staging;
-    const size_t desc_at = *words, win_at = desc_at + (4 * (size_t)n_quads + 63) / 64 * 64;
+    const size_t desc_at = plan.size(), win_at = desc_at + (4 * (size_t)n_quads + 63) / 64 * 64;
     const size_t recs_at = win_at + ((size_t)n_quads * (n_win + 1) + 63) / 64 * 64;
     plan.resize(recs_at, 0);
     auto rounds_so_far = [&] { return (int32_t)((plan.size() - recs_at) / 64); };
@@ -497,12 +544,35 @@ void build_sweep_plan(bsr_matrix* W, const int32_t* indptr, const int32_t* indic
         d[2] = p[n_win];
         std::copy(p, p + n_win + 1, plan.begin() + (ptrdiff_t)(win_at + (size_t)s * (n_win + 1)));
     }
-    W->sw_desc = W->row_order + desc_at;
-    W->sw_win_ptr = W->row_order + win_at;
-    W->sw_recs = W->row_order + recs_at;
-    W->sw_rounds = rounds_so_far();
-    *words = plan.size();                             // rounds are 64 words
-    W->sw_quads = n_quads;
-    W->sw_windows = n_win;
-    W->sw_longest = n_quads ? load[(size_t)order[0]] : 0;
+    W->sw.win_at = win_at - desc_at;
+    W->sw.recs_at = recs_at - desc_at;
+    if (!W->sw.counted.load(std::memory_order_relaxed)) {
+        W->sw.rounds = rounds_so_far();
+        W->sw.longest = n_quads ? load[(size_t)order[0]] : 0;
+        W->sw.counted.store(true, std::memory_order_release);
+    }
+    W->sw.built = true;                               // not before: whatever throws leaves it to be built again
+}
+
+bool sweep_ready(const bsr_matrix* W, hipStream_t stream)
+{
+    bsr_matrix::sweep_plan& p = W->sw;
+    if (W->sw_created || p.landed.load(std::memory_order_acquire)) return true;
+    std::lock_guard<std::mutex> lock(W->sw_mu);
+    if (is_capturing(stream)) return p.sent && upload_landed(p.uploaded, p.landed);
+    if (p.sent) {
+        order_after_upload(stream, p.uploaded, p.landed);
+        return true;
+    }
+    if (!p.built) {
+        try {
+            p.host.clear();
+            build_sweep_plan(W, W->sl_indptr.data(), W->sl_indices.data(), p.host);
+        } catch (const std::bad_alloc&) {             // no memory for the plan: the caller takes a kernel that needs none
+            return false;
+        }
+    }
+    p.sent = p.host.size() <= W->sw_words && upload_words(W->sw_base, p.host, stream, p.uploaded, p.landed);
+    if (!p.sent) (void)hipGetLastError();             // nothing was launched, and another kernel will be
+    return p.sent;
 }
