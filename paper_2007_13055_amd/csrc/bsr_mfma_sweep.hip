@@ -61,7 +61,8 @@ __device__ __forceinline__ void load_to_lds(const i32x4& rsrc, unsigned offset, 
 __device__ __forceinline__ constexpr unsigned turn(unsigned r) { return (r >> 1) & 7; }
 __device__ __forceinline__ void window_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-template <typename T, typename O, int SUB>
+// OWN: outputs that come out as NaN are summed again (below).
+template <typename T, typename O, int SUB, bool OWN>
 __global__ __launch_bounds__(64 * (kWaves + kLoaders), 3) void bsr_mfma_sweep(
     const T* __restrict__ X, const T* __restrict__ data, unsigned w_bytes, const i32x4* __restrict__ recs,
     const int32_t* __restrict__ win_ptr, const i32x4* __restrict__ quads, O* __restrict__ Y, int m, int k, int n,
@@ -83,6 +84,7 @@ __global__ __launch_bounds__(64 * (kWaves + kLoaders), 3) void bsr_mfma_sweep(
     const int Q = 1 << q_log, KS = kWaves / Q;
 
     __shared__ int column[kWaves];                    // first output of each of the workgroup's quads
+    __shared__ int not_finite;                        // OWN: some sum may be a NaN
     const int li = lane & 15, h = lane >> 4;
     f32x4 acc[4][SUB];
 #pragma unroll
@@ -133,6 +135,7 @@ __global__ __launch_bounds__(64 * (kWaves + kLoaders), 3) void bsr_mfma_sweep(
         const int32_t* __restrict__ wq = win_ptr + (size_t)min(slot, n_quads - 1) * (n_win + 1);
         int w = -1;
         const int e_first = desc.y, e_last = slot < n_quads ? desc.z : e_first;
+        if (OWN && tid == 0) not_finite = 0;
         if (lane == 0 && ks == 0) column[wave / KS] = slot < n_quads ? desc.x * 64 : n;
         if (e_first + ks < e_last) {
             const unsigned lane_w = (unsigned)((li & (bs_r - 1)) * row_bytes + (h & (row_bytes / 16 - 1)) * 16);
@@ -203,6 +206,16 @@ __global__ __launch_bounds__(64 * (kWaves + kLoaders), 3) void bsr_mfma_sweep(
             }
         }
         for (; w < n_win - 1; ++w) window_barrier();
+        if constexpr (OWN) {
+            f32x4 all = acc[0][0];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int s = 0; s < SUB; ++s)
+                    if (j + s > 0) all += acc[j][s];
+            const float sum = all.x + all.y + all.z + all.w;
+            if (sum != sum) not_finite = 1;           // behind the barriers of the windows
+        }
     }
 
     // The wavefronts' sums through LDS: added over a quad's wavefronts in order, stored as whole lines of Y.
@@ -235,27 +248,6 @@ __global__ __launch_bounds__(64 * (kWaves + kLoaders), 3) void bsr_mfma_sweep(
 #pragma unroll
                 for (int e = 0; e < EPT; ++e) v[e] += src[e];
             }
-            // An entry of two block-rows multiplies the zeros of the one that does not store the column: an infinity or a
-            // NaN there is no part of its outputs.  Those that came out as NaN are summed again from their own blocks.
-            if (indptr) {                             // uniform
-                bool again = false;
-#pragma unroll
-                for (int e = 0; e < EPT; ++e) again = again || v[e] != v[e];
-                if (again) {
-                    const int bs_c = row_bytes / S;
-                    const T* x = X + (size_t)i * (size_t)k;
-                    const T* w = data + (size_t)(col & 7) * bs_c;
-                    float own[EPT] = {};
-                    for (int b = indptr[col >> 3]; b < indptr[(col >> 3) + 1]; ++b)
-                        for (int u = 0; u < bs_c; ++u) {
-                            const float xv = (float)x[(size_t)indices[b] * bs_c + u];
-#pragma unroll
-                            for (int e = 0; e < EPT; ++e) own[e] += xv * (float)w[((size_t)b * 8 + e) * bs_c + u];
-                        }
-#pragma unroll
-                    for (int e = 0; e < EPT; ++e) v[e] = v[e] != v[e] ? own[e] : v[e];
-                }
-            }
             O* dst = Y + (size_t)i * (size_t)n + col;
             if constexpr (EPT == 4) {
                 *reinterpret_cast<f32x4*>(dst) = f32x4{v[0], v[1], v[2], v[3]};
@@ -267,6 +259,30 @@ __global__ __launch_bounds__(64 * (kWaves + kLoaders), 3) void bsr_mfma_sweep(
                 *reinterpret_cast<o8*>(dst) = r;
             }
         }
+    }
+    // An entry of two block-rows multiplies the zeros of the one that does not store the column: an infinity or a NaN there
+    // is no part of its outputs.  Outputs that came out as NaN are summed again, from their own blocks, by the thread that
+    // has stored them.  (Looked for in the accumulators: in the loop above it takes 0.5 of 10 us.)
+    if (OWN && not_finite) {
+        asm volatile("" ::: "memory");
+        const int bs_c = row_bytes / S;
+        for (int p = 0; p < 16 * SUB / RP; ++p)
+            for (int t = tid; t < Q * RP * TPR; t += 64 * (kWaves + kLoaders)) {
+                const int i = i_base + p * RP + t / TPR % RP, col = column[t / (RP * TPR)] + t % TPR * EPT;
+                if (col >= n || i >= m) continue;
+                O* dst = Y + (size_t)i * (size_t)n + col;
+                for (int e = 0; e < EPT; ++e) {
+                    const float stored = (float)dst[e];
+                    if (stored == stored) continue;
+                    float own = 0.f;
+                    for (int b = indptr[(col + e) >> 3]; b < indptr[((col + e) >> 3) + 1]; ++b) {
+                        const T* x = X + (size_t)i * (size_t)k + (size_t)indices[b] * bs_c;
+                        const T* w = data + ((size_t)b * 8 + ((col + e) & 7)) * bs_c;
+                        for (int c = 0; c < bs_c; ++c) own += (float)x[c] * (float)w[c];
+                    }
+                    dst[e] = from_f32<O>(own);
+                }
+            }
     }
 }
 
@@ -298,7 +314,7 @@ sweep_shape_t choose(const bsr_matrix* W, int64_t m, int q_most, int64_t all_rou
     return best;
 }
 
-template <typename T, typename O, int SUB>
+template <typename T, typename O, int SUB, bool OWN>
 bsr_status launch_sub(const spmm_args& a, int q_log)
 {
     const bsr_matrix* W = a.W;
@@ -310,17 +326,15 @@ bsr_status launch_sub(const spmm_args& a, int q_log)
     const int64_t blocks = (int64_t)padded * n_groups;
     if (blocks >= ((int64_t)1 << 31)) return BSR_ERR_SHAPE;
     constexpr size_t ring = (size_t)kRing * SUB * kPitch, out = (size_t)kWaves * (SUB >= 2 ? kRowsOut : 16) * kLdOut * sizeof(float);
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&bsr_mfma_sweep<T, O, SUB>),
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&bsr_mfma_sweep<T, O, SUB, OWN>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)std::max(ring, out));
     if (attr != hipSuccess) return BSR_ERR_HIP;
-    // where the wavefront kernels would run else, which keep every output to its own blocks
-    const bool own_blocks = W->bs_r == 8 && !mfma_small_supports(W);
-    hipLaunchKernelGGL((bsr_mfma_sweep<T, O, SUB>), dim3((unsigned)blocks), dim3(64 * (kWaves + kLoaders)), std::max(ring, out), a.stream,
+    hipLaunchKernelGGL((bsr_mfma_sweep<T, O, SUB, OWN>), dim3((unsigned)blocks), dim3(64 * (kWaves + kLoaders)), std::max(ring, out), a.stream,
                        (const T*)a.X, (const T*)W->data, (unsigned)(W->nnzb * W->bs_r * W->bs_c * sizeof(T)),
                        reinterpret_cast<const i32x4*>(W->sw_base + W->sw.recs_at), W->sw_base + W->sw.win_at,
                        reinterpret_cast<const i32x4*>(W->sw_base), (O*)a.Y, m, (int)W->k, (int)W->n,
                        n_tiles, padded, W->sw_quads, W->sw_windows, q_log, W->bs_r, W->bs_c * (int)sizeof(T),
-                       own_blocks ? W->indptr : nullptr, W->indices);
+                       W->indptr, W->indices);
     return hipGetLastError() == hipSuccess ? BSR_OK : BSR_ERR_HIP;
 }
 
@@ -341,9 +355,13 @@ bsr_status launch_types(const spmm_args& a, const tune_opts& tune)
     if ((tune.mt == 1 || tune.mt == 2 || tune.mt == 4) && reaches(a.W, tune.mt)) sub = tune.mt;
     if (tune.nw == 1 || tune.nw == 2 || tune.nw == 4 || tune.nw == 8)
         for (q_log = 0; (1 << q_log) < std::min(tune.nw, q_most);) ++q_log;
-    if (sub == 4) return launch_sub<T, O, 4>(a, q_log);
-    if (sub == 2) return launch_sub<T, O, 2>(a, q_log);
-    return launch_sub<T, O, 1>(a, q_log);
+    auto launch = [&](auto own) {
+        constexpr bool OWN = decltype(own)::value;
+        return sub == 4 ? launch_sub<T, O, 4, OWN>(a, q_log) : sub == 2 ? launch_sub<T, O, 2, OWN>(a, q_log) : launch_sub<T, O, 1, OWN>(a, q_log);
+    };
+    // sizes without whole tiles: the wavefront kernels, which would run else, keep every output to its own blocks
+    if (a.W->bs_r == 8 && !mfma_small_supports(a.W)) return launch(std::true_type{});
+    return launch(std::false_type{});
 }
 
 }  // namespace
