@@ -471,7 +471,7 @@ bsr_status bsr_create(bsr_matrix** out, int64_t n, int64_t k, int32_t bs_r, int3
             W->sw_base = const_cast<int32_t*>(W->row_order) + words;
             W->staging.resize(words);
             build_sweep_plan(W, index_pointer_host, block_indices_host, W->staging);
-            words = W->staging.size();                // records of 64 words end it
+            words = W->staging.size();                // a multiple of 64
         }
     }
     size_t upload_words = words;

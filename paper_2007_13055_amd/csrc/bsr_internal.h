@@ -116,8 +116,8 @@ struct bsr_matrix {
     int32_t wide_nq = 0;
     // Sweep kernel (bsr_mfma_sweep.hip; block sides 8 or 16).  Its plan: the quads (64 outputs) by rounds, longest
     // first, {quad, first round, end of its rounds, 0}; at win_at per quad the first round of each window and the end,
-    // [sw_quads][sw_windows + 1]; at recs_at per round 64 words, {byte offset of the values, place of the granule in the
-    // window} for (granule, half of the rows, group of 16 rows).  Where another kernel can stand in for it the first
+    // [sw_quads][sw_windows + 1]; at recs_at per round {byte offset of the values, place of the granule in the window} for
+    // (granule, half of the rows, group of 16 rows), 64 words, without the halves 32 where blocks are 16 rows tall.  Where another kernel can stand in for it the first
     // product that wants it builds it, from the pattern below (an fp32 W of 8-wide blocks that only sees few rows never
     // pays for it); else bsr_create does, as part of what it uploads.
     int32_t* sw_base = nullptr;              // device; null when the kernel cannot take this W

@@ -10,10 +10,10 @@
 //   entry    one group of 16 rows of W times four granules, anywhere in the window: one v_mfma_f32_16x16x32 (fp32: four
 //            16x16x4) per 16 rows of X.  Blocks of 8 rows come two block-rows to an entry: of the 16 x 4 granules 55 % hold
 //            stored values at 20 % density, where 16x16 tiles of W hold 34 %.
-//   round    an entry for each of a quad's four groups.  Its record holds, for each granule and half of the 16 rows, {byte
-//            offset of the values in block_data, place of the granule in the window}; what is not stored has an offset
-//            past the end of W (read as zeros), a granule that is not there the place of a granule of zeros.  A group that
-//            has fewer entries in a window than the others multiplies zeros (fp32: is left out).
+//   round    an entry for each of a quad's four groups.  Its record holds, for each granule and (blocks of 8 rows) half of
+//            the 16 rows, {byte offset of the values in block_data, place of the granule in the window}; what is not stored
+//            has an offset past the end of W (read as zeros), a granule that is not there the place of a granule of zeros.
+//            A group that has fewer entries in a window than the others multiplies zeros (fp32: is left out).
 //   list     a quad's rounds by window: one run of records from end to end, so that records are read two rounds and values
 //            one round ahead whatever the windows hold.
 //
@@ -140,11 +140,12 @@ __global__ __launch_bounds__(64 * (kWaves + kLoaders), 3) void bsr_mfma_sweep(
         if (e_first + ks < e_last) {
             const unsigned lane_w = (unsigned)((li & (bs_r - 1)) * row_bytes + (h & (row_bytes / 16 - 1)) * 16);
             const unsigned lane_x = (unsigned)(li * 128 + turn(li) * 16);
-            const i32x4* __restrict__ rl = recs + (h * 2 + (li >> 3)) * 2;
+            const int halves = bs_r == 8 ? 1 : 0;     // log2 of the parts of a granule's record
+            const i32x4* __restrict__ rl = recs + ((h << halves) + (halves ? li >> 3 : 0)) * 2;
             const int e_max = e_first + ks + (e_last - 1 - e_first - ks) / KS * KS;   // this wavefront's last round
             struct record { i32x4 a, b; };            // {offset, place} of the round's four entries
             auto load_rec = [&](int e) {
-                const i32x4* p = rl + (size_t)min(e, e_max) * 16;
+                const i32x4* p = rl + ((size_t)min(e, e_max) << (3 + halves));
                 return record{p[0], p[1]};
             };
             auto offset = [](const record& r, int j) { return j == 0 ? r.a.x : j == 1 ? r.a.z : j == 2 ? r.b.x : r.b.z; };
@@ -442,6 +443,9 @@ bsr_status launch_mfma_sweep(const spmm_args& a, const tune_opts& t)
 // (6016, 1536), 20 % 45, 63); 16x16 blocks of fp32 wait for the matrix cores wherever they are.
 static bool sweep_shape(int32_t bs_r, int32_t bs_c) { return (bs_r == 8 || bs_r == 16) && (bs_c == 8 || bs_c == 16); }
 
+// Words of a round's record: {offset, place} for four granules of four groups, blocks of 8 rows for two of them each.
+static int round_words(int32_t bs_r) { return bs_r == 8 ? 64 : 32; }
+
 // Words of the plan: {quad, rounds} and the windows' first rounds per quad, and the rounds' records.  A window has as many
 // rounds as the longest of a quad's groups has entries: at worst all of its blocks are in that one.  fp32 makes the most of
 // both: windows of 256 columns, entries of 16; 16x16 blocks are always of a 16-bit type, two to an entry.
@@ -453,7 +457,7 @@ size_t sweep_plan_words(int64_t n, int64_t k, int32_t bs_r, int32_t bs_c, int64_
     // moving all of X through LDS is no gain either
     if (quads * (windows + 1) > 4 * (size_t)nnzb + 65536) return 0;
     const size_t rounds = std::min((size_t)nnzb, (size_t)nnzb / (bs_r == 16 && bs_c == 16 ? 2 : 16 / bs_c) + quads * windows);
-    return 4 * quads + quads * (windows + 1) + 64 * rounds + 2 * 64;
+    return 4 * quads + quads * (windows + 1) + (size_t)round_words(bs_r) * rounds + 3 * 64;
 }
 
 int32_t sweep_windows(const bsr_matrix* W)
@@ -482,7 +486,8 @@ void build_sweep_plan(const bsr_matrix* W, const int32_t* indptr, const int32_t*
     const size_t desc_at = plan.size(), win_at = desc_at + (4 * (size_t)n_quads + 63) / 64 * 64;
     const size_t recs_at = win_at + ((size_t)n_quads * (n_win + 1) + 63) / 64 * 64;
     plan.resize(recs_at, 0);
-    auto rounds_so_far = [&] { return (int32_t)((plan.size() - recs_at) / 64); };
+    const int rec = round_words(bs_r), part = rec / 4;   // words of a round, of a granule in it
+    auto rounds_so_far = [&] { return (int32_t)((plan.size() - recs_at) / (size_t)rec); };
     std::vector<int32_t> ptr((size_t)n_quads * (n_win + 1));
     std::vector<int32_t> load((size_t)n_quads);
     struct stored { int32_t col, at; };               // block-column, number of the stored block
@@ -531,18 +536,19 @@ void build_sweep_plan(const bsr_matrix* W, const int32_t* indptr, const int32_t*
                 rounds = std::max(rounds, (end[j] - at[j] + per_entry - 1) / per_entry);
             }
             const size_t here = plan.size();
-            plan.resize(here + rounds * 64);
+            plan.resize(here + rounds * (size_t)rec);
             int32_t* r = plan.data() + here;
-            for (size_t i = 0; i < rounds * 32; ++i) { r[2 * i] = INT32_MIN; r[2 * i + 1] = kNone; }
+            for (size_t i = 0; i < rounds * (size_t)rec / 2; ++i) { r[2 * i] = INT32_MIN; r[2 * i + 1] = kNone; }
             for (int j = 0; j < 4; ++j) {
                 for (size_t i = at[j]; i < end[j]; ++i) {
                     const slot& s = rows[j][i];
                     const size_t rd = (i - at[j]) / (size_t)per_entry, u = (i - at[j]) % (size_t)per_entry;
                     const int byte = (s.col - w * win_cols) * S, place = byte / 128 * 2048 + byte % 128;   // a block's granules share a slab
-                    int32_t* e = r + rd * 64 + u * (size_t)gran * 16 + j * 2;
-                    for (int v = 0; v < gran; ++v, e += 16) {
-                        e[0] = s.off[0]; e[8] = s.off[1];
-                        e[1] = e[9] = place + v * 16;
+                    int32_t* e = r + rd * (size_t)rec + u * (size_t)(gran * part) + j * 2;
+                    for (int v = 0; v < gran; ++v, e += part) {
+                        e[0] = s.off[0];
+                        e[1] = place + v * 16;
+                        if (bs_r == 8) { e[8] = s.off[1]; e[9] = e[1]; }
                     }
                 }
                 at[j] = end[j];
@@ -562,10 +568,12 @@ void build_sweep_plan(const bsr_matrix* W, const int32_t* indptr, const int32_t*
         d[2] = p[n_win];
         std::copy(p, p + n_win + 1, plan.begin() + (ptrdiff_t)(win_at + (size_t)s * (n_win + 1)));
     }
+    const int32_t all_rounds = rounds_so_far();
+    plan.resize((plan.size() + 63) & ~(size_t)63, 0);
     W->sw.win_at = win_at - desc_at;
     W->sw.recs_at = recs_at - desc_at;
     if (!W->sw.counted.load(std::memory_order_relaxed)) {
-        W->sw.rounds = rounds_so_far();
+        W->sw.rounds = all_rounds;
         W->sw.longest = n_quads ? load[(size_t)order[0]] : 0;
         W->sw.counted.store(true, std::memory_order_release);
     }

@@ -60,6 +60,7 @@ def test_workspace_follows_rows_and_blocks(lib):
     it is below 400 bytes)."""
     for size in (1 << 20, 1 << 22):
         assert lib.bsr_workspace_size(size, size, 8, 8, 10000) < size // 8 * 400 + (16 << 20)
+    assert lib.bsr_workspace_size(8192, 8192, 16, 16, 52429) < 52429 * 250       # a quarter of fp32 values
 
 
 def test_status_strings(lib):

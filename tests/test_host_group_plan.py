@@ -33,3 +33,17 @@ def test_slab_plan_is_consistent(tmp_path):
     out = subprocess.run([exe], capture_output=True, text=True, timeout=300)
     assert out.returncode == 0, out.stdout + out.stderr
     assert "all consistent" in out.stdout
+
+
+def test_sweep_plan_is_consistent(tmp_path):
+    """The sweep kernel's rounds and windows, decoded as its kernel decodes them."""
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    exe = str(tmp_path / "host_sweep_plan_driver")
+    csrc = os.path.join(ROOT, "paper_2007_13055_amd", "csrc")
+    cmd = [hipcc, "--offload-arch=gfx950", "-O1", "-std=c++17", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+           "-Wno-unused-command-line-argument", "-I", os.path.join(ROOT, "include"), "-I", csrc,
+           os.path.join(ROOT, "tests", "host_sweep_plan_driver.cpp"), os.path.join(csrc, "bsr_mfma_sweep.hip"), "-o", exe]
+    subprocess.run(cmd, check=True, capture_output=True, timeout=600)
+    out = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    assert out.returncode == 0, out.stdout + out.stderr
+    assert "all consistent" in out.stdout
