@@ -757,37 +757,46 @@ def test_sibling_product_through_transposed_handle(oracle_mod, case):
 def test_small_blocks_on_matrix_cores(oracle_mod, monkeypatch, extra, dtype, bs):
     """Blocks below the MFMA tile grouped into 16x16 tiles of W: every shape and type, empty and long
     tile-rows (more entries than a descriptor's inline columns), duplicates (a second block at a taken
-    position opens a second entry), a ragged last m-tile, and the wave path on the same handle."""
+    position opens a second entry), a ragged last m-tile, and the wave path on the same handle.  16-bit types
+    have tiles only for long, thin rows of W (2048 columns, 80 blocks per 16 rows); which kernel ran shows in the
+    bits of an fp32 result, which differ from the sweep kernel's."""
     import paper_2007_13055_amd as lib
-    if extra:
-        monkeypatch.setenv("BSR_SPMM_TUNE", extra)
     bs_r, bs_c = bs
-    R, C = 12 * (16 // bs_r), 40 * (16 // bs_c)
+    R, C = 12 * (16 // bs_r), 130 * (16 // bs_c)
     rng = np.random.default_rng(bs_r * 3 + bs_c)
     counts = rng.integers(0, 12, size=R)
     counts[0] = counts[1] = 0                      # an empty tile-row (its block-rows are empty)
-    counts[2] = counts[3] = C                      # a full one: 40 entries > 28 inline columns
+    counts[2] = counts[3] = C                      # a full one: 130 entries > 28 inline columns
     counts[-1] = 1
+
+    def tuned(settings):
+        monkeypatch.setenv("BSR_SPMM_TUNE", settings) if settings else monkeypatch.delenv("BSR_SPMM_TUNE", raising=False)
+
     for m in (16, 45, 300):
         p = wl.make_problem("sm", m, C * bs_c, R * bs_r, bs_r, bs_c, dtype, dtype, ("counts", counts), ("normal", 1.0),
                             ("normal", 1.0), 1000 + m + bs_r)
         Yo, So = oracle_of(oracle_mod, p)
+        tuned(extra and "variant=7," + extra)
         Yg, W = gpu_product(p, path=MFMA)
         assert lib.bsr_query_path(W, m) == MFMA
         check(Yg, Yo, So, p.tau, f"small {bs} {dtype} m={m} {extra}", out_dtype=dtype)
+        Yf, _ = gpu_product(p, path=MFMA, W=W, y_dtype="f32")
+        check(Yf, Yo, So, p.tau, f"small {bs} {dtype}->f32 m={m} {extra}")
         Yw, _ = gpu_product(p, path=WAVE, W=W)
         check(Yw, Yo, So, p.tau, f"small {bs} {dtype} m={m} wave", out_dtype=dtype)
+        tuned("variant=6")
+        swept, _ = gpu_product(p, path=MFMA, y_dtype="f32")
+        assert np.array_equal(Yf, swept) == (not extra and m == 300 and dtype != "f32")
     # duplicates and unsorted block-columns
     ptr = np.array([0, 3, 3, 5, 6], dtype=np.int32)
     idx = np.array([2, 2, 0, 1, 1, 3], dtype=np.int32)
     data = wl.round_to_storage(rng.normal(size=(6, bs_r, bs_c)).astype(np.float32), dtype)
-    X = wl.round_to_storage(rng.normal(size=(33, 4 * bs_c)).astype(np.float32), dtype)
-    n4 = 4 * bs_r
-    if n4 % 16 == 0 and (4 * bs_c) % 16 == 0:
-        q = wl.Problem("dup", 33, 4 * bs_c, n4, bs_r, bs_c, dtype, dtype, X, data, idx, ptr)
-        Yo, So = oracle_of(oracle_mod, q)
-        Yg, _ = gpu_product(q, path=MFMA)
-        check(Yg, Yo, So, q.tau, f"small {bs} {dtype} duplicates", out_dtype=dtype)
+    X = wl.round_to_storage(rng.normal(size=(33, C * bs_c)).astype(np.float32), dtype)
+    q = wl.Problem("dup", 33, C * bs_c, 4 * bs_r, bs_r, bs_c, dtype, dtype, X, data, idx, ptr)
+    Yo, So = oracle_of(oracle_mod, q)
+    tuned("variant=7," + extra)
+    Yg, _ = gpu_product(q, path=MFMA)
+    check(Yg, Yo, So, q.tau, f"small {bs} {dtype} duplicates", out_dtype=dtype)
 
 
 def test_small_blocks_need_whole_tiles():
