@@ -393,7 +393,13 @@ bsr_status bsr_create(bsr_matrix** out, int64_t n, int64_t k, int32_t bs_r, int3
                        n % 16 == 0 && k % 16 == 0 && nnzb > 0 &&
                        nnzb * bs_r * bs_c * (dtype == BSR_F32 ? 4 : 2) < ((int64_t)1 << 31);
     if (small) W->sb_rows = (int32_t)(n / 16);
-    if (small && (dtype == BSR_F32 || small_blocks_16bit(W, 16) || !sweep_takes(W))) {
+    if (sweep_takes(W)) {
+        W->sw_words = sweep_plan_words(n, k, bs_r, bs_c, nnzb);
+        W->sw_quads = (int32_t)((n + 63) / 64);
+        W->sw_windows = sweep_windows(W);
+    }
+    if (small && (dtype == BSR_F32 || !W->sw_words || sweep_leaves_tiles(W, index_pointer_host, block_indices_host))) {
+        W->sb_max_entries = 0;
         const int SR = 16 / bs_r, SC = 16 / bs_c;
         const int64_t TR = n / 16;
         const int32_t blk_bytes = bs_r * bs_c * (dtype == BSR_F32 ? 4 : 2);
@@ -425,6 +431,7 @@ bsr_status bsr_create(bsr_matrix** out, int64_t n, int64_t k, int32_t bs_r, int3
             std::stable_sort(list.begin(), list.end(), [](const entry& a, const entry& b) { return a.tc < b.tc; });
             n_entries += list.size();
         }
+        W->sb_tiles = (int64_t)n_entries;
         std::vector<int32_t> order((size_t)TR);
         std::iota(order.begin(), order.end(), 0);
         std::stable_sort(order.begin(), order.end(),
@@ -462,17 +469,12 @@ bsr_status bsr_create(bsr_matrix** out, int64_t n, int64_t k, int32_t bs_r, int3
     build_group_plan(W, index_pointer_host, block_indices_host, &words);
     build_thinrow_plan(W, index_pointer_host, block_indices_host, &words);
     build_wide_plan(W, index_pointer_host, block_indices_host, &words);
-    if (sweep_takes(W)) {
-        W->sw_words = sweep_plan_words(n, k, bs_r, bs_c, nnzb);
-        W->sw_quads = (int32_t)((n + 63) / 64);
-        W->sw_windows = sweep_windows(W);
-        W->sw_created = small && !W->sb_desc;         // nothing else stands in for it
-        if (W->sw_created) {
-            W->sw_base = const_cast<int32_t*>(W->row_order) + words;
-            W->staging.resize(words);
-            build_sweep_plan(W, index_pointer_host, block_indices_host, W->staging);
-            words = W->staging.size();                // a multiple of 64
-        }
+    if (W->sw_words && small && !W->sb_desc) {        // nothing else stands in for it
+        W->sw_created = true;
+        W->sw_base = const_cast<int32_t*>(W->row_order) + words;
+        W->staging.resize(words);
+        build_sweep_plan(W, index_pointer_host, block_indices_host, W->staging);
+        words = W->staging.size();                    // a multiple of 64
     }
     size_t upload_words = words;
     {   // the per-m tables sit behind everything else, 256-byte aligned

@@ -21,7 +21,7 @@ constexpr int kRowDescCols = kRowDescWords - kRowDescColsAt;
 constexpr int kMaxKsplitItems = 4096;             // the k-split kernel is used below this many (block-row, m-tile) items
 constexpr int kStripeChunkPairs = 3;              // the stripe kernel's pair table lists block-rows in chunks of this many pairs
 constexpr int kThinRange = 256;                   // columns between the positions kept for thin blocks
-constexpr int kSweepRowsF32 = 384;                // fp32 blocks below the MFMA tile: the sweep kernel from here on
+constexpr int kSweepRowsF32 = 384;                // fp32 blocks below the MFMA tile: no sweep below
 constexpr int kItemSlots = 4;                     // k-split work-item tables a handle keeps (one per recent m)
 
 // Development knobs, read from the environment variable BSR_SPMM_TUNE ("key=value,key=value"), and
@@ -33,7 +33,7 @@ constexpr int kItemSlots = 4;                     // k-split work-item tables a 
 //            started first; stripe a = block-row groups; thin a = groups of 4 blocks in flight
 //            thin blocks: variant 1 = transposed copy in scratch + gather, 2 = rows of X staged in LDS
 //            (a = slots per wavefront)
-//            8-wide blocks and 16-bit 16x16: variant 6 = sweep (mt = 16-row tiles, nw = quads per workgroup); 8-wide: 7 = 16x16 tiles (fp32)
+//            8-wide blocks and 16-bit 16x16: variant 6 = sweep (mt = 16-row tiles, nw = quads per workgroup); 8-wide: 7 = 16x16 tiles
 //   sd       sampled product: 1 a workgroup per block (thin: X transposed), 2 groups of blocks that share slabs (thin: turned over in LDS)
 struct tune_opts {
     int variant = 0, nw = 0, mt = 0, a = 0, b = 0, sd = 0;
@@ -144,7 +144,7 @@ struct bsr_matrix {
     int device = 0;                          // that device
     tune_opts env_tune;                      // BSR_SPMM_TUNE as it was when the handle was created
     // Blocks smaller than an MFMA tile (bs_r, bs_c in {8,16}, not both 16; n and k multiples of 16; 16-bit types: only
-    // where small_blocks_16bit() may want it or the sweep kernel does not take W), grouped into 16x16 tiles of W (see bsr_create): descriptors of the tile-rows, longest first,
+    // where sweep_leaves_tiles() or the sweep kernel does not take W), grouped into 16x16 tiles of W (see bsr_create): descriptors of the tile-rows, longest first,
     // [sb_rows][kRowDescWords] = {tile-row, first entry, entries, 0, first tile-columns}; per entry the
     // byte offsets of the tile's blocks in block_data, [entries][4] (2^31: no block there), and its
     // tile-column, [entries].
@@ -172,7 +172,9 @@ struct bsr_matrix {
     const int32_t* sb_desc = nullptr;
     const int32_t* sb_entries = nullptr;
     const int32_t* sb_cols = nullptr;
-    int32_t sb_rows = 0, sb_max_entries = 0; // tile-rows (set where there are no tables too)
+    int32_t sb_rows = 0;                     // tile-rows (set where there are no tables too)
+    int32_t sb_max_entries = 0;              // of the longest tile-row
+    int64_t sb_tiles = 0;                    // entries of all of them
     int32_t max_row_blocks = 0;              // longest block-row
     int32_t long_rows = 0;                   // leading slots whose block count is > 4x the mean and > 8 ("long" bin)
     int32_t empty_rows = 0;                  // block-rows with no stored block
@@ -270,19 +272,15 @@ void build_wide_plan(bsr_matrix* W, const int32_t* index_pointer_host, const int
 size_t wide_plan_words(int64_t R, int64_t k, int64_t nnzb, int32_t bs_r, int32_t bs_c);
 bsr_status launch_mfma_small(const spmm_args& a, const tune_opts& t);   // bs_r, bs_c in {8,16}, not both 16
 bool mfma_small_supports(const bsr_matrix* W);
-// 16-bit blocks: few workgroups over long, thin rows of W, where the sweep kernel's windows, one after the other, take longer
-// than 16x16 tiles dealt out to wavefronts (us of the tiles and the sweep: 97 x (256, 4160), 65 blocks per 16 rows, 4.8,
-// 5.7; 64 x (512, 4096), 51 blocks, 4.5, 5.5, 205 blocks 8.4, 6.6; 17 x (1024, 2048), 102 blocks, 5.7, 4.9).
-inline bool small_blocks_16bit(const bsr_matrix* W, int64_t m)
-{
-    const int64_t tile_rows = W->n / 16;
-    return (m + 15) / 16 * tile_rows <= 128 && W->k >= 2048 && W->nnzb <= 80 * tile_rows;
-}
 // The same blocks, many rows of X: swept in windows of columns that a workgroup's outputs share through LDS.  n and k may
 // be any multiples of 8.  BSR_ERR_UNSUPPORTED without a launch where sweep_ready() is false.
 bsr_status launch_mfma_sweep(const spmm_args& a, const tune_opts& t);
 bool mfma_sweep_supports(const bsr_matrix* W);
-bool sweep_is_quicker(const bsr_matrix* W, int64_t m, bsr_dtype y_dtype, bool than_stripes);   // 16x16 blocks
+// Whether the sweep kernel takes less time, by estimates, than the kernel that would run else.
+enum class sweep_rival { ksplit, stripes, tiles };
+bool sweep_is_quicker(const bsr_matrix* W, int64_t m, bsr_dtype y_dtype, sweep_rival than);
+// 16-bit W with a side of 8: whether some m leaves it to the kernel of 16x16 tiles, so that those are listed (may throw).
+bool sweep_leaves_tiles(bsr_matrix* W, const int32_t* index_pointer_host, const int32_t* block_indices_host);
 bool sweep_takes(const bsr_matrix* W);              // by its shape, type and sizes
 // Appends the plan to `out` and fills W->sw; may throw.
 void build_sweep_plan(const bsr_matrix* W, const int32_t* index_pointer_host, const int32_t* block_indices_host, std::vector<int32_t>& out);

@@ -220,7 +220,8 @@ bsr_status launch_mfma(const spmm_args& a, const tune_opts& tune)
         else if (a.W->mean_row_blocks > 4.0) variant = 2;
         // one block-row long beside short ones, which a wavefront of the direct kernel would walk alone
         else variant = (long_row = a.W->max_row_blocks >= 16 && mfma_ksplit_reaches(a.W)) ? 2 : 1;
-        if ((variant == 2 || variant == 4) && sweep_is_quicker(a.W, a.m, a.y_dtype, variant == 4)) {
+        if ((variant == 2 || variant == 4) && a.W->bs_r == 16 && a.W->bs_c == 16 &&
+            sweep_is_quicker(a.W, a.m, a.y_dtype, variant == 4 ? sweep_rival::stripes : sweep_rival::ksplit)) {
             const bsr_status st = launch_mfma_sweep(a, t);
             if (st != BSR_ERR_UNSUPPORTED) return st; // else its plan is not there
         }

@@ -211,16 +211,14 @@ bsr_status launch_small_types(const spmm_args& a, const tune_opts& t)
 
 bool mfma_small_supports(const bsr_matrix* W) { return W->sb_rows > 0; }
 
-// Many rows, and most products of 16-bit blocks, go to the sweep kernel, which reads X once for 64 to 512 outputs instead
-// of 16 (microseconds of this kernel and that one, 8x8 blocks: bf16 17 x (512, 512) 3.9, 3.8; 260 x (512, 4096), 10 %
-// 9.6, 5.8; 2000 x (6016, 640), 20 % 82, 20.  fp32 waits for the matrix cores in both: 100 x (512, 512) 4.0, 5.2;
-// 260 x (512, 4096), 10 % 13.8, 13.0; 700 x the same 23.5, 19.6; 2000 x (4096, 1024), 5 % 50, 34).
+// Many rows, and many products of 16-bit blocks, go to the sweep kernel, which reads X once for 64 to 512 outputs instead
+// of 16, where estimates of both have it ahead (fp32 from 384 rows on).
 bsr_status launch_mfma_small(const spmm_args& a, const tune_opts& tune)
 {
     const bsr_matrix* W = a.W;
     tune_opts t = tune;
     if (!mfma_small_supports(W)) return BSR_ERR_UNSUPPORTED;
-    const bool sweep = t.variant == 6 || (t.variant != 7 && (W->dtype == BSR_F32 ? a.m >= kSweepRowsF32 : !small_blocks_16bit(W, a.m)));
+    const bool sweep = t.variant == 6 || (t.variant != 7 && (W->dtype != BSR_F32 || a.m >= kSweepRowsF32) && sweep_is_quicker(W, a.m, a.y_dtype, sweep_rival::tiles));
     if (!W->sb_desc || (sweep && mfma_sweep_supports(W))) {
         const bsr_status st = launch_mfma_sweep(a, t);
         if (st != BSR_ERR_UNSUPPORTED || !W->sb_desc) return st;

@@ -369,59 +369,122 @@ bsr_status launch_types(const spmm_args& a, const tune_opts& tune)
 
 bool mfma_sweep_supports(const bsr_matrix* W) { return W->sw_base != nullptr; }
 
-// Rounds of all quads and of the longest of a W of 16x16 blocks, without its plan: a window has as many as half of the
-// blocks of the block-row with the most, rounded up.
+// Rounds of all quads and of the longest, without the plan (a window has as many as the longest of a quad's groups has
+// entries), and the 16x16 tiles of W that hold a block, of all tile-rows and of the longest.  May throw.
+struct sweep_counts { int64_t rounds, longest, tiles; int32_t longest_tiles; };
+static sweep_counts count_plan(const bsr_matrix* W, const int32_t* indptr, const int32_t* indices)
+{
+    const int row_bytes = W->bs_c * (W->dtype == BSR_F32 ? 4 : 2), per_entry = 64 / row_bytes;
+    const int per_window = kSlabs * 128 / row_bytes, per_tile = 16 / W->bs_c;      // block-columns
+    std::vector<int32_t> most((size_t)W->sw_windows), mine((size_t)W->sw_windows), first(W->bs_r == 8 ? (size_t)W->C : 0);
+    std::vector<int32_t> tile_of((size_t)(W->C / per_tile + 1), -1);
+    sweep_counts c{0, 0, 0, 0};
+    for (int32_t q = 0; q < W->sw_quads; ++q) {
+        std::fill(most.begin(), most.end(), 0);
+        for (int32_t g = 4 * q; g < 4 * q + 4; ++g) {
+            std::fill(mine.begin(), mine.end(), 0);
+            int32_t tiles = 0;
+            const int32_t r = g * (16 / W->bs_r);
+            auto row = [&](int32_t rr, auto visit) {
+                if (rr >= W->R) return;
+                for (int32_t p = indptr[rr]; p < indptr[rr + 1]; ++p) visit(indices[p]);
+            };
+            auto count = [&](int32_t col, bool opens) {
+                mine[(size_t)(col / per_window)] += opens;
+                int32_t& t = tile_of[(size_t)(col / per_tile)];
+                tiles += t != g;
+                t = g;
+            };
+            row(r, [&](int32_t col) { count(col, true); if (W->bs_r == 8) ++first[(size_t)col]; });
+            if (W->bs_r == 8) {                       // the second block-row's block shares the first's slot of that column
+                row(r + 1, [&](int32_t col) { int32_t& f = first[(size_t)col]; count(col, f == 0); f -= f > 0; });
+                row(r, [&](int32_t col) { first[(size_t)col] = 0; });
+            }
+            for (size_t w = 0; w < mine.size(); ++w) most[w] = std::max(most[w], (mine[w] + per_entry - 1) / per_entry);
+            c.tiles += tiles;
+            c.longest_tiles = std::max(c.longest_tiles, tiles);
+        }
+        const int64_t rounds = std::accumulate(most.begin(), most.end(), (int64_t)0);
+        c.rounds += rounds;
+        c.longest = std::max(c.longest, rounds);
+    }
+    return c;
+}
+
+// The same for the choice of a product, once per handle; false if there is no memory for it.
 static bool count_rounds(const bsr_matrix* W)
 {
     if (W->sw.counted.load(std::memory_order_acquire)) return true;
     std::lock_guard<std::mutex> lock(W->sw_mu);
     if (W->sw.counted.load(std::memory_order_relaxed)) return true;
-    const int per_window = kSlabs * 128 / 2 / 16;     // block-columns
-    std::vector<int32_t> most, mine;
     try {
-        most.resize((size_t)W->sw_windows);
-        mine.resize((size_t)W->sw_windows);
+        const sweep_counts c = count_plan(W, W->sl_indptr.data(), W->sl_indices.data());
+        W->sw.rounds = c.rounds;
+        W->sw.longest = c.longest;
     } catch (const std::bad_alloc&) {
         return false;
     }
-    int64_t all = 0, longest = 0;
-    for (int32_t q = 0; q < W->sw_quads; ++q) {
-        std::fill(most.begin(), most.end(), 0);
-        for (int32_t r = 4 * q; r < std::min(4 * q + 4, W->R); ++r) {
-            std::fill(mine.begin(), mine.end(), 0);
-            for (int32_t p = W->sl_indptr[(size_t)r]; p < W->sl_indptr[(size_t)r + 1]; ++p) ++mine[(size_t)(W->sl_indices[(size_t)p] / per_window)];
-            for (size_t w = 0; w < mine.size(); ++w) most[w] = std::max(most[w], mine[w]);
-        }
-        int64_t rounds = 0;
-        for (int32_t c : most) rounds += (c + 1) / 2;
-        all += rounds;
-        longest = std::max(longest, rounds);
-    }
-    W->sw.rounds = all;
-    W->sw.longest = longest;
     W->sw.counted.store(true, std::memory_order_release);
     return true;
 }
 
-// The choice for 16x16 blocks between this kernel and the one that would run else, from estimates in microseconds fitted to
-// 225 bf16 products (16 .. 8192 rows, sides 128 .. 8192, 3 to 30 %, uniform and power law).  Half of the estimates are
-// within 5 % (this kernel), 8 % (k-split) and 9 % (stripes) of the time and nine tenths within 16, 31 and 36 %, so this
-// kernel is taken only where its own is lower by a quarter, against stripes by three tenths: of those and 268 other products
-// 65 are, up to 5 times quicker and none slower (a fifth lower: 96, five of them 4 to 28 % slower).
-bool sweep_is_quicker(const bsr_matrix* W, int64_t m, bsr_dtype y_dtype, bool than_stripes)
+// Microseconds of the kernel that would run else.
+// Stripes: X staged, Y stored, products, and a term for the rows' length.  k-split: stored blocks and block-rows of every tile
+// of 16 rows (its X comes from L2 or beyond once per stored block), and the longest block-row.  16x16 tiles: workgroups,
+// tiles of W (more where X is past L2: each fetches its own), and the longest tile-row's share of a wavefront.
+static double rival_us(const bsr_matrix* W, int64_t m, sweep_rival than)
 {
-    if (W->bs_r != 16 || W->bs_c != 16 || !mfma_sweep_supports(W)) return false;
-    const double tiles = (double)((m + 15) / 16);
-    // stripes: X staged, Y stored, products, and a term for the rows' length; k-split: stored blocks and block-rows of every
-    // tile of 16 rows (its X comes from L2 or beyond once per stored block), and the longest block-row
-    const double other = than_stripes ? 4.6 + 6.3e-7 * (double)(m * W->k) + 4.7e-7 * (double)(m * W->n) + 2.3e-5 * tiles * (double)W->nnzb + 2.9e-3 * (double)W->k
-                                      : 4.1 + 0.84e-4 * tiles * (double)W->nnzb + 3.7e-4 * tiles * W->R + 2.7e-2 * W->max_row_blocks;
-    auto quicker = [&](int64_t rounds, int64_t longest) {
-        const double sweep = 2.8 + 1.03 * choose(W, m, most_quads(W, m, y_dtype == BSR_F32), rounds, longest).us + 2.1e-6 * tiles * (double)W->n;
-        return sweep < (than_stripes ? 0.7 : 0.75) * other;
-    };
+    const double mt = (double)((m + 15) / 16);
+    if (than == sweep_rival::stripes)
+        return 4.6 + 6.3e-7 * (double)(m * W->k) + 4.7e-7 * (double)(m * W->n) + 2.3e-5 * mt * (double)W->nnzb + 2.9e-3 * (double)W->k;
+    if (than == sweep_rival::ksplit) return 4.1 + 0.84e-4 * mt * (double)W->nnzb + 3.7e-4 * mt * W->R + 2.7e-2 * W->max_row_blocks;
+    const double items = mt * W->sb_rows, tiles = mt * (double)W->sb_tiles;
+    const double chain = (double)W->sb_max_entries / std::max(1, std::min(items > 1024 ? 2 : items > 256 ? 4 : 8, (W->sb_max_entries + 1) / 2));
+    const double x = (double)(m * W->k);
+    if (W->dtype == BSR_F32) return 2.5 + 4e-4 * items + (7.4e-5 + 1.74e-4 * x / (x + 1.25e8)) * tiles + 0.257 * chain * (1 + 16.3 * x / (x + 1.25e8));
+    return 2.5 + 4e-4 * items + (5.1e-5 + 5e-5 * std::min(1.0, x / 3.2e7)) * tiles + 0.244 * chain;
+}
+
+// The choice between this kernel and the one that would run else, from estimates in microseconds.
+// 16x16 blocks, fitted to 225 bf16 products (16 .. 8192 rows, sides 128 .. 8192, 3 to 30 %, uniform and power law): half of
+// the estimates are within 5 % (this kernel), 8 % (k-split) and 9 % (stripes) of the time and nine tenths within 16, 31 and
+// 36 %, so this kernel is taken only where its own is lower by a quarter, against stripes by three tenths: of those and 268
+// other products 65 are, up to 5 times quicker and none slower (a fifth lower: 96, five of them 4 to 28 % slower).
+// Blocks with a side of 8, fitted to half of 4000 products of the same ranges: half of the estimates within 4 % (this
+// kernel), 5 % (tiles), fp32 8 and 6 %, nine tenths within 14, 15, 21 and 17 %.  On the other half, 16-bit: of 1011 products 14
+// are more than 5 % slower than with the kernel of tiles and 7 than with this one (this one for all but long, thin rows of
+// W: 240, up to 1.7 times as slow, 3.3 us where tiles take 2.5).  fp32 from 384 rows on: of 475 13 and 50 (this one for all: 151,
+// up to 2.4 times as slow; 647 x (128, 960), 3.4 %, tiles 3.6, this one 5.5; 1073 x (832, 192), 4.1 % 4.4, 7.0).
+static bool quicker(const bsr_matrix* W, int64_t m, bsr_dtype y_dtype, sweep_rival than, int64_t rounds, int64_t longest)
+{
+    const double us = choose(W, m, most_quads(W, m, y_dtype == BSR_F32), rounds, longest).us, out = (double)((m + 15) / 16) * (double)W->n;
+    if (than == sweep_rival::tiles)
+        return W->dtype == BSR_F32 ? 2.4 + 0.775 * us + 6.3e-6 * out < 0.95 * rival_us(W, m, than) : 1.64 + us + 2.9e-6 * out < rival_us(W, m, than);
+    return 2.8 + 1.03 * us + 2.1e-6 * out < (than == sweep_rival::stripes ? 0.7 : 0.75) * rival_us(W, m, than);
+}
+
+bool sweep_is_quicker(const bsr_matrix* W, int64_t m, bsr_dtype y_dtype, sweep_rival than)
+{
+    if (!mfma_sweep_supports(W)) return false;
     // with as few rounds as that many blocks can have; only then are they counted
-    return quicker((W->nnzb + 7) / 8, (W->max_row_blocks + 1) / 2) && count_rounds(W) && quicker(W->sw.rounds, W->sw.longest);
+    const int slots = 64 / (W->bs_c * (W->dtype == BSR_F32 ? 4 : 2));   // block-columns of an entry
+    if (!W->sw.counted.load(std::memory_order_acquire) &&
+        (!quicker(W, m, y_dtype, than, W->nnzb / (4 * slots * (16 / W->bs_r)), W->max_row_blocks / slots) || !count_rounds(W)))
+        return false;
+    return quicker(W, m, y_dtype, than, W->sw.rounds, W->sw.longest);
+}
+
+bool sweep_leaves_tiles(bsr_matrix* W, const int32_t* indptr, const int32_t* indices)
+{
+    const sweep_counts c = count_plan(W, indptr, indices);
+    W->sw.rounds = c.rounds;
+    W->sw.longest = c.longest;
+    W->sw.counted.store(true, std::memory_order_release);
+    W->sb_tiles = c.tiles;
+    W->sb_max_entries = c.longest_tiles;
+    for (int64_t m : {16, 32, 64, 128, 256, 512, 1024})
+        if (!quicker(W, m, W->dtype, sweep_rival::tiles, c.rounds, c.longest)) return true;
+    return false;
 }
 
 bsr_status launch_mfma_sweep(const spmm_args& a, const tune_opts& t)

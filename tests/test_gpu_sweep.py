@@ -118,11 +118,11 @@ def test_tuning_of_sizes_without_whole_tiles(oracle_mod, out):
     check(Y, Yo, So, p.tau, f"tuned {out}", out_dtype=out)
 
 
-@pytest.mark.parametrize("dtype,m,R,C,tiles", [("f32", 383, 24, 60, True), ("f32", 384, 24, 60, False), ("f16", 32, 128, 256, True),
-                                               ("f16", 33, 128, 256, False), ("bf16", 32, 128, 256, True), ("bf16", 33, 128, 256, False)])
+@pytest.mark.parametrize("dtype,m,R,C,tiles", [("f32", 383, 80, 200, True), ("f32", 384, 80, 200, False), ("f32", 400, 24, 60, True),
+                                               ("f16", 64, 64, 64, True), ("f16", 600, 64, 64, False),
+                                               ("bf16", 64, 42, 66, True), ("bf16", 600, 42, 66, False)])
 def test_which_kernel(oracle_mod, monkeypatch, dtype, m, R, C, tiles):
-    """Both sides of the rules between the sweep kernel and the one of 16x16 tiles, told by the bits.  (A 16-bit W with fewer
-    columns or more blocks has no tiles.)"""
+    """Both sides of the rules between the sweep kernel and the one of 16x16 tiles, told by the bits."""
     import paper_2007_13055_amd as lib
     p = _problem(m, R, C, (8, 8), dtype, "f32", 9)
     Yo, So = oracle_mod.bsr_spmm(p.X, p.block_data, p.block_indices, p.index_pointer, p.n)

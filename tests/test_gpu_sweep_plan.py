@@ -9,9 +9,10 @@ from gpu_util import check, to_device, torch_dtype
 
 pytestmark = pytest.mark.gpu
 
-# dtype, result, rows, blocks, block-rows, block-columns, blocks per block-row: products that the sweep kernel takes
-SHAPES = {"16x16": ("f16", "f32", 600, (16, 16), 96, 376, 40), "8x8 fp32": ("f32", "f32", 400, (8, 8), 24, 60, 20),
-          "8x8 16-bit": ("bf16", "f32", 203, (8, 8), 66, 68, 20), "odd sizes": ("f16", "f16", 203, (8, 8), 67, 67, 20)}
+# dtype, result, rows, blocks, block-rows, block-columns, blocks per block-row: products that the sweep kernel takes;
+# "created": no other matrix-core kernel for any number of rows, and bsr_create builds the plan
+SHAPES = {"16x16": ("f16", "f32", 600, (16, 16), 96, 376, 40), "8x8 fp32": ("f32", "f32", 400, (8, 8), 64, 128, 40),
+          "8x8 16-bit": ("bf16", "f32", 203, (8, 8), 66, 68, 20), "created": ("bf16", "f32", 203, (8, 8), 512, 128, 40), "odd sizes": ("f16", "f16", 203, (8, 8), 67, 67, 20)}
 
 
 def _case(oracle_mod, shape):
@@ -95,7 +96,7 @@ def test_first_products_of_several_threads(oracle_mod, monkeypatch, shape):
     assert all(torch.equal(Y, want) for Y in ys)
 
 
-@pytest.mark.parametrize("shape", ["16x16", "8x8 fp32", "odd sizes"])
+@pytest.mark.parametrize("shape", ["16x16", "8x8 fp32", "8x8 16-bit", "odd sizes"])
 def test_built_by_the_first_product_that_wants_it(oracle_mod, monkeypatch, shape):
     """A handle that only sees few rows has no such plan: a granule that is not there has the place 0xFFFF, which no other
     table holds."""
@@ -113,7 +114,7 @@ def test_built_by_the_first_product_that_wants_it(oracle_mod, monkeypatch, shape
         assert bool((words == 0xFFFF).any()) == there
 
 
-@pytest.mark.parametrize("shape", ["8x8 fp32", "8x8 16-bit"])
+@pytest.mark.parametrize("shape", ["8x8 fp32", "created"])
 def test_debug_mode_checks_the_plan(oracle_mod, monkeypatch, shape):
     """BSR_SPMM_DEBUG=1: a damaged word of the plan, sent by the first product or by bsr_create, is reported and nothing is
     stored; repaired, the product is the oracle's again."""
