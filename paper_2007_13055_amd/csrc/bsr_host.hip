@@ -409,6 +409,7 @@ bsr_status bsr_create(bsr_matrix** out, int64_t n, int64_t k, int32_t bs_r, int3
         std::vector<int32_t> from((size_t)(k / 16), -1);   // the tile-row's first entry of each tile-column
         for (int64_t tr = 0; tr < TR; ++tr) {
             auto& list = rows[(size_t)tr];
+            list.reserve((size_t)(index_pointer_host[(tr + 1) * SR] - index_pointer_host[tr * SR]));
             for (int qa = 0; qa < SR; ++qa) {
                 const int64_t r = tr * SR + qa;
                 for (int32_t p = index_pointer_host[r]; p < index_pointer_host[r + 1]; ++p) {
@@ -428,7 +429,8 @@ bsr_status bsr_create(bsr_matrix** out, int64_t n, int64_t k, int32_t bs_r, int3
                 }
             }
             for (const auto& e : list) from[(size_t)e.tc] = -1;
-            std::stable_sort(list.begin(), list.end(), [](const entry& a, const entry& b) { return a.tc < b.tc; });
+            auto by_column = [](const entry& a, const entry& b) { return a.tc < b.tc; };
+            if (!std::is_sorted(list.begin(), list.end(), by_column)) std::stable_sort(list.begin(), list.end(), by_column);
             n_entries += list.size();
         }
         W->sb_tiles = (int64_t)n_entries;
