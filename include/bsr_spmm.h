@@ -201,8 +201,8 @@ bsr_status bsr_tune(bsr_matrix* W, int64_t m, const void* X_dev, void* Y_dev, bs
 /*
  * What bsr_tune() remembered for (m, y_dtype): settings_out = {kernel family (bsr_path), matrix-core
  * kernel variant (0 the library's choice, 1 direct, 2 k-split, 3 LDS tiles, 4 LDS stripe, 5 row groups for
- * the longest block-rows and LDS tiles for the others), wavefronts
- * per workgroup, tile setting, two per-variant settings}, 0 = the kernel's default; us_out (may be
+ * the longest block-rows and LDS tiles for the others, 6 the sweep kernel for sides of 8 and 16, 7 16x16 tiles of
+ * 8-wide blocks), wavefronts (variant 6: groups of 64 outputs) per workgroup, tile setting, two per-variant settings}, 0 = the kernel's default; us_out (may be
  * NULL) its measured microseconds per product.  BSR_ERR_UNSUPPORTED if nothing is remembered.
  */
 bsr_status bsr_tune_result(const bsr_matrix* W, int64_t m, bsr_dtype y_dtype, int32_t settings_out[6], float* us_out);
