@@ -19,6 +19,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 template <typename O> __device__ __forceinline__ O from_f32(float v);
 template <> __device__ __forceinline__ float from_f32<float>(float v) { return v; }
@@ -30,6 +31,16 @@ template <> __device__ __forceinline__ bf16_t from_f32<bf16_t>(float v) { return
 // reasons about one lane, and may otherwise keep an operand it read before ("this lane stored nothing since")
 // or move a read in front of the lane's own write to another address.  No instruction is emitted.
 __device__ __forceinline__ void wave_lds_fence() { asm volatile("" ::: "memory"); }
+
+// Loads that write LDS by themselves, and the wait for all but the last N of them.
+namespace lds_loads {
+template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+// 16 bytes per lane from buffer `rsrc` at the lane's offset to LDS bytes [lds_base, + 1024) in lane order.
+__device__ __forceinline__ void load_to_lds(const i32x4& rsrc, unsigned offset, unsigned lds_base)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_base), "v"(offset), "s"(rsrc) : "memory");
+}
+}  // namespace lds_loads
 
 // A lane's operand: CH contiguous elements of type T, kept as 32-bit words.
 template <typename T, int CH>

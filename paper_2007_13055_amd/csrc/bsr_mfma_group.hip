@@ -106,11 +106,7 @@ constexpr int kMaxGroups = 2;
 constexpr int kLookAhead = GRP_LOOK;                  // how far behind a window's first block-column the plan looks for more to fill it
 static_assert(kRingWin * kWin <= kSlots && (kRingWin == 2 || kRingWin == 3) && kWin <= 9, "the windows fit the ring; a record lists at most 9 tiles");
 
-template <int N>
-__device__ __forceinline__ void wait_vm()
-{
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
+using lds_loads::wait_vm;
 
 // Returns when at most the `loads` youngest loads of this wavefront are still in flight.
 __device__ __forceinline__ void wait_all_but(int loads)

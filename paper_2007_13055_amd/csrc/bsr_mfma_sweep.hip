@@ -20,12 +20,14 @@
 // Twelve wavefronts: eight multiply, each a quad or every KS-th round of one (the shares are added in fixed order at the
 // end), four only move X into a ring of two windows (loads that write LDS directly, one barrier per window).
 //
-// What bounds it: the LDS reads of X (16 KiB a round and wavefront; 832 of the 1000-1180 clocks that a round of eight
-// wavefronts takes, counters: LDS busy 38 %, matrix cores 32 % of a whole 16-bit product); fp32 the matrix cores.  Windows
-// of 512 columns rather than 256: 54 against 63 us, values two rounds ahead 55, progress words polled in LDS in place of
-// the barrier 56, twelve multiplying wavefronts 54 (bf16 8x8, 5889 x (1216, 5184), 21.8 %).
-// Measured (us, with the kernel of 16x16 tiles and now): that product 432, 54; fp16 8x8, 2662 x (832, 6528), 19.3 % 181,
-// 32; fp16, 2285 x (6016, 1536), 15.6 %, power law 163, 37; fp32 8x8, 3607 x (320, 5056), 7.3 % 83, 47.
+// What bounds it: no unit by itself.  Counters, as shares of the kernel's clocks (bf16 8x8, 5889 x (1216, 5184), 21.8 %): LDS
+// busy 42 (12 of them bank conflicts: an entry's four granules lie anywhere), matrix cores 26, and a wavefront issues in 20
+// of 100 of its clocks; two multiplying wavefronts a SIMD do not cover the chain of a round (record, values, X, MFMAs) and the
+// barrier of a window.  fp32 8x8: LDS 17, matrix cores 26.  bf16 16x16, 3540 x (5184, 1536): 23 and 21, and its 168 workgroups
+// leave 88 CUs without one.  Windows of 512 columns take 0.86 of the time of windows of 256; values two rounds ahead, progress
+// words polled in LDS in place of the barrier, and twelve multiplying wavefronts gain nothing.
+// Measured (us in graph replays, with the kernel that ran before and now): that product 393, 61; fp16 8x8, 2662 x (832, 6528),
+// 19.3 % 145, 31; fp16 8x8, 2285 x (6016, 1536), 15.6 %, power law 286, 49; fp32 8x8, 3607 x (320, 5056), 7.3 % 58, 52.
 #include <algorithm>
 #include <cmath>
 #include <numeric>
@@ -33,6 +35,7 @@
 #include "bsr_mfma_common.h"
 
 using namespace bsr_dev;
+using namespace bsr_dev::lds_loads;
 
 namespace {
 
@@ -48,14 +51,6 @@ constexpr int kXcds = 8;
 constexpr int kRowsOut = 32;                          // rows of Y per pass of the epilogue
 constexpr int kLdOut = 64 + 4;                        // floats of a row there
 
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-
-template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
-// 16 bytes per lane from buffer `rsrc` at the lane's offset to LDS bytes [lds_base, + 1024) in lane order.
-__device__ __forceinline__ void load_to_lds(const i32x4& rsrc, unsigned offset, unsigned lds_base)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_base), "v"(offset), "s"(rsrc) : "memory");
-}
 // The 16-byte pieces of row r of a slab are stored XOR turn(r): sixteen rows' pieces of one column fill all banks once
 // (measured: 6.4 clocks a read, as contiguous ones; 8.2 with r mod 8, 16 unturned).
 __device__ __forceinline__ constexpr unsigned turn(unsigned r) { return (r >> 1) & 7; }

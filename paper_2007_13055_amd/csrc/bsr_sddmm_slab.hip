@@ -41,6 +41,7 @@
 #include "bsr_mfma_common.h"
 
 using namespace bsr_dev;
+using namespace bsr_dev::lds_loads;
 
 namespace {
 
@@ -56,8 +57,6 @@ constexpr int kHdrSlabsAt = 4;
 constexpr int kXcds = 8;
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-
 // Chunk shape and chunks per wavefront by tile size and block shape.
 struct slab_shape { int V, CR, CC, NCH; };
 inline slab_shape slab_shape_of(int bs_r, int bs_c)
@@ -67,12 +66,6 @@ inline slab_shape slab_shape_of(int bs_r, int bs_c)
     return {16, 1, 4, 5};
 }
 
-template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
-// 16 bytes per lane from buffer `rsrc` at the lane's offset to LDS bytes [lds_base, + 1024) in lane order.
-__device__ __forceinline__ void load_to_lds(const i32x4& rsrc, unsigned offset, unsigned lds_base)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(lds_base), "v"(offset), "s"(rsrc) : "memory");
-}
 
 template <typename T, int V>
 __device__ __forceinline__ int sigma(int r)
