@@ -680,7 +680,7 @@ static std::vector<tuned_choice> tune_candidates(const bsr_matrix* W, int64_t m,
         if (W->scratch && W->scratch_bytes >= mfma_thin_scratch_bytes(W, m) && m >= 16)
             for (int a : {4, 6, 8, 10, 12, 14, 16}) add(BSR_PATH_MFMA, 1, 0, 0, a, 0);
     } else if (mfma_small_supports(W) || (mfma_sweep_supports(W) && !mfma_supports(W))) {
-        if (m >= 8 && mfma_small_supports(W) && W->dtype == BSR_F32)
+        if (m >= 8 && W->sb_desc)
             for (int nw : {2, 4, 8})
                 for (int per : {1, 2, 4}) add(BSR_PATH_MFMA, 7, nw, 0, per, 0);
         if (m >= 8 && (mfma_small_supports(W) || sweeps_odd_sizes(W, m, y_dtype)))

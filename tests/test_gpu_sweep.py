@@ -118,6 +118,20 @@ def test_tuning_of_sizes_without_whole_tiles(oracle_mod, out):
     check(Y, Yo, So, p.tau, f"tuned {out}", out_dtype=out)
 
 
+@pytest.mark.parametrize("dtype,R,C,tiles", [("f16", 64, 64, True), ("f32", 64, 64, True), ("f16", 768, 128, False)])
+def test_tuning_offers_both_kernels(oracle_mod, dtype, R, C, tiles):
+    """Trials of 8-wide blocks: nine settings of the kernel of 16x16 tiles where W has those, and twelve of the sweep kernel."""
+    import paper_2007_13055_amd as lib
+    from gpu_util import to_device
+    p = _problem(100, R, C, (8, 8), dtype, dtype, 4)
+    W = lib.bsr_create(p.n, p.k, p.block_data, p.block_indices, p.index_pointer, dtype=dtype)
+    tried, _ = lib.bsr_tune(W, to_device(p.X, dtype), trials=2)
+    assert tried == (21 if tiles else 12)
+    Yo, So = oracle_mod.bsr_spmm(p.X, p.block_data, p.block_indices, p.index_pointer, p.n)
+    Y, _ = gpu_product(p, W=W)
+    check(Y, Yo, So, p.tau, dtype, out_dtype=dtype)
+
+
 @pytest.mark.parametrize("dtype,m,R,C,tiles", [("f32", 383, 80, 200, True), ("f32", 384, 80, 200, False), ("f32", 400, 24, 60, True),
                                                ("f16", 64, 64, 64, True), ("f16", 600, 64, 64, False),
                                                ("bf16", 64, 42, 66, True), ("bf16", 600, 42, 66, False)])
