@@ -55,7 +55,7 @@ typedef enum {
     BSR_ERR_ALIGN = 6,       /* a device pointer is not 16-byte aligned */
     BSR_ERR_WORKSPACE = 7,   /* workspace smaller than bsr_workspace_size() reports, or the chosen kernel needs
                                 scratch (bsr_scratch_size) that has not been lent with bsr_set_scratch */
-    BSR_ERR_HIP = 8,         /* a HIP runtime call failed (launch, copy) */
+    BSR_ERR_HIP = 8,         /* a HIP runtime call failed (launch, copy), or bsr_create() found no host memory for its plan */
     BSR_ERR_UNSUPPORTED = 9, /* the requested kernel path cannot handle this block shape */
     BSR_ERR_SCRATCH_LIMIT = 10 /* bsr_spmm_static(): the product needs more scratch than the library's built-in
                                   BSR_STATIC_SCRATCH_BYTES */

@@ -4,6 +4,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <memory>
 #include <string>
 #include <new>
 #include <numeric>
@@ -265,7 +266,7 @@ bsr_status bsr_workspace_size(int64_t n, int64_t k, int32_t bs_r, int32_t bs_c, 
     return BSR_OK;
 }
 
-bsr_status bsr_create(bsr_matrix** out, int64_t n, int64_t k, int32_t bs_r, int32_t bs_c, int64_t nnzb,
+static bsr_status create(bsr_matrix** out, int64_t n, int64_t k, int32_t bs_r, int32_t bs_c, int64_t nnzb,
                       bsr_dtype dtype, const void* block_data_dev,
                       const int32_t* block_indices_dev, const int32_t* index_pointer_dev,
                       const int32_t* block_indices_host, const int32_t* index_pointer_host,
@@ -284,8 +285,8 @@ bsr_status bsr_create(bsr_matrix** out, int64_t n, int64_t k, int32_t bs_r, int3
     const int64_t R = n / bs_r;
     if (workspace_bytes < plan_bytes(R, nnzb, bs_r, bs_c, k)) return BSR_ERR_WORKSPACE;
 
-    bsr_matrix* W = new (std::nothrow) bsr_matrix();
-    if (!W) return BSR_ERR_HIP;
+    std::unique_ptr<bsr_matrix> held(new bsr_matrix());
+    bsr_matrix* const W = held.get();
     W->n = n; W->k = k; W->nnzb = nnzb; W->bs_r = bs_r; W->bs_c = bs_c;
     W->R = (int32_t)R; W->C = (int32_t)(k / bs_c);
     W->dtype = dtype;
@@ -501,7 +502,7 @@ bsr_status bsr_create(bsr_matrix** out, int64_t n, int64_t k, int32_t bs_r, int3
         }
     }
     // the plan must fit what bsr_workspace_size promised (its bound is per block-row and per stored block)
-    if (sizeof(int32_t) * words > workspace_bytes) { delete W; return BSR_ERR_WORKSPACE; }
+    if (sizeof(int32_t) * words > workspace_bytes) return BSR_ERR_WORKSPACE;
     words = upload_words;
     {
         const char* dbg = std::getenv("BSR_SPMM_DEBUG");
@@ -512,7 +513,7 @@ bsr_status bsr_create(bsr_matrix** out, int64_t n, int64_t k, int32_t bs_r, int3
     if (R > 0) {
         hipError_t e = hipMemcpyAsync(workspace_dev, W->staging.data(), sizeof(int32_t) * words,
                                       hipMemcpyHostToDevice, (hipStream_t)hip_stream);
-        if (e != hipSuccess) { delete W; return BSR_ERR_HIP; }
+        if (e != hipSuccess) return BSR_ERR_HIP;
         if (hipEventCreateWithFlags(&W->plan_uploaded, hipEventDisableTiming) == hipSuccess)
             (void)hipEventRecord(W->plan_uploaded, (hipStream_t)hip_stream);
         else
@@ -522,8 +523,22 @@ bsr_status bsr_create(bsr_matrix** out, int64_t n, int64_t k, int32_t bs_r, int3
     // thin blocks: look up the built-in scratch array's address for this device now, so that
     // bsr_spmm_static() has no set-up left to do
     if (mfma_thin_supports(W)) (void)mfma_thin_static_scratch(nullptr);
-    *out = W;
+    *out = held.release();
     return BSR_OK;
+}
+
+bsr_status bsr_create(bsr_matrix** out, int64_t n, int64_t k, int32_t bs_r, int32_t bs_c, int64_t nnzb,
+                      bsr_dtype dtype, const void* block_data_dev,
+                      const int32_t* block_indices_dev, const int32_t* index_pointer_dev,
+                      const int32_t* block_indices_host, const int32_t* index_pointer_host,
+                      void* workspace_dev, size_t workspace_bytes, void* hip_stream)
+{
+    try {
+        return create(out, n, k, bs_r, bs_c, nnzb, dtype, block_data_dev, block_indices_dev, index_pointer_dev,
+                      block_indices_host, index_pointer_host, workspace_dev, workspace_bytes, hip_stream);
+    } catch (const std::bad_alloc&) {                 // no host memory for the plan
+        return BSR_ERR_HIP;
+    }
 }
 
 void bsr_destroy(bsr_matrix* W)

@@ -146,6 +146,33 @@ def test_plan_fits_the_promised_workspace(lib, bs_r, bs_c, dtype, pattern):
     assert st == 7
 
 
+def test_create_without_host_memory_is_a_status(lib):
+    """The address space runs out while the plan is built: BSR_ERR_HIP, no exception through the C interface."""
+    code = ("import ctypes, resource, sys\n"
+            "import numpy as np\n"
+            "import paper_2007_13055_amd as lib\n"
+            "so = lib.load_library()\n"
+            "R = C = 1024\n"
+            "ptr = np.arange(R + 1, dtype=np.int32) * 300\n"
+            "idx = np.tile(np.arange(300, dtype=np.int32) * 3, R)\n"
+            "need = lib.bsr_workspace_size(R * 8, C * 8, 8, 8, len(idx))\n"
+            "buf = np.zeros(64, dtype=np.uint8)\n"
+            "at = (buf.ctypes.data + 15) & ~15\n"
+            "h = ctypes.c_void_p()\n"
+            "def create(code):\n"
+            "    return so.bsr_create(ctypes.byref(h), R * 8, C * 8, 8, 8, len(idx), code, at, idx.ctypes.data, ptr.ctypes.data,\n"
+            "                         idx.ctypes.data, ptr.ctypes.data, at, need, None)\n"
+            "used = int(open('/proc/self/statm').read().split()[0]) * resource.getpagesize()\n"
+            "for more in (1 << 20, 8 << 20, 20 << 20):\n"
+            "    for code in (0, 1):\n"
+            "        resource.setrlimit(resource.RLIMIT_AS, (used + more, resource.RLIM_INFINITY))\n"
+            "        assert create(code) == 8 and not h\n"
+            "print('survived')\n")
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=120,
+                       env=dict(os.environ, HIP_VISIBLE_DEVICES="-1"))
+    assert r.returncode == 0 and "survived" in r.stdout, r.stdout + r.stderr
+
+
 def test_pattern_checks_need_no_torch(lib):
     """bsr_validate, bsr_workspace_size and bsr_transpose_pattern work on host arrays: neither torch nor the native
     module of the binding has to be there."""
