@@ -268,9 +268,12 @@ bsr_status launch_stripe_types(const spmm_args& a, const tune_opts& tune)
     // read W less often; too few leave CUs idle while a stripe is staged)
     int tm = tune.mt > 0 ? tune.mt * 16 : (m >= 32 * 64 ? 64 : (m >= 32 * 32 ? 32 : 16));
     while (tm > 16 && !mfma_stripe_supports(W, tm)) tm /= 2;      // wide X: a shorter stripe still fits LDS
-    if (tm == 16) return go(std::integral_constant<int, 16>{});
-    if (tm == 32) return go(std::integral_constant<int, 32>{});
-    return go(std::integral_constant<int, 64>{});
+    // that was asked for fp32 results; the wavefronts' areas for 16-bit ones are a little larger from 32 rows on (12 of them:
+    // 54 KiB against 51), and where a stripe of that height does not fit with them, nothing has been launched
+    bsr_status st = BSR_ERR_UNSUPPORTED;
+    if (tm == 64) st = go(std::integral_constant<int, 64>{});
+    if (tm >= 32 && st == BSR_ERR_UNSUPPORTED) st = go(std::integral_constant<int, 32>{});
+    return st == BSR_ERR_UNSUPPORTED ? go(std::integral_constant<int, 16>{}) : st;
 }
 
 }  // namespace

@@ -989,3 +989,17 @@ def test_debug_mode_checks_device_arrays_before_every_product(oracle_mod, monkey
     D = torch.zeros((p.nnzb, 32, 32), dtype=torch.float16, device="cuda")
     assert so.bsr_sddmm(W.handle, p.m, G.data_ptr(), X.data_ptr(), D.data_ptr(), 1, stream) == 4
     idx[1] = int(p.block_indices[1])
+
+
+@pytest.mark.parametrize("dtype,out", [("f16", "f16"), ("bf16", "bf16"), ("bf16", "f32")])
+@pytest.mark.parametrize("m,k", [(2048, 816), (2048, 832), (2048, 848), (1030, 1616), (1030, 1632), (1030, 1664), (1030, 1680)])
+@pytest.mark.parametrize("path", [0, MFMA])
+def test_stripe_at_the_limits_of_lds(oracle_mod, monkeypatch, dtype, out, m, k, path):
+    """The widths at which a stripe of 64 and of 32 rows fits LDS with the areas of twelve wavefronts, and the next ones, for
+    16-bit results (which need more) and fp32 ones: the library's choice, and the stripe kernel by name."""
+    if path == MFMA:
+        monkeypatch.setenv("BSR_SPMM_TUNE", "variant=4")
+    p = wl.make_problem("stripe", m, k, 360 * 16, 16, 16, dtype, out, ("counts", np.arange(360) % 5), ("normal", 1.0), ("normal", 1.0), k)
+    Yo, So = oracle_of(oracle_mod, p)
+    Y, _ = gpu_product(p, path=path)
+    check(Y, Yo, So, p.tau, f"stripe {dtype}->{out} m={m} k={k}", out_dtype=out)
