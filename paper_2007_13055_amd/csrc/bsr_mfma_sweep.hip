@@ -444,7 +444,8 @@ static double rival_us(const bsr_matrix* W, int64_t m, sweep_rival than)
 // 16x16 blocks, fitted to 225 bf16 products (16 .. 8192 rows, sides 128 .. 8192, 3 to 30 %, uniform and power law): half of
 // the estimates are within 5 % (this kernel), 8 % (k-split) and 9 % (stripes) of the time and nine tenths within 16, 31 and
 // 36 %, so this kernel is taken only where its own is lower by a quarter, against stripes by three tenths: of those and 268
-// other products 65 are, up to 5 times quicker and none slower (a fifth lower: 96, five of them 4 to 28 % slower).
+// other products 65 are, up to 5 times quicker and none slower (a fifth lower: 96, five of them 4 to 28 % slower); of 809
+// drawn afterwards 90 are more than a tenth quicker and four slower, by 8 to 36 % (2624 x (1440, 3008), 11 %: stripes 15.9 us).
 // Blocks with a side of 8, fitted to half of 4000 products of the same ranges: half of the estimates within 4 % (this
 // kernel), 5 % (tiles), fp32 8 and 6 %, nine tenths within 14, 15, 21 and 17 %.  On the other half, 16-bit: of 1011 products 14
 // are more than 5 % slower than with the kernel of tiles and 7 than with this one (this one for all but long, thin rows of
